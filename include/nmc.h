@@ -172,8 +172,10 @@ typedef struct {
 
 typedef struct {
   int blocks_per_cu;   /* resident work-groups per compute unit for the persistent grid (0 = auto) */
-  int chunk;           /* points taken per work-queue grab (>= 1) */
-  int persistent;      /* 1: persistent grid with an atomic work queue; 0: one work-group per chunk */
+  int chunk;           /* most points taken per work-queue grab (>= 1); short batches take fewer */
+  int persistent;      /* 1: persistent grid with an atomic work queue (with blocks_per_cu 0, batches of a few
+                        * rounds of the chip get one work-group per point or pair instead); 0: one work-group per
+                        * chunk */
   int kernel_store;    /* NMC_KERNELS_ON_CHIP or NMC_KERNELS_HBM (see below) */
 } nmc_launch;
 

@@ -453,14 +453,9 @@ static int solve_batch_impl(const char* who, const nmc_model* m, const nmc_solve
   a.n_outer = out->n_outer;
   a.n_inner = out->n_inner;
   a.status = out->status;
-  a.chunk = L.chunk;
   a.kstore = kstore;
   hipStream_t s = (hipStream_t)stream;
-  if (L.persistent) {
-    a.queue = (int*)ws;
-    hipError_t e = nmc::launch_reset_counter(a.queue, s);
-    if (e != hipSuccess) return hip_fail(e, "counter reset");
-  }
+  if (L.persistent) a.queue = (int*)ws;  // the launcher clears the counters where it uses them
   const bool coupled = (m->host.flags & (NMC_NES | NMC_PAIR)) != 0;
   hipError_t e = nmc::launch_forward(a, m->host.nq, m->host.ns, coupled, m->host.fd_projection != 0, L, m->num_cu, s);
   if (e == hipErrorInvalidValue)
@@ -553,13 +548,8 @@ int nmc_solve_batch_v(const nmc_model* m, const nmc_solver_params* prm, int64_t 
   a.n_outer = out->n_outer;
   a.n_inner = out->n_inner;
   a.status = out->status;
-  a.chunk = L.chunk;
   hipStream_t s = (hipStream_t)stream;
-  if (L.persistent) {
-    a.queue = (int*)ws;
-    hipError_t e = nmc::launch_reset_counter(a.queue, s);
-    if (e != hipSuccess) return hip_fail(e, "solve_batch_v: counter reset");
-  }
+  if (L.persistent) a.queue = (int*)ws;
   const bool coupled = (m->host.flags & (NMC_NES | NMC_PAIR)) != 0;
   const bool phi1 = coupled && (m->host.phi1_nes != 0.0 || m->host.phi1_pair != 0.0);
   // two points per wavefront unless the one-point kernel is asked for; both

@@ -581,11 +581,11 @@ struct PointSolver {
   }
 };
 
-template <int NS, int NQ, bool COUPLED, int KM>
+template <int NS, int NQ, bool COUPLED, int KM, bool QUEUE>
 __global__ __launch_bounds__(kLanes, KM == 1 ? 3 : 2) void fwd_kernel(FwdArgs a) {
   __shared__ WaveLds<NS, KM> S;
   load_model(a.mdl, a.theta, S.m);
-  if (a.queue) {
+  if constexpr (QUEUE) {
     WorkQueue wq(a.queue, a.P, a.chunk);
     for (int64_t g; (g = wq.next()) >= 0;) {
       const int64_t b0 = uniform64(g * a.chunk);
@@ -604,31 +604,16 @@ __global__ void reset_counter_kernel(int* c) {
 }
 
 template <int NS, int NQ, bool COUPLED, int KM>
-hipError_t launch_fwd_t(const FwdArgs& a, const nmc_launch& L, int num_cu, hipStream_t s) {
-  auto kern = fwd_kernel<NS, NQ, COUPLED, KM>;
-  int64_t grid;
-  if (a.queue) {
-    int bpc = L.blocks_per_cu;
-    if (bpc <= 0) {
-      // occupancy of this kernel variant, queried once per process
-      static int occ = 0;
-      if (occ <= 0) {
-        int o = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, kern, kLanes, 0) != hipSuccess || o <= 0) o = 8;
-        // the query under-reports resident one-wave work-groups; a surplus is
-        // harmless (late work-groups find the queue drained and exit)
-        occ = o < 16 ? 16 : o;
-      }
-      bpc = occ;
-    }
-    grid = (int64_t)bpc * num_cu;
-    const int64_t need = (a.P + a.chunk - 1) / a.chunk;
-    if (grid > need) grid = need;
-  } else {
-    grid = (a.P + a.chunk - 1) / a.chunk;
+hipError_t launch_fwd_t(FwdArgs a, const nmc_launch& L, int num_cu, hipStream_t s) {
+  const LaunchPlan lp = plan_launch(L, a.P, KM == 1 ? 12 : 8, num_cu);
+  a.chunk = lp.chunk;
+  auto kern = fwd_kernel<NS, NQ, COUPLED, KM, false>;
+  if (lp.queue) {
+    const hipError_t e = launch_reset_counter(a.queue, s);
+    if (e != hipSuccess) return e;
+    kern = fwd_kernel<NS, NQ, COUPLED, KM, true>;
   }
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kLanes), 0, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)lp.grid), dim3(kLanes), 0, s, a);
   return hipGetLastError();
 }
 

@@ -68,20 +68,21 @@ struct PairSolver {
 
   // settle() is called once the pair's inputs are loaded (work-queue hook)
   template <class Settle>
-  __device__ static void solve(const FwdArgs& a, int64_t u, PairLds<NS>& S, Settle&& settle) {
-    const_ptr<DevModel> md = scalar_ptr(a.mdl);
+  __device__ static void solve(int64_t u, PairLds<NS>& S, Settle&& settle) {
+    const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
+    const_ptr<DevModel> md = scalar_ptr(a->mdl);
     const ModelLds& mt = S.m;
     const int lane = threadIdx.x;
     const int h = lane >> 5, q0 = lane & 31;
-    const double dtau = a.dtau;
+    const double dtau = a->dtau;
     // point of this half; past the end of an odd batch the half mirrors its
     // neighbour and stores nothing
     const int64_t p_raw = 2 * u + h;
-    const bool has_point = p_raw < a.P;
+    const bool has_point = p_raw < a->P;
     const int64_t p = has_point ? p_raw : p_raw - 1;
     const int64_t base = p * (int64_t)(NS * NQ);
-    const double rho = a.rho11[p];
-    const bool fixedT = a.prm.fixed_matter && a.T_fixed;
+    const double rho = in_global(a->rho11)[p];
+    const bool fixedT = a->prm.fixed_matter && a->T_fixed;
     typename PairLds<NS>::Pt& pt = S.pt[h];
     // ||D_c^[k,1]||_W^2 of the current inner loop for this lane's species
     // class c (spread_conv_sums; zero beyond NS), in a register
@@ -92,8 +93,8 @@ struct PairSolver {
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
       const int64_t o = base + md->ext[t] * NQ + q0;
-      Dst[t] = D[t] = a.D0[o];
-      Ist[t] = I[t] = a.I0[o];
+      Dst[t] = D[t] = in_global(a->D0)[o];
+      Ist[t] = I[t] = in_global(a->I0)[o];
     }
     settle();
 
@@ -104,11 +105,11 @@ struct PairSolver {
     pt.K = md->kcoup / rho;
     pt.An = (md->flags & NMC_NES) ? mt.theta[NQ] * rho : 0.0;
     pt.Ap = (md->flags & NMC_PAIR) ? mt.theta[NQ + 1] * rho : 0.0;
-    pt.ye_st = pt.y[0] = a.ye0[p];
-    pt.e_st = pt.y[1] = a.e0[p];
-    pt.chi0 = a.chi0 ? a.chi0[p] : md->chi_ref * rho;
-    if (fixedT) pt.T_fix = a.T_fixed[p];
-    if (a.prm.fixed_matter && a.mu_fixed) pt.mu_fix = a.mu_fixed[p];
+    pt.ye_st = pt.y[0] = in_global(a->ye0)[p];
+    pt.e_st = pt.y[1] = in_global(a->e0)[p];
+    pt.chi0 = a->chi0 ? in_global(a->chi0)[p] : md->chi_ref * rho;
+    if (fixedT) pt.T_fix = in_global(a->T_fixed)[p];
+    if (a->prm.fixed_matter && a->mu_fixed) pt.mu_fix = in_global(a->mu_fixed)[p];
 #pragma unroll
     for (int i = 0; i < 2; ++i) pt.oq[i] = pt.of[i] = pt.odq[i] = pt.odf[i] = 0.0;
     {
@@ -126,8 +127,9 @@ struct PairSolver {
     int k_done = 0, total_inner = 0;
     double T_last = 0.0;  // temperature of the last outer iteration this half ran
 
-    for (int k = 1; k <= a.prm.max_outer && __builtin_amdgcn_ballot_w64(run) != 0; ++k) {
-      const_ptr<DevModel> md = scalar_ptr(a.mdl);
+    for (int k = 1; k <= a->prm.max_outer && __builtin_amdgcn_ballot_w64(run) != 0; ++k) {
+      const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
+      const_ptr<DevModel> md = scalar_ptr(a->mdl);
       const int q = opaque(q0);
       if (run) k_done = k;
       // ---- ComputeOpacities(y^[k]) --------------------------------------
@@ -137,7 +139,7 @@ struct PairSolver {
       // evaluated per lane once per outer iteration
       const double T = fixedT ? pt.T_fix
                               : (y1 - md->eos_b * ye43(y0) * r3) * rcp_nr(md->eos_a * (1.0 + y0));
-      const double mu = (a.prm.fixed_matter && a.mu_fixed)
+      const double mu = (a->prm.fixed_matter && a->mu_fixed)
                             ? pt.mu_fix
                             : md->mu_a * (y0 - md->mu_ye0) * r3 + md->mu_b * log_pos(T * md->inv_mu_t0);
       if (run && (!(T > 0.0) || !(y0 >= 0.0) || !isfinite(T) || !isfinite(mu))) {
@@ -159,7 +161,7 @@ struct PairSolver {
       double pD[PROJ ? NS : 1], pC[PROJ ? NS : 1];
       if constexpr (PROJ) {
 #pragma unroll
-        for (int t = 0; t < NS; ++t) fdp::projected_node(a.mdl, q, Tu, md->imusign[t] * muu, pD[t], pC[t]);
+        for (int t = 0; t < NS; ++t) fdp::projected_node(a->mdl, q, Tu, md->imusign[t] * muu, pD[t], pC[t]);
       }
       double dsig = 0.0;  // dtau sigma: 1 + dtau kappa = 1 + dtau chi + dsig
       {
@@ -270,7 +272,9 @@ struct PairSolver {
       bool act = run;        // this half is still iterating the inner loop
       bool cvd = false;      // this half's inner loop converged
       int l_done = 0;
-      for (int l = 1; l <= a.prm.max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
+      const int m_inner = held(a->prm.m_inner), max_inner = held(a->prm.max_inner);
+      const double tol2 = held(a->tol_inner2);
+      for (int l = 1; l <= max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
         if (act) l_done = l;
         double etaN[NS], outN[NS], annP[NS], etaP[NS];
 #pragma unroll
@@ -356,7 +360,7 @@ struct PairSolver {
           Fx[NS + t] = Qx[NS + t] - I[t];
         }
         // Anderson step over min(l, M_inner) residuals (difference form)
-        const int mem = l < a.prm.m_inner ? l : a.prm.m_inner;
+        const int mem = l < m_inner ? l : m_inner;
         double Xn[2 * NS];
         if (mem == 1) {
           // the older difference column is weighted zero at the second
@@ -422,7 +426,7 @@ struct PairSolver {
           double dm2[1], dn2;
           spread_conv_sums<NS, 2>(vm, vn, dm2, dn2);
           const double dref2 = dref0 > dn2 ? dref0 : dn2;
-          const bool conv = !half_any(!(dm2[0] <= a.tol_inner2 * dref2));
+          const bool conv = !half_any(!(dm2[0] <= tol2 * dref2));
           // ||D^[k,*]|| is the reference of the next inner loop
           dref = (act && conv) ? dn2 : dref;
           if (act) {
@@ -475,13 +479,13 @@ struct PairSolver {
           yq1 = pt.e_st - pt.K * s[1];
         }
       }
-      if (a.prm.fixed_matter) {
+      if (a->prm.fixed_matter) {
         if (run) outer_conv = true;
         run = false;
       }
       if (run) {
         const double f0 = yq0 - pt.y[0], f1 = yq1 - pt.y[1];
-        const int omem = k < a.prm.m_outer ? k : a.prm.m_outer;
+        const int omem = k < a->prm.m_outer ? k : a->prm.m_outer;
         double yn0, yn1;
         if (omem == 1) {
           yn0 = yq0;
@@ -512,8 +516,8 @@ struct PairSolver {
           run = false;
         } else {
           // Algorithm outerConverged: componentwise against y*
-          const bool oc = fabs(yn0 - pt.y[0]) <= a.prm.tol_outer * fabs(pt.ye_st) &&
-                          fabs(yn1 - pt.y[1]) <= a.prm.tol_outer * fabs(pt.e_st);
+          const bool oc = fabs(yn0 - pt.y[0]) <= a->prm.tol_outer * fabs(pt.ye_st) &&
+                          fabs(yn1 - pt.y[1]) <= a->prm.tol_outer * fabs(pt.e_st);
           pt.y[0] = yn0;
           pt.y[1] = yn1;
           if (oc) {
@@ -529,6 +533,8 @@ struct PairSolver {
     }
 
     // ---- outputs --------------------------------------------------------
+    const_ptr<FwdArgs> ao = kernel_args<FwdArgs>();
+    const_ptr<DevModel> mo = scalar_ptr(ao->mdl);
     const double ye_st = pt.ye_st, e_st = pt.e_st;
     double ye_out = ye_st, e_out = e_st, T_out = T_last;
     {
@@ -537,85 +543,70 @@ struct PairSolver {
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
         const double dd = D[t] - Dst[t];
-        mv[0] += md->ig[t] * w2 * dd;
-        mv[1] += md->imult[t] * w3 * dd;
+        mv[0] += mo->ig[t] * w2 * dd;
+        mv[1] += mo->imult[t] * w3 * dd;
       }
       half_own_sums<1>(mv, s);
       if (skip) {
-        T_out = fixedT ? pt.T_fix : (e_st - md->eos_b * ye43(ye_st) * pt.r3) / (md->eos_a * (1.0 + ye_st));
-      } else if (!a.prm.fixed_matter) {
+        T_out = fixedT ? pt.T_fix : (e_st - mo->eos_b * ye43(ye_st) * pt.r3) / (mo->eos_a * (1.0 + ye_st));
+      } else if (!ao->prm.fixed_matter) {
         ye_out = ye_st - pt.K * s[0];
         e_out = e_st - pt.K * s[1];
-        T_out = (e_out - md->eos_b * ye43(ye_out) * pt.r3) / (md->eos_a * (1.0 + ye_out));
+        T_out = (e_out - mo->eos_b * ye43(ye_out) * pt.r3) / (mo->eos_a * (1.0 + ye_out));
       } else if (status == NMC_STATUS_EOS_DOMAIN) {
-        T_out = fixedT ? pt.T_fix : (e_st - md->eos_b * ye43(ye_st) * pt.r3) / (md->eos_a * (1.0 + ye_st));
+        T_out = fixedT ? pt.T_fix : (e_st - mo->eos_b * ye43(ye_st) * pt.r3) / (mo->eos_a * (1.0 + ye_st));
       }
     }
     if (has_point) {
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
-        const int64_t o = base + md->ext[t] * NQ + q0;
-        a.D[o] = D[t];
-        a.I[o] = I[t];
+        const int64_t o = base + mo->ext[t] * NQ + q0;
+        in_global(ao->D)[o] = D[t];
+        in_global(ao->I)[o] = I[t];
       }
       if (q0 == 0) {
-        a.ye[p] = ye_out;
-        a.e[p] = e_out;
-        a.T[p] = T_out;
-        a.n_outer[p] = skip ? 0 : k_done;
-        a.n_inner[p] = total_inner;
-        a.status[p] = status;
+        in_global(ao->ye)[p] = ye_out;
+        in_global(ao->e)[p] = e_out;
+        in_global(ao->T)[p] = T_out;
+        in_global(ao->n_outer)[p] = skip ? 0 : k_done;
+        in_global(ao->n_inner)[p] = total_inner;
+        in_global(ao->status)[p] = status;
       }
     }
     __syncthreads();
   }
 };
 
-template <int NS, bool COUPLED, bool PROJ>
+template <int NS, bool COUPLED, bool PROJ, bool QUEUE>
 __global__ __launch_bounds__(kLanes, 2) void fwd_pair_kernel(FwdArgs a) {
   __shared__ PairLds<NS> S;
   load_model(a.mdl, a.theta, S.m);
   const int64_t pairs = (a.P + 1) / 2;
-  if (a.queue) {
+  if constexpr (QUEUE) {
     WorkQueue wq(a.queue, pairs, a.chunk);
     for (int64_t g; (g = wq.next()) >= 0;) {
       const int64_t b0 = uniform64(g * a.chunk);
       const int64_t end = uniform64(b0 + a.chunk < pairs ? b0 + a.chunk : pairs);
-      for (int64_t u = b0; u < end; ++u) PairSolver<NS, COUPLED, PROJ>::solve(a, u, S, [&] { wq.settle(); });
+      for (int64_t u = b0; u < end; ++u) PairSolver<NS, COUPLED, PROJ>::solve(u, S, [&] { wq.settle(); });
     }
   } else {
     const int64_t b0 = (int64_t)blockIdx.x * a.chunk;
     const int64_t end = b0 + a.chunk < pairs ? b0 + a.chunk : pairs;
-    for (int64_t u = b0; u < end; ++u) PairSolver<NS, COUPLED, PROJ>::solve(a, u, S, [] {});
+    for (int64_t u = b0; u < end; ++u) PairSolver<NS, COUPLED, PROJ>::solve(u, S, [] {});
   }
 }
 
 template <int NS, bool COUPLED, bool PROJ>
-hipError_t launch_pair_t(const FwdArgs& a, const nmc_launch& L, int num_cu, hipStream_t s) {
-  auto kern = fwd_pair_kernel<NS, COUPLED, PROJ>;
-  const int64_t pairs = (a.P + 1) / 2;
-  const int64_t need = (pairs + a.chunk - 1) / a.chunk;
-  int64_t grid;
-  if (a.queue) {
-    int bpc = L.blocks_per_cu;
-    if (bpc <= 0) {
-      static int occ = 0;
-      if (occ <= 0) {
-        int o = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, kern, kLanes, 0) != hipSuccess || o <= 0) o = 8;
-        // the query under-reports resident one-wave work-groups; a surplus is
-        // harmless (late work-groups find the queue drained and exit)
-        occ = o < 16 ? 16 : o;
-      }
-      bpc = occ;
-    }
-    grid = (int64_t)bpc * num_cu;
-    if (grid > need) grid = need;
-  } else {
-    grid = need;
+hipError_t launch_pair_t(FwdArgs a, const nmc_launch& L, int num_cu, hipStream_t s) {
+  const LaunchPlan lp = plan_launch(L, (a.P + 1) / 2, 8, num_cu);
+  a.chunk = lp.chunk;
+  auto kern = fwd_pair_kernel<NS, COUPLED, PROJ, false>;
+  if (lp.queue) {
+    const hipError_t e = launch_reset_counter(a.queue, s);
+    if (e != hipSuccess) return e;
+    kern = fwd_pair_kernel<NS, COUPLED, PROJ, true>;
   }
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kLanes), 0, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)lp.grid), dim3(kLanes), 0, s, a);
   return hipGetLastError();
 }
 

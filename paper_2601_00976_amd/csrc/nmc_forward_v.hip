@@ -616,11 +616,11 @@ struct PointSolverV {
   }
 };
 
-template <int NS, bool COUPLED, bool PHI1>
+template <int NS, bool COUPLED, bool PHI1, bool QUEUE>
 __global__ __launch_bounds__(kLanes, 2) void fwd_v_kernel(FwdVArgs a) {
   __shared__ VLds<NS, PHI1> S;
   load_model(a.mdl, a.theta, S.m);
-  if (a.queue) {
+  if constexpr (QUEUE) {
     WorkQueue wq(a.queue, a.P, a.chunk);
     for (int64_t g; (g = wq.next()) >= 0;) {
       const int64_t b0 = uniform64(g * a.chunk);
@@ -635,28 +635,16 @@ __global__ __launch_bounds__(kLanes, 2) void fwd_v_kernel(FwdVArgs a) {
 }
 
 template <int NS, bool COUPLED, bool PHI1 = false>
-hipError_t launch_v_t(const FwdVArgs& a, const nmc_launch& L, int num_cu, hipStream_t s) {
-  auto kern = fwd_v_kernel<NS, COUPLED, PHI1>;
-  int64_t grid;
-  if (a.queue) {
-    int bpc = L.blocks_per_cu;
-    if (bpc <= 0) {
-      static int occ = 0;
-      if (occ <= 0) {
-        int o = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, kern, kLanes, 0) != hipSuccess || o <= 0) o = 8;
-        occ = o;
-      }
-      bpc = occ;
-    }
-    grid = (int64_t)bpc * num_cu;
-    const int64_t need = (a.P + a.chunk - 1) / a.chunk;
-    if (grid > need) grid = need;
-  } else {
-    grid = (a.P + a.chunk - 1) / a.chunk;
+hipError_t launch_v_t(FwdVArgs a, const nmc_launch& L, int num_cu, hipStream_t s) {
+  const LaunchPlan lp = plan_launch(L, a.P, 8, num_cu);
+  a.chunk = lp.chunk;
+  auto kern = fwd_v_kernel<NS, COUPLED, PHI1, false>;
+  if (lp.queue) {
+    const hipError_t e = launch_reset_counter(a.queue, s);
+    if (e != hipSuccess) return e;
+    kern = fwd_v_kernel<NS, COUPLED, PHI1, true>;
   }
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kLanes), 0, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)lp.grid), dim3(kLanes), 0, s, a);
   return hipGetLastError();
 }
 

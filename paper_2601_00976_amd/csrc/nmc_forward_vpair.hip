@@ -128,7 +128,7 @@ struct VPairSolver {
     double eN[NS], oN[NS], aP[NS], eP[NS];
 #pragma unroll
     for (int t = 0; t < NS; ++t) eN[t] = oN[t] = aP[t] = eP[t] = 0.0;
-    if (sym) {
+    if (__builtin_expect(sym, 1)) {
       double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
@@ -174,34 +174,36 @@ struct VPairSolver {
   }
 
   template <class Settle>
-  __device__ static void solve(const FwdVArgs& a, int64_t u, VPairLds<NS>& S, Settle&& settle) {
-    const_ptr<DevModel> md = scalar_ptr(a.mdl);
+  __device__ static void solve(int64_t u, VPairLds<NS>& S, Settle&& settle) {
+    const_ptr<FwdVArgs> a = kernel_args<FwdVArgs>();
+    const DevModel* mdl = a->mdl;
+    const_ptr<DevModel> md = scalar_ptr(mdl);
     const ModelLds& mt = S.m;
     const int lane = threadIdx.x;
     const int h = lane >> 5, q0 = lane & 31;
-    const double dtau = a.dtau;
+    const double dtau = a->dtau;
     // point of this half; past the end of an odd batch the half mirrors its
     // neighbour and stores nothing
     const int64_t p_raw = 2 * u + h;
-    const bool has_point = p_raw < a.P;
+    const bool has_point = p_raw < a->P;
     const int64_t p = has_point ? p_raw : p_raw - 1;
     const int64_t baseD = p * (int64_t)(NS * NQ), baseI = p * (int64_t)(NS * 3 * NQ);
-    const double rho = a.rho11[p];
+    const double rho = in_global(a->rho11)[p];
     typename VPairLds<NS>::Pt& pt = S.pt[h];
 
     double D[NS], I[NS][3];
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
       const int ex = md->ext[t];
-      D[t] = a.D0[baseD + ex * NQ + q0];
+      D[t] = in_global(a->D0)[baseD + ex * NQ + q0];
 #pragma unroll
-      for (int j = 0; j < 3; ++j) I[t][j] = a.I0[baseI + (ex * 3 + j) * NQ + q0];
+      for (int j = 0; j < 3; ++j) I[t][j] = in_global(a->I0)[baseI + (ex * 3 + j) * NQ + q0];
     }
     double yst[5];
-    yst[0] = a.ye0[p];
-    yst[1] = a.ef0[p];
+    yst[0] = in_global(a->ye0)[p];
+    yst[1] = in_global(a->ef0)[p];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) yst[2 + j] = a.v0[3 * p + j];
+    for (int j = 0; j < 3; ++j) yst[2 + j] = in_global(a->v0)[3 * p + j];
     settle();
 
     // coupling disabled at low density (Sec. 7.2): the state passes through
@@ -210,7 +212,7 @@ struct VPairSolver {
     pt.K = md->kcoup / rho;
     pt.An = (md->flags & NMC_NES) ? mt.theta[NQ] * rho : 0.0;
     pt.Ap = (md->flags & NMC_PAIR) ? mt.theta[NQ + 1] * rho : 0.0;
-    pt.chi0 = a.chi0 ? a.chi0[p] : md->chi_ref * rho;
+    pt.chi0 = a->chi0 ? in_global(a->chi0)[p] : md->chi_ref * rho;
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
       pt.yst[i] = pt.y[i] = pt.yused[i] = yst[i];
@@ -246,14 +248,14 @@ struct VPairSolver {
     bool run = !skip;  // this half's point is still iterating the outer loop
     int k_done = 0, total_inner = 0;
 
-    for (int k = 1; k <= a.prm.max_outer && __builtin_amdgcn_ballot_w64(run) != 0; ++k) {
-      const_ptr<DevModel> md = scalar_ptr(a.mdl);
+    for (int k = 1; k <= a->prm.max_outer && __builtin_amdgcn_ballot_w64(run) != 0; ++k) {
+      const_ptr<DevModel> md = scalar_ptr(mdl);
       const int q = opaque(q0);
       if (run) k_done = k;
       // ---- ComputeOpacities(y^[k]) --------------------------------------
       const double v[3] = {pt.y[2], pt.y[3], pt.y[4]};
       const double lam = rcp_nr(1.0 + sqrt(v[0] * v[0] + v[1] * v[1] + v[2] * v[2]));
-      const double T = temperature_v(md, a.prm.fixed_matter ? pt.yst : pt.y, pt.r3);
+      const double T = temperature_v(md, a->prm.fixed_matter ? pt.yst : pt.y, pt.r3);
       const double y0 = pt.y[0];
       const double mu = md->mu_a * (y0 - md->mu_ye0) * pt.r3 + md->mu_b * log_pos(T * md->inv_mu_t0);
       if (run && (!(T > 0.0) || !(y0 >= 0.0) || !isfinite(T) || !isfinite(mu))) {
@@ -316,13 +318,13 @@ struct VPairSolver {
                                 __builtin_amdgcn_ballot_w64(run && nhi - nlo > kDirectBits) == 0)) != 0;
         gq = sym ? ldexp(xs.R, c - xs.n) : 1.0;
         rgq = sym ? ldexp(xs.P, xs.n - c) : 1.0;
-        if (direct) {
+        if (__builtin_expect(direct, 1)) {
           // rows of the symmetric core from the point's scaled h, broadcast
           // from registers
           direct_row_regs(gq * gq, rgq * rgq, B);
         } else {
           double (*Tt)[NQ] = S.u.tile[h];
-          if (sym) {
+          if (__builtin_expect(sym, 1)) {
             pair_tile_rows<true>(&Tt[0][0], E.P2, E.R2, E.n2, q, xs.P, xs.R, xs.n);
             Tt[q][q] = 1.0;
           } else {
@@ -346,7 +348,9 @@ struct VPairSolver {
       bool act = run;
       bool cvd = false;
       int l_done = 0;
-      for (int l = 1; l <= a.prm.max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
+      const int m_inner = held(a->prm.m_inner), max_inner = held(a->prm.max_inner);
+      const double tol2 = held(a->tol_inner2);
+      for (int l = 1; l <= max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
         if (act) l_done = l;
         double etaN[NS], outN[NS], annP[NS], etaP[NS];
 #pragma unroll
@@ -354,7 +358,7 @@ struct VPairSolver {
         if constexpr (COUPLED) {
 #pragma unroll
           for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
-          if (sym) {
+          if (__builtin_expect(sym, 1)) {
             double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
@@ -439,7 +443,7 @@ struct VPairSolver {
         // the current iterate in moment order, and the residual F = Q - M
         auto cur = [&](int x) { return (x & 3) == 0 ? D[x >> 2] : I[x >> 2][(x & 3) - 1]; };
         // Anderson step over min(l, M_inner) residuals (difference form)
-        const int mem = l < a.prm.m_inner ? l : a.prm.m_inner;
+        const int mem = l < m_inner ? l : m_inner;
         double Xn[NM];
         if constexpr (HREG) {
           // history in registers
@@ -553,7 +557,7 @@ struct VPairSolver {
           spread_conv_sums<NS, 4>(vm, vn, dm2, dn2);
           const int cls = spread_class(lane);
           const double d0 = cls < NS ? pt.dref[cls < NS ? cls : 0] : 0.0;
-          const double tr2 = a.tol_inner2 * (d0 > dn2 ? d0 : dn2);
+          const double tr2 = tol2 * (d0 > dn2 ? d0 : dn2);
           const bool conv = !half_any(!(dm2[0] <= tr2 && dm2[1] <= tr2));
           // ||D^[k,*]|| is the reference of the next inner loop
           if (act && conv && cls < NS) pt.dref[cls < NS ? cls : 0] = dn2;
@@ -586,7 +590,7 @@ struct VPairSolver {
         }
         eulerian_point<NS>(md, w2q, mt.w3[q], D, I, v, X);
       }
-      if (a.prm.fixed_matter) {
+      if (a->prm.fixed_matter) {
         if (run) outer_conv = true;
         run = false;
       }
@@ -596,7 +600,7 @@ struct VPairSolver {
         matter_rhs(pt, X, yq);
 #pragma unroll
         for (int i = 0; i < 5; ++i) f[i] = yq[i] - pt.y[i];
-        const int omem = k < a.prm.m_outer ? k : a.prm.m_outer;
+        const int omem = k < a->prm.m_outer ? k : a->prm.m_outer;
         if (omem == 1) {
 #pragma unroll
           for (int i = 0; i < 5; ++i) yn[i] = yq[i];
@@ -640,10 +644,10 @@ struct VPairSolver {
           const double vst = sqrt(pt.yst[2] * pt.yst[2] + pt.yst[3] * pt.yst[3] + pt.yst[4] * pt.yst[4]);
           const double vnw = sqrt(yn[2] * yn[2] + yn[3] * yn[3] + yn[4] * yn[4]);
           const double vref = vst > vnw ? vst : vnw;
-          bool oc = fabs(yn[0] - pt.y[0]) <= a.prm.tol_outer * fabs(pt.yst[0]) &&
-                    fabs(yn[1] - pt.y[1]) <= a.prm.tol_outer * fabs(pt.yst[1]);
+          bool oc = fabs(yn[0] - pt.y[0]) <= a->prm.tol_outer * fabs(pt.yst[0]) &&
+                    fabs(yn[1] - pt.y[1]) <= a->prm.tol_outer * fabs(pt.yst[1]);
 #pragma unroll
-          for (int j = 0; j < 3; ++j) oc = oc && fabs(yn[2 + j] - pt.y[2 + j]) <= a.prm.tol_outer * vref;
+          for (int j = 0; j < 3; ++j) oc = oc && fabs(yn[2 + j] - pt.y[2 + j]) <= a->prm.tol_outer * vref;
 #pragma unroll
           for (int i = 0; i < 5; ++i) pt.y[i] = yn[i];
           if (oc) {
@@ -659,93 +663,82 @@ struct VPairSolver {
     }
 
     // ---- outputs --------------------------------------------------------
+    const_ptr<FwdVArgs> ao = kernel_args<FwdVArgs>();
+    const_ptr<DevModel> mo = scalar_ptr(ao->mdl);
     // matter right-hand side at the final moments and the matter iterate they
     // were solved at (every lane of both halves takes part in the reduction)
     double yout[5];
     {
       const double vu[3] = {pt.yused[2], pt.yused[3], pt.yused[4]};
       double X[5];
-      eulerian_point<NS>(md, mt.w2[q0], mt.w3[q0], D, I, vu, X);
+      eulerian_point<NS>(mo, mt.w2[q0], mt.w3[q0], D, I, vu, X);
       matter_rhs(pt, X, yout);
     }
     double T_out;
     if (skip) {
 #pragma unroll
       for (int i = 0; i < 5; ++i) yout[i] = pt.yst[i];
-      T_out = temperature_v(md, pt.yst, pt.r3);
-    } else if (a.prm.fixed_matter) {
+      T_out = temperature_v(mo, pt.yst, pt.r3);
+    } else if (ao->prm.fixed_matter) {
 #pragma unroll
       for (int i = 0; i < 5; ++i) yout[i] = pt.yst[i];
       T_out = pt.T_last;
     } else {
-      T_out = temperature_v(md, yout, pt.r3);
+      T_out = temperature_v(mo, yout, pt.r3);
     }
     if (has_point) {
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
-        const int ex = md->ext[t];
-        a.D[baseD + ex * NQ + q0] = D[t];
+        const int ex = mo->ext[t];
+        in_global(ao->D)[baseD + ex * NQ + q0] = D[t];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) a.I[baseI + (ex * 3 + j) * NQ + q0] = I[t][j];
+        for (int j = 0; j < 3; ++j) in_global(ao->I)[baseI + (ex * 3 + j) * NQ + q0] = I[t][j];
       }
       if (q0 == 0) {
-        a.ye[p] = yout[0];
-        a.ef[p] = yout[1];
+        in_global(ao->ye)[p] = yout[0];
+        in_global(ao->ef)[p] = yout[1];
 #pragma unroll
-        for (int j = 0; j < 3; ++j) a.v[3 * p + j] = yout[2 + j];
-        a.T[p] = T_out;
-        a.n_outer[p] = skip ? 0 : k_done;
-        a.n_inner[p] = total_inner;
-        a.status[p] = status;
+        for (int j = 0; j < 3; ++j) in_global(ao->v)[3 * p + j] = yout[2 + j];
+        in_global(ao->T)[p] = T_out;
+        in_global(ao->n_outer)[p] = skip ? 0 : k_done;
+        in_global(ao->n_inner)[p] = total_inner;
+        in_global(ao->status)[p] = status;
       }
     }
     __syncthreads();
   }
 };
 
-template <int NS, bool COUPLED, bool PHI1>
+template <int NS, bool COUPLED, bool PHI1, bool QUEUE>
 __global__ __launch_bounds__(kLanes, COUPLED ? 1 : 2) void fwd_vpair_kernel(FwdVArgs a) {
   __shared__ VPairLds<NS> S;
   load_model(a.mdl, a.theta, S.m);
   const int64_t pairs = (a.P + 1) / 2;
-  if (a.queue) {
+  if constexpr (QUEUE) {
     WorkQueue wq(a.queue, pairs, a.chunk);
     for (int64_t g; (g = wq.next()) >= 0;) {
       const int64_t b0 = uniform64(g * a.chunk);
       const int64_t end = uniform64(b0 + a.chunk < pairs ? b0 + a.chunk : pairs);
-      for (int64_t u = b0; u < end; ++u) VPairSolver<NS, COUPLED, PHI1>::solve(a, u, S, [&] { wq.settle(); });
+      for (int64_t u = b0; u < end; ++u) VPairSolver<NS, COUPLED, PHI1>::solve(u, S, [&] { wq.settle(); });
     }
   } else {
     const int64_t b0 = (int64_t)blockIdx.x * a.chunk;
     const int64_t end = b0 + a.chunk < pairs ? b0 + a.chunk : pairs;
-    for (int64_t u = b0; u < end; ++u) VPairSolver<NS, COUPLED, PHI1>::solve(a, u, S, [] {});
+    for (int64_t u = b0; u < end; ++u) VPairSolver<NS, COUPLED, PHI1>::solve(u, S, [] {});
   }
 }
 
 template <int NS, bool COUPLED, bool PHI1>
-hipError_t launch_vpair_t(const FwdVArgs& a, const nmc_launch& L, int num_cu, hipStream_t s) {
-  auto kern = fwd_vpair_kernel<NS, COUPLED, PHI1>;
-  const int64_t pairs = (a.P + 1) / 2;
-  const int64_t need = (pairs + a.chunk - 1) / a.chunk;
-  int64_t grid;
-  if (a.queue) {
-    int bpc = L.blocks_per_cu;
-    if (bpc <= 0) {
-      static int occ = 0;
-      if (occ <= 0) {
-        int o = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, kern, kLanes, 0) != hipSuccess || o <= 0) o = 8;
-        occ = o;
-      }
-      bpc = occ;
-    }
-    grid = (int64_t)bpc * num_cu;
-    if (grid > need) grid = need;
-  } else {
-    grid = need;
+hipError_t launch_vpair_t(FwdVArgs a, const nmc_launch& L, int num_cu, hipStream_t s) {
+  const LaunchPlan lp = plan_launch(L, (a.P + 1) / 2, COUPLED ? 4 : 8, num_cu);
+  a.chunk = lp.chunk;
+  auto kern = fwd_vpair_kernel<NS, COUPLED, PHI1, false>;
+  if (lp.queue) {
+    const hipError_t e = launch_reset_counter(a.queue, s);
+    if (e != hipSuccess) return e;
+    kern = fwd_vpair_kernel<NS, COUPLED, PHI1, true>;
   }
-  if (grid < 1) grid = 1;
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kLanes), 0, s, a);
+  hipLaunchKernelGGL(kern, dim3((unsigned)lp.grid), dim3(kLanes), 0, s, a);
   return hipGetLastError();
 }
 

@@ -276,6 +276,29 @@ __device__ __forceinline__ const_ptr<T> scalar_ptr(const T* p) {
   return c;
 }
 
+// The argument struct of a kernel whose only parameter it is (offset 0 of the
+// kernarg segment), laundered like opaque_ptr: its members are read by scalar
+// loads where they are used.  As ordinary parameters they would be loaded
+// once and held, some 60 scalar registers that the solve kernels do not have:
+// they were spilled to vector-register lanes and read back lane by lane.
+template <class A>
+__device__ __forceinline__ const_ptr<A> kernel_args() {
+  return scalar_ptr((const A*)__builtin_amdgcn_kernarg_segment_ptr());
+}
+// A uniform value held in scalar registers from here on (not loaded again
+// where it is used).
+template <class T>
+__device__ __forceinline__ T held(T x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+// An array of such a struct as global memory (a pointer read from memory is
+// generic to the compiler, and flat accesses occupy the LDS queue as well).
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* in_global(T* p) {
+  return (__attribute__((address_space(1))) T*)p;
+}
+
 // Four columns of the contraction for every species and both matrices in one
 // asm block: acc1[t] += bcast(x[t], L0 + jj) * m1[jj], acc2[t] += bcast(x[t], L0 + jj) * m2[jj].
 // The leading s_nop 1 provides the two wait states a DPP source needs after
@@ -477,34 +500,49 @@ constexpr int kQueueRun = 32;     // chunks
 struct WorkQueue {
   int* ctr;
   int64_t nchunks, full;  // chunks; tickets per counter inside whole blocks
+  int64_t early;          // tickets below this reserve their successor ahead
   int nq, c;
-  int pend;  // lane 0: ticket returned by the grab in flight
-  int cur;   // ticket of the next chunk (uniform)
+  int pend;    // lane 0: ticket returned by the grab in flight
+  int cur;     // ticket of the next chunk (uniform)
+  bool ahead;  // the next chunk's ticket is reserved already (uniform)
   __device__ __forceinline__ WorkQueue(int* queue, int64_t P, int chunk) {
     nq = gridDim.x < kQueues ? (int)gridDim.x : kQueues;
     c = blockIdx.x % nq;
     ctr = queue + c * kQueueStride;
     nchunks = (P + chunk - 1) / chunk;
     full = nchunks / ((int64_t)kQueueRun * nq) * kQueueRun;
+    early = (nchunks - 2 * (int64_t)gridDim.x) / nq;
     pend = 0;
     if (threadIdx.x == 0) pend = atomicAdd(ctr, 1);
     cur = __builtin_amdgcn_readfirstlane(pend);
+    ahead = true;
   }
-  // next chunk index of this work-group (uniform), or -1 once drained; the
-  // following grab is issued here and must be settled before the next call
+  // next chunk index of this work-group (uniform), or -1 once drained; a
+  // grab issued ahead must be settled before the next call.  Towards the end
+  // of the batch (the last two chunks per work-group) the ticket is taken only
+  // here, when the work-group is free: one reserved ahead would wait for the
+  // end of its holder's chunk, and a slow chunk's holder would keep it from
+  // the work-groups that are out of work.
   __device__ __forceinline__ int64_t next() {
+    if (!ahead) {
+      if (threadIdx.x == 0) pend = atomicAdd(ctr, 1);
+      cur = __builtin_amdgcn_readfirstlane(pend);
+    }
     const int64_t t = cur;
     const int64_t g = t < full ? (t / kQueueRun) * kQueueRun * nq + (int64_t)c * kQueueRun + t % kQueueRun
                                : full * nq + (t - full) * nq + c;
     if (g >= nchunks) return -1;
-    if (threadIdx.x == 0) pend = atomicAdd(ctr, 1);
+    ahead = t < early;
+    if (ahead && threadIdx.x == 0) pend = atomicAdd(ctr, 1);
     return g;
   }
-  // takes the result of the grab in flight.  Called once the chunk's inputs
+  // takes the result of a grab in flight.  Called once the chunk's inputs
   // are loaded: the wait for the atomic then overlaps that of the loads
   // instead of the drain of the chunk's output stores (vector memory
   // counters complete in order).
-  __device__ __forceinline__ void settle() { cur = __builtin_amdgcn_readfirstlane(pend); }
+  __device__ __forceinline__ void settle() {
+    if (ahead) cur = __builtin_amdgcn_readfirstlane(pend);
+  }
 };
 
 // Pair partner of internal species s (species sorted by id: nu_e, anti-nu_e
