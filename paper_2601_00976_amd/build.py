@@ -29,6 +29,10 @@ COMMON = [
     # atomics stay plain single-lane operations, so the work-queue grab's
     # result is not waited for where it is issued
     "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
+    # blocks reached by a jump alone start a 64-byte line: at one or two waves
+    # per SIMD the solve kernels' speed depends on where their loop bodies
+    # fall (O(v) solve of 16384 points 941 us at one placement, 889 us so)
+    "-mllvm", "-align-all-nofallthru-blocks=6",
     "-Wall", "-Wno-unused-function",
 ]
 

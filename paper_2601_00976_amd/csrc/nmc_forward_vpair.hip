@@ -56,7 +56,7 @@ __device__ __forceinline__ double temperature_v(const_ptr<DevModel> md, const do
 
 // The lane's contributions to the Eulerian integrals (N, E, F_1, F_2, F_3) of
 // its node's moments at velocity v
-template <int NS>
+template <int NS, bool FLAT>
 __device__ __forceinline__ void eulerian_node(const_ptr<DevModel> md, double w2, double w3, const double (&D)[NS],
                                               const double (&I)[NS][3], const double (&v)[3], double (&acc)[5]) {
 #pragma unroll
@@ -64,7 +64,8 @@ __device__ __forceinline__ void eulerian_node(const_ptr<DevModel> md, double w2,
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
     double vI, vK[3];
-    closure_terms(D[t], I[t], v, vI, vK);
+    if constexpr (FLAT) closure_terms_flat(D[t], I[t], v, vI, vK);
+    else closure_terms(D[t], I[t], v, vI, vK);
     acc[0] += md->ig[t] * w2 * (D[t] + vI);
     acc[1] += md->imult[t] * w3 * (D[t] + 2.0 * vI);
 #pragma unroll
@@ -74,12 +75,14 @@ __device__ __forceinline__ void eulerian_node(const_ptr<DevModel> md, double w2,
 
 // Eulerian integrals (N, E, F_1, F_2, F_3) of the half's point, in every lane
 // of the half; one reduction shape for every caller, so that equal moments
-// give bitwise equal integrals
-template <int NS>
+// give bitwise equal integrals.  FLAT: the closure by selects; the old state's
+// integrals keep the branching one, whose values the compiler shares with N*
+// and G*
+template <int NS, bool FLAT = true>
 __device__ __forceinline__ void eulerian_point(const_ptr<DevModel> md, double w2, double w3, const double (&D)[NS],
                                                const double (&I)[NS][3], const double (&v)[3], double (&X)[5]) {
   double acc[5], s[6];
-  eulerian_node<NS>(md, w2, w3, D, I, v, acc);
+  eulerian_node<NS, FLAT>(md, w2, w3, D, I, v, acc);
   const double vv[6] = {acc[0], acc[1], acc[2], acc[3], acc[4], 0.0};
   half_own_sums<3>(vv, s);
 #pragma unroll
@@ -235,7 +238,7 @@ struct VPairSolver {
         for (int j = 0; j < 3; ++j) Gst[t][j] = I[t][j] + vK[j];
       }
       double X0[5], n0[NS];
-      eulerian_point<NS>(md, mt.w2[q0], mt.w3[q0], D, I, vs, X0);
+      eulerian_point<NS, false>(md, mt.w2[q0], mt.w3[q0], D, I, vs, X0);
       dnorms<NS>(mt.w2[q0], D, n0);
 #pragma unroll
       for (int t = 0; t < NS; ++t) pt.dref[t] = n0[t];
@@ -358,6 +361,8 @@ struct VPairSolver {
         if constexpr (COUPLED) {
 #pragma unroll
           for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+          // the expected form lies on the loop's straight path (placement alone
+          // is worth 4% with the linear-order terms, whose passes repeat it)
           if (__builtin_expect(sym, 1)) {
             double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
 #pragma unroll
@@ -414,7 +419,7 @@ struct VPairSolver {
             }
           });
 #pragma unroll
-          for (int t = 0; t < NS; ++t) phi1_collision(D[t], I[t], Pc[t], Rc[t], cN[t], cI[t]);
+          for (int t = 0; t < NS; ++t) phi1_collision_flat(D[t], I[t], Pc[t], Rc[t], cN[t], cI[t]);
         }
         // Q and residual of the owned moments (Eq. implicitMomentsNodal):
         //   Q_D  = ((1 - lam) D - lam v.I + lam (N* + dtau (eta + c))) / (1 + lam dtau chi)
@@ -427,7 +432,7 @@ struct VPairSolver {
           const double eta = __builtin_fma(Aeq * gq, etaN[t], Apqh * etaP[t]);
           const double chi = __builtin_fma(Aeq * rgq, outN[t], __builtin_fma(Apq, annP[t], eta));
           double vI, vK[3];
-          closure_terms(D[t], I[t], v, vI, vK);
+          closure_terms_flat(D[t], I[t], v, vI, vK);
           const double dD = __builtin_fma(ldt, chi, denD[t]), dI = __builtin_fma(ldt, chi, denI[t]);
           const double r = rcp_nr(dD * dI);
           double nD = __builtin_fma(oml, D[t], baseD[t]) - lam * vI + ldt * eta;
