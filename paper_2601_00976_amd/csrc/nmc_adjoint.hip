@@ -13,18 +13,32 @@
 // and dL/dtheta_j = -lambda_D^T dR_D/dtheta_j for theta = (s_1..s_nq, a_nes,
 // a_pair), L = gE (e* - e) + gY (Ye - Ye*).
 //
-// A is block diagonal over pair-coupled species: NES couples the nodes of one
-// species, pair processes couple a species with its partner, so with species
-// in id order the blocks are (nu_e, anti-nu_e) of size 64 and nu_x of size
-// 32.  Each block is factorised in registers, one wavefront per point: lane r
-// holds row r of A^T (column r of A) and the two right-hand sides.  Block
-// Gaussian elimination with 2 x 2 pivot blocks runs without row exchanges
-// (the W-scaled columns of A are strictly diagonally dominant), broadcasting
-// the two pivot rows of each step through LDS; block back substitution
-// follows.  Per-point terms go to a
-// (P, nq + 2) array and are summed over points by a fixed-order two-stage
-// reduction.
-#include "nmc_wave.h"
+// Two ways to solve for Z, both FP64:
+//
+// Iteration (the usual one, PairAdjoint): two points per wavefront as in the
+// forward kernel.  A^T = G - N with G its diagonal is iterated as
+// z <- G^-1 (c + N z).  The W-scaled columns of A are strictly diagonally
+// dominant, so this always converges, and over a time step of a transport
+// code N is small against G: on the radial profile at dtau = 1e-3 km it takes
+// 3.7 iterations on average and 11 at most to reach rounding, each one the
+// forward solve's contraction on the symmetric core (24 n^2 multiply-adds for
+// both columns of C) where an elimination takes (2/3) (64^3 + 32^3).
+//
+// Elimination (PointAdjoint): for points that the iteration does not settle
+// (slow convergence, a non-finite value) or whose grid spans too many powers
+// of two for it.  A is block diagonal over pair-coupled species: NES couples
+// the nodes of one species, pair processes couple a species with its partner,
+// so with species in id order the blocks are (nu_e, anti-nu_e) of size 64 and
+// nu_x of size 32.  Each block is factorised in registers, one wavefront per
+// point: lane r holds row r of A^T (column r of A) and the two right-hand
+// sides.  Block Gauss-Jordan elimination with 2 x 2 pivot blocks runs without
+// row exchanges, broadcasting the two pivot rows of each step through LDS.
+//
+// Every work-group adds its points' terms in order and writes one row of
+// partial sums; a second kernel adds the rows of each column in a fixed
+// order.  Where the caller asks for them, the per-point terms go to a
+// (P, nq + 2) array as well.
+#include "nmc_pair.h"
 
 namespace nmc {
 namespace {
@@ -260,18 +274,14 @@ struct PointAdjoint {
     return ok;
   }
 
-  __device__ static void run(const AdjArgs& a, int64_t pt, AdjLds<NS>& S) {
+  // the terms of a point that has any: its s_q term in lane q (lanes 0..31), its a_nes
+  // and a_pair terms in every lane
+  __device__ static void run(const AdjArgs& a, int64_t pt, AdjLds<NS>& S, double& g_s, double& g_nes,
+                             double& g_pair) {
     constexpr int ST = kTileStride;
-    constexpr int NT = NQ + 2;
     const DevModel* __restrict__ md = a.mdl;
     const int lane = opaque((int)threadIdx.x);  // laundered: lane-derived indices are not hoisted out of the point loop
     const int h = lane >> 5, q = lane & 31;
-    double* gout = a.grad_pp + pt * NT;
-    if (a.status[pt] != NMC_STATUS_OK || a.n_outer[pt] == 0) {
-      // skipped or failed points contribute nothing
-      if (lane < NT) gout[lane] = 0.0;
-      return;
-    }
     const int64_t base = pt * (int64_t)(NS * NQ);
     if (lane < 32) {
 #pragma unroll
@@ -427,78 +437,382 @@ struct PointAdjoint {
     double gs[4];
     wave_sums4(v2, gs);
     const double nan = __builtin_nan("");
-    if (lane < 32) gout[lane] = ok ? gq : nan;
-    if (lane == 32) gout[NQ] = ok ? gs[0] : nan;
-    if (lane == 33) gout[NQ + 1] = ok ? gs[1] : nan;
+    g_s = ok ? gq : nan;
+    g_nes = ok ? gs[0] : nan;
+    g_pair = ok ? gs[1] : nan;
     __syncthreads();
   }
 };
 
 template <int NS>
-__global__ __launch_bounds__(kLanes) void adj_kernel(AdjArgs a) {
-  __shared__ AdjLds<NS> S;
-  load_model(a.mdl, a.theta, S.m);
-  for (int64_t p = blockIdx.x; p < a.P; p += gridDim.x) PointAdjoint<NS>::run(a, p, S);
-}
+struct AdjPairLds {
+  ModelLds m;
+  double row[5][NS][kLanes];  // dR_D / d(Ye, e, a_nes, a_pair, s_q) of the lane's rows
+};
 
-// Column sums of a (P, ncol) row-major array in a fixed order: block b sums
-// its contiguous range of rows, then one block adds the block partials in
-// order into out (accumulating).
-__global__ void reduce_stage1(const double* __restrict__ x, int64_t P, int ncol, int64_t rows_per_block,
-                              double* __restrict__ partial) {
-  const int c = threadIdx.x;
-  if (c >= ncol) return;
-  const int64_t r0 = (int64_t)blockIdx.x * rows_per_block;
-  const int64_t r1 = r0 + rows_per_block < P ? r0 + rows_per_block : P;
-  double s = 0.0;
-  for (int64_t r = r0; r < r1; ++r) s += x[r * ncol + c];
-  partial[(int64_t)blockIdx.x * ncol + c] = s;
-}
+// most iterations before a point is left to the elimination, and the relative
+// change of an entry at which it has settled (16 ulp; the next iteration
+// would change it by a fraction of that)
+constexpr int kAdjMaxIt = 24;
+constexpr double kAdjSettled = 0x1p-48;
 
-__global__ __launch_bounds__(256) void reduce_stage2(const double* __restrict__ partial, int nblk, int ncol,
-                                                     double* __restrict__ out) {
-  // per column: thread t sums partials t, t + 256, ... in order, then a
-  // fixed-shape tree over the 256 threads
-  __shared__ double red[256];
-  const int t = threadIdx.x;
-  for (int c = 0; c < ncol; ++c) {
-    double s = 0.0;
-    for (int b = t; b < nblk; b += 256) s += partial[(int64_t)b * ncol + c];
-    red[t] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-      if (t < w) red[t] += red[t + w];
-      __syncthreads();
+// Two points per wavefront by iteration: lane 32 h + q holds node q of the
+// point of half h, for every species.
+//
+// The contractions run on the symmetric core B2 = exp(-|e_q - e_p| / T) as in
+// the forward kernel (columns broadcast by DPP, the factors g, 1 / g and h of
+// the nodes on the vectors and the row sums).  65536 points of the radial
+// profile: 324 us, against 1488 us by elimination alone, whose steps are a
+// chain of pivot broadcasts and reciprocals; here the multiply-adds' issue at
+// two waves per SIMD bounds it, a third of them the rates and their
+// derivatives.
+template <int NS>
+struct PairAdjoint {
+  // acc[t] += sum_j bcast_j(x[t]) B[j], acc2[t] likewise with f(j) (the
+  // second matrix, formed per column): Fmac4 takes four columns of the lane's
+  // 16-lane row at a time
+  template <class F>
+  __device__ __forceinline__ static void contract2(const double (&x)[NS], const double (&B)[NQ], double (&s)[NS],
+                                                   double (&d)[NS], F&& f) {
+    double R[2][NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      swap16(x[t], R[0][t], R[1][t]);
+      s[t] = d[t] = 0.0;
     }
-    if (t == 0) out[c] += red[0];
+    static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
+      constexpr int j = 4 * decltype(jj)::value;
+      Fmac4<NS>::template run<j % 16>(s, d, R[j / 16], B[j], B[j + 1], B[j + 2], B[j + 3], f(j), f(j + 1), f(j + 2),
+                                      f(j + 3));
+    });
+  }
+
+  // live: the half's point has terms (solved forward, not skipped).  Returns
+  // in every lane whether its half's point was solved here; g_s is the lane's
+  // s_q term, g_nes and g_pair the point's.
+  __device__ __forceinline__ static bool run(const AdjArgs& a, int64_t pt, bool live, AdjPairLds<NS>& S, double& g_s,
+                                             double& g_nes, double& g_pair) {
+    const_ptr<DevModel> md = scalar_ptr(a.mdl);
+    const int lane = opaque((int)threadIdx.x);
+    const int h = lane >> 5, q = lane & 31;
+    const int64_t base = pt * (int64_t)(NS * NQ);
+    double D[NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) D[t] = a.D[base + md->ext[t] * NQ + q];
+    const double rho = a.rho11[pt], ye = a.ye[pt], e = a.e[pt];
+    const double chi0 = a.chi0 ? a.chi0[pt] : md->chi_ref * rho;
+    const double dtau = a.dtau;
+    // EOS and its derivatives
+    const double r3 = cbrt(rho), cye = cbrt(ye);
+    const double ia = rcp_nr(md->eos_a * (1.0 + ye));
+    const double T = (e - md->eos_b * (ye * cye) * r3) * ia;
+    const bool warm = live && T > 0.0 && isfinite(T);
+    const double Tu = warm ? T : 1.0;
+    const double mu = md->mu_a * (ye - md->mu_ye0) * r3 + md->mu_b * log_pos(Tu * md->inv_mu_t0);
+    const double invT = rcp_nr(Tu);
+    const double dT_de = ia;
+    const double dT_dye = -(4.0 / 3.0) * md->eos_b * cye * r3 * ia - T * rcp_nr(1.0 + ye);
+    const double dmu_dye = md->mu_a * r3 + md->mu_b * invT * dT_dye;
+    const double dmu_de = md->mu_b * invT * dT_de;
+    const double K = md->kcoup * rcp_nr(rho);
+    const unsigned flags = md->flags;
+    const double a_nes = (flags & NMC_NES) ? S.m.theta[NQ] : 0.0;
+    const double a_pair = (flags & NMC_PAIR) ? S.m.theta[NQ + 1] : 0.0;
+
+    // rows of the symmetric core and the nodes' factors (scaled by 2^+-c, c
+    // the middle of the point's exponent range)
+    const double eq = S.m.eps[q], w2q = S.m.w2[q], weq = w2q * eq;
+    const ExpSplit xs = exp_split(eq, invT);
+    const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
+    const int lo1 = __builtin_amdgcn_readlane(xs.n, 32), hi1 = __builtin_amdgcn_readlane(xs.n, 63);
+    const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
+    const int c = (nlo + nhi) >> 1;
+    bool act = warm && nhi - nlo <= pairk::kDirectBits;
+    const double gq = ldexp(xs.R, c - xs.n), rgq = ldexp(xs.P, xs.n - c);
+    const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
+    double B[NQ];
+    pairk::direct_row_regs(gq * gq, rgq * rgq, B);
+
+    // ---- rates with unit-amplitude kernels, their temperature derivatives
+    // (times T^2) and the rows of dR_D / d(Ye, e, a_nes, a_pair, s_q) -------
+    double dg[NS], c0[NS], c1[NS];  // diagonal of A^T, right-hand sides over it
+    {
+      double x[NS], en[NS], dn[NS], on[NS], dout[NS], an[NS], dan[NS], ep[NS], dpr[NS];
+      // d = e_q - e_j and its magnitude; e_q is laundered between the passes,
+      // so that they are formed again instead of held
+      double ev = eq;
+      auto ad = [&](int j) { return fabs(ev - md->eps[j]); };
+      auto dl = [&](int j) { return ev - md->eps[j]; };
+#pragma unroll
+      for (int t = 0; t < NS; ++t) x[t] = weq * D[t] * rgq;
+      contract2(x, B, en, dn, [&](int j) { return B[j] * __builtin_fma(0.5, dl(j), ad(j)); });
+      asm volatile("" : "+v"(ev));
+#pragma unroll
+      for (int t = 0; t < NS; ++t) x[t] = weq * (1.0 - D[t]) * gq;
+      contract2(x, B, on, dout, [&](int j) { return B[j] * __builtin_fma(-0.5, dl(j), ad(j)); });
+      asm volatile("" : "+v"(ev));
+#pragma unroll
+      for (int t = 0; t < NS; ++t) x[t] = weq * D[pair_partner<NS>(t)];
+      contract2(x, B, an, dan, [&](int j) { return B[j] * ad(j); });
+      asm volatile("" : "+v"(ev));
+#pragma unroll
+      for (int t = 0; t < NS; ++t) x[t] = weq * (1.0 - D[pair_partner<NS>(t)]) * hq;
+      contract2(x, B, ep, dpr, [&](int j) { return B[j] * (ad(j) + (ev + md->eps[j])); });
+      const double sc = rho * eq, scg = sc * gq, scr = sc * rgq, sch = sc * hq;
+      const double shape = chi0 * S.m.shape[q], iT2 = invT * invT;
+      const double wen = dtau * a_nes * sc * weq, wep = dtau * a_pair * sc * weq;
+#pragma unroll
+      for (int t = 0; t < NS; ++t) {
+        en[t] *= scg;
+        dn[t] *= scg;
+        on[t] *= scr;
+        dout[t] *= scr;
+        an[t] *= sc;
+        dan[t] *= sc;
+        ep[t] *= sch;
+        dpr[t] *= sch;
+        const double chia = (flags & NMC_EMAB) ? md->iemab[t] * S.m.theta[q] * shape : 0.0;
+        const double xf = (eq - md->imusign[t] * mu) * invT;
+        const double ex = exp(-fabs(xf));
+        const double r = rcp_nr(1.0 + ex);
+        const double f = xf > 0.0 ? ex * r : r;   // Fermi-Dirac D_eq
+        const double fc = xf > 0.0 ? r : ex * r;  // 1 - D_eq
+        const double ddeq_dT = f * fc * xf * invT;
+        const double ddeq_dmu = f * fc * md->imusign[t] * invT;
+        const double chi = chia + a_nes * (en[t] + on[t]) + a_pair * (ep[t] + an[t]);
+        const double deta_dT = chia * ddeq_dT + (a_nes * dn[t] + a_pair * dpr[t]) * iT2;
+        const double dchi_dT = (a_nes * (dn[t] + dout[t]) + a_pair * (dpr[t] + dan[t])) * iT2;
+        const double dR_dT = dtau * (D[t] * dchi_dT - deta_dT);
+        const double dR_dmu = -dtau * chia * ddeq_dmu;
+        S.row[0][t][lane] = dR_dT * dT_dye + dR_dmu * dmu_dye;
+        S.row[1][t][lane] = dR_dT * dT_de + dR_dmu * dmu_de;
+        S.row[2][t][lane] = (flags & NMC_NES) ? dtau * (D[t] * (en[t] + on[t]) - en[t]) : 0.0;
+        S.row[3][t][lane] = (flags & NMC_PAIR) ? dtau * (D[t] * (ep[t] + an[t]) - ep[t]) : 0.0;
+        S.row[4][t][lane] = (flags & NMC_EMAB) ? dtau * shape * md->iemab[t] * (D[t] - f) : 0.0;
+        // the diagonal entry: NES self term Phi_in[q][q] = Phi_out[q][q] = A e^2, and for a species that is its own
+        // pair partner the pair term of Phi_ann[q][q] = A' e^2, Phi_pro[q][q] = A' e^2 h^2
+        double diag = 1.0 + dtau * chi - wen;
+        if (pair_partner<NS>(t) == t) diag += wep * (D[t] + (1.0 - D[t]) * (hq * hq));
+        dg[t] = diag;
+        const double rd = rcp_nr(diag);
+        c0[t] = K * md->ig[t] * w2q * rd;
+        c1[t] = K * md->imult[t] * S.m.w3[q] * rd;
+      }
+    }
+
+    // ---- z <- (c + (G - A^T) z) / G for both right-hand sides --------------
+    // (A^T z)_q = G z + the NES sum over the own species and the pair sum over
+    // the partner, with the diagonal terms taken out again
+    double z[2][NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      z[0][t] = c0[t];
+      z[1][t] = c1[t];
+    }
+    bool solved = false;
+    const double wn = dtau * a_nes * rho * weq, wp = dtau * a_pair * rho * weq;
+    for (int it = 0; it < kAdjMaxIt && __builtin_amdgcn_ballot_w64(act) != 0; ++it) {
+#pragma unroll
+      for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+      bool moved = false;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+          const double ez = eq * z[k][t], xd = ez * D[t], yd = ez - xd;
+          swap16(xd * rgq, AR[0][t], AR[1][t]);
+          swap16(yd * gq, BR[0][t], BR[1][t]);
+          swap16(xd, CR[0][t], CR[1][t]);
+          swap16(yd * hq, DR[0][t], DR[1][t]);
+        }
+        double eN[NS], oN[NS], aP[NS], eP[NS];
+#pragma unroll
+        for (int t = 0; t < NS; ++t) eN[t] = oN[t] = aP[t] = eP[t] = 0.0;
+        static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
+          constexpr int j = 4 * decltype(jj)::value;
+          pairk::ColSym<NS>::template run<j % 16>(eN, oN, aP, eP, AR[j / 16], BR[j / 16], CR[j / 16], DR[j / 16],
+                                                  B[j], B[j + 1], B[j + 2], B[j + 3]);
+        });
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+          const double ez = eq * z[k][t];
+          // the sums without their q-th terms, B2(q, q) = 1
+          double nes = __builtin_fma(gq, eN[t], rgq * oN[t]) - ez;
+          double pr = __builtin_fma(hq, eP[t], aP[t]);
+          if (pair_partner<NS>(t) == t) pr -= ez * __builtin_fma(1.0 - D[t], hq * hq, D[t]);
+          const double off = __builtin_fma(wn, nes, -wp * pr);
+          const double cc = k ? c1[t] : c0[t];
+          const double zn = __builtin_fma(off, rcp_nr(dg[t]), cc);
+          moved = moved || !(fabs(zn - z[k][t]) <= kAdjSettled * (fabs(zn) + fabs(cc)));
+          z[k][t] = act ? zn : z[k][t];
+        }
+      }
+      const bool on = pairk::half_any(moved);
+      solved = solved || (act && !on);
+      act = act && on;
+    }
+
+    // ---- Schur complement on (Ye, e), multipliers and gradient ------------
+    double v4[4] = {0.0, 0.0, 0.0, 0.0}, bz[4];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      const double b0 = S.row[0][t][lane], b1 = S.row[1][t][lane];
+      v4[0] += b0 * z[0][t];
+      v4[1] += b0 * z[1][t];
+      v4[2] += b1 * z[0][t];
+      v4[3] += b1 * z[1][t];
+    }
+    pairk::half_sums4(v4, bz);
+    const double s00 = 1.0 - bz[0], s01 = -bz[1], s10 = -bz[2], s11 = 1.0 - bz[3];
+    const double g_e = a.gbar[2 * pt], g_y = a.gbar[2 * pt + 1];
+    const double r0 = g_y, r1 = -g_e;  // dL/dYe, dL/de
+    const double idet = 1.0 / (s00 * s11 - s01 * s10);
+    const double l0 = (s11 * r0 - s01 * r1) * idet;
+    const double l1 = (s00 * r1 - s10 * r0) * idet;
+    double v2[2] = {0.0, 0.0}, gs[2];
+    g_s = 0.0;
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      const double lam = z[0][t] * l0 + z[1][t] * l1;  // -lambda
+      g_s += lam * S.row[4][t][lane];
+      v2[0] += lam * S.row[2][t][lane];
+      v2[1] += lam * S.row[3][t][lane];
+    }
+    pairk::half_own_sums<1>(v2, gs);
+    g_nes = gs[0];
+    g_pair = gs[1];
+    return solved;
+  }
+};
+
+// What a work-group adds up: the terms of the points of each half, the lane's
+// node and the two amplitudes
+struct AdjSums {
+  double s = 0.0, nes = 0.0, pair = 0.0;
+  // the work-group's row of partial sums, set or added to
+  __device__ __forceinline__ void store(double* __restrict__ row, bool add) const {
+    const int lane = threadIdx.x;
+    const double a = sum_halves(s), b = sum_halves(nes), c = sum_halves(pair);
+    const double v = lane < NQ ? a : (lane == NQ ? b : c);
+    if (lane < NQ + 2) row[lane] = add ? row[lane] + v : v;
+  }
+};
+
+// the terms of point pt, one lane half's worth, to the caller's array
+__device__ __forceinline__ void store_terms(double* grad_pp, int64_t pt, double s, double nes, double pair) {
+  const int q = threadIdx.x & 31;
+  double* gout = grad_pp + pt * (NQ + 2);
+  gout[q] = s;
+  if (q < 2) gout[NQ + q] = q ? pair : nes;
+}
+
+template <int NS>
+__global__ __launch_bounds__(kLanes, 2) void adj_kernel(AdjArgs a) {
+  __shared__ AdjPairLds<NS> S;
+  load_model(a.mdl, a.theta, S.m);
+  const int lane = threadIdx.x, h = lane >> 5;
+  AdjSums sum;
+  const int64_t pairs = (a.P + 1) / 2;
+  for (int64_t u = blockIdx.x; u < pairs; u += gridDim.x) {
+    // past the end of an odd batch the half mirrors its neighbour and counts for nothing
+    const int64_t raw = 2 * u + h;
+    const bool has_point = raw < a.P;
+    const int64_t pt = has_point ? raw : raw - 1;
+    // skipped or failed points contribute nothing
+    const bool live = has_point && a.status[pt] == NMC_STATUS_OK && a.n_outer[pt] != 0;
+    double g_s = 0.0, g_nes = 0.0, g_pair = 0.0;
+    uint64_t left = 0;
+    if (__builtin_amdgcn_ballot_w64(live) != 0) {
+      const bool solved = PairAdjoint<NS>::run(a, pt, live, S, g_s, g_nes, g_pair);
+      if (!solved) g_s = g_nes = g_pair = 0.0;
+      left = __builtin_amdgcn_ballot_w64(live && !solved);
+    }
+    sum.s += g_s;
+    sum.nes += g_nes;
+    sum.pair += g_pair;
+    if (a.grad_pp && has_point) store_terms(a.grad_pp, pt, g_s, g_nes, g_pair);
+    if (lane == 0) a.left[u] = (uint8_t)((left & 1) | ((left >> 32) & 1) << 1);
     __syncthreads();
   }
+  sum.store(a.partial + (int64_t)blockIdx.x * (NQ + 2), false);
+}
+
+// The points that the iteration left over, by elimination: every work-group
+// looks through the flags of its own pairs (the same ones as in adj_kernel, 64
+// at a time) and adds to its own row, so the order of the sums is fixed.
+template <int NS>
+__global__ __launch_bounds__(kLanes) void adj_left_kernel(AdjArgs a) {
+  __shared__ AdjLds<NS> S;
+  const int lane = threadIdx.x, h = lane >> 5;
+  AdjSums sum;
+  bool any = false;
+  const int64_t pairs = (a.P + 1) / 2;
+  for (int64_t u0 = blockIdx.x; u0 < pairs; u0 += (int64_t)kLanes * gridDim.x) {
+    const int64_t u = u0 + (int64_t)lane * gridDim.x;
+    const int f = u < pairs ? a.left[u] : 0;
+    for (uint64_t todo = __builtin_amdgcn_ballot_w64(f != 0); todo != 0; todo &= todo - 1) {
+      const int l = __builtin_ctzll(todo);
+      const int bits = __builtin_amdgcn_readlane(f, l);
+      if (!any) load_model(a.mdl, a.theta, S.m);
+      any = true;
+      for (int k = 0; k < 2; ++k) {
+        if (((bits >> k) & 1) == 0) continue;
+        const int64_t pt = uniform64(2 * (u0 + (int64_t)l * gridDim.x) + k);
+        double g_s, g_nes, g_pair, own, other;
+        PointAdjoint<NS>::run(a, pt, S, g_s, g_nes, g_pair);
+        swap32(g_s, own, other);  // the s_q terms of lanes 0..31 in both halves
+        sum.s += h == 0 ? own : 0.0;
+        sum.nes += h == 0 ? g_nes : 0.0;
+        sum.pair += h == 0 ? g_pair : 0.0;
+        if (a.grad_pp && h == 0) store_terms(a.grad_pp, pt, own, g_nes, g_pair);
+      }
+    }
+  }
+  if (any) sum.store(a.partial + (int64_t)blockIdx.x * (NQ + 2), true);
+}
+
+template <int NS>
+void launch_adjoint_t(const AdjArgs& a, unsigned grid, hipStream_t s) {
+  hipLaunchKernelGGL(adj_kernel<NS>, dim3(grid), dim3(kLanes), 0, s, a);
+  hipLaunchKernelGGL(adj_left_kernel<NS>, dim3(grid), dim3(kLanes), 0, s, a);
+}
+
+// Adds the work-groups' rows of partial sums to out, one work-group per
+// column: thread t adds rows t, t + 256, ... in order, then a fixed-shape tree
+// over the 256 threads.  (One work-group for all 34 columns took 55 us.)
+__global__ __launch_bounds__(256) void reduce_partials(const double* __restrict__ partial, int rows, int ncol,
+                                                       double* __restrict__ out) {
+  __shared__ double red[256];
+  const int t = threadIdx.x, c = blockIdx.x;
+  double s = 0.0;
+  for (int b = t; b < rows; b += 256) s += partial[(int64_t)b * ncol + c];
+  red[t] = s;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if (t < w) red[t] += red[t + w];
+    __syncthreads();
+  }
+  if (t == 0) out[c] += red[0];
 }
 
 }  // namespace
 
-hipError_t launch_adjoint(const AdjArgs& a, int nq, int ns, int num_cu, hipStream_t s) {
+hipError_t launch_adjoint(const AdjArgs& a, int nq, int ns, int num_cu, double* grad_theta, hipStream_t s) {
   if (nq != NQ || ns < 1 || ns > 3) return hipErrorInvalidValue;
   if (a.P == 0) return hipSuccess;
-  const int64_t want = (int64_t)num_cu * 16;
-  const unsigned grid = (unsigned)(a.P < want ? a.P : want);
+  const int64_t pairs = (a.P + 1) / 2;
+  int64_t grid = (int64_t)num_cu * 8;  // two work-groups per SIMD stay resident
+  if (grid > pairs) grid = pairs;
+  if (grid > kAdjPartials) grid = kAdjPartials;
   switch (ns) {
-    case 1: hipLaunchKernelGGL(adj_kernel<1>, dim3(grid), dim3(kLanes), 0, s, a); break;
-    case 2: hipLaunchKernelGGL(adj_kernel<2>, dim3(grid), dim3(kLanes), 0, s, a); break;
-    default: hipLaunchKernelGGL(adj_kernel<3>, dim3(grid), dim3(kLanes), 0, s, a); break;
+    case 1: launch_adjoint_t<1>(a, (unsigned)grid, s); break;
+    case 2: launch_adjoint_t<2>(a, (unsigned)grid, s); break;
+    default: launch_adjoint_t<3>(a, (unsigned)grid, s); break;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_reduce_columns(const double* x, int64_t P, int ncol, double* partial, double* out,
-                                 hipStream_t s) {
-  if (P == 0) return hipSuccess;
-  if (ncol > 256) return hipErrorInvalidValue;
-  const int64_t nblk = P < kReduceBlocks ? P : kReduceBlocks;
-  const int64_t rows = (P + nblk - 1) / nblk;
-  const int64_t used = (P + rows - 1) / rows;
-  hipLaunchKernelGGL(reduce_stage1, dim3((unsigned)used), dim3(256), 0, s, x, P, ncol, rows, partial);
-  hipLaunchKernelGGL(reduce_stage2, dim3(1), dim3(256), 0, s, partial, (int)used, ncol, out);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(reduce_partials, dim3(NQ + 2), dim3(256), 0, s, a.partial, (int)grid, NQ + 2, grad_theta);
   return hipGetLastError();
 }
 

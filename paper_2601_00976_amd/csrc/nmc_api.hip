@@ -350,13 +350,17 @@ int nmc_model_destroy(nmc_model* m) {
   return e == hipSuccess ? NMC_OK : hip_fail(e, "model_destroy");
 }
 
+static size_t adj_partial_bytes(const nmc_model* m, int64_t P) {
+  const size_t pairs = ((size_t)P + 1) / 2, most = (size_t)nmc::kAdjPartials;
+  return ((pairs < most ? pairs : most) * ((size_t)m->host.nq + 2) * sizeof(double) + 255) & ~(size_t)255;
+}
+
 size_t nmc_workspace_bytes(const nmc_model* m, int64_t P) {
   if (!m || P < 0) return 0;
-  // queue counters + per-point adjoint terms and a column-partial buffer
-  const size_t nt = (size_t)m->host.nq + 2;
-  const size_t pp = ((size_t)P * nt * sizeof(double) + 255) & ~(size_t)255;
-  const size_t part = ((size_t)nmc::kReduceBlocks * nt * sizeof(double) + 255) & ~(size_t)255;
-  return kCounterBytes + pp + part;
+  // queue counters + the adjoint's rows of partial sums, one per work-group,
+  // and its flags, one byte per pair of points
+  const size_t pairs = ((size_t)P + 1) / 2;
+  return kCounterBytes + adj_partial_bytes(m, P) + ((pairs + 255) & ~(size_t)255);
 }
 
 size_t nmc_kernel_store_bytes(const nmc_model* m, int64_t P) {
@@ -721,9 +725,6 @@ int nmc_solve_batch_adjoint(const nmc_model* m, const nmc_solver_params* prm, in
     return fail(NMC_E_INVALID_ARG, "adjoint: null array");
   if (!ws || !aligned256(ws) || ws_bytes < nmc_workspace_bytes(m, P))
     return fail(NMC_E_WORKSPACE, "adjoint: workspace must be 256-byte aligned and at least nmc_workspace_bytes");
-  const int nt = m->host.nq + 2;
-  const size_t pp = ((size_t)P * nt * sizeof(double) + 255) & ~(size_t)255;
-  char* w = (char*)ws + kCounterBytes;
   nmc::AdjArgs a;
   memset(&a, 0, sizeof(a));
   a.mdl = m->dev;
@@ -738,13 +739,11 @@ int nmc_solve_batch_adjoint(const nmc_model* m, const nmc_solver_params* prm, in
   a.status = fwd->status;
   a.n_outer = fwd->n_outer;
   a.gbar = gbar;
-  a.grad_pp = grad_pp ? grad_pp : (double*)w;
-  hipStream_t s = (hipStream_t)stream;
-  hipError_t e = nmc::launch_adjoint(a, m->host.nq, m->host.ns, m->num_cu, s);
-  if (e != hipSuccess) return hip_fail(e, "adjoint: launch");
-  e = nmc::launch_reduce_columns(a.grad_pp, P, nt, (double*)(w + pp), grad_theta, s);
-  if (e != hipSuccess) return hip_fail(e, "adjoint: reduction");
-  return NMC_OK;
+  a.grad_pp = grad_pp;
+  a.partial = (double*)((char*)ws + kCounterBytes);
+  a.left = (uint8_t*)ws + kCounterBytes + adj_partial_bytes(m, P);
+  hipError_t e = nmc::launch_adjoint(a, m->host.nq, m->host.ns, m->num_cu, grad_theta, (hipStream_t)stream);
+  return e == hipSuccess ? NMC_OK : hip_fail(e, "adjoint: launch");
 }
 
 int nmc_init_state(const nmc_model* m, int64_t P, const double* T, const double* mu, const double* rho11,

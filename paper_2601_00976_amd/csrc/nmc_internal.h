@@ -10,7 +10,7 @@ namespace nmc {
 
 constexpr int kMaxNq = 64;
 constexpr int kMaxNs = 3;
-constexpr int kReduceBlocks = 1024;  // first-stage blocks of the point reduction
+constexpr int kAdjPartials = 4096;  // most work-groups of the adjoint, a row of partial sums each
 
 // Model table resident in device memory.  The kernels copy the per-node
 // tables into LDS once per work-group and read the uniform scalars through
@@ -111,7 +111,9 @@ struct AdjArgs {
   const double *D, *ye, *e;
   const int32_t *status, *n_outer;
   const double* gbar;
-  double* grad_pp;     // (P, nq + 2) per-point terms, always written
+  double* grad_pp;     // (P, nq + 2) per-point terms or nullptr
+  double* partial;     // (work-groups, nq + 2) partial sums
+  uint8_t* left;       // per pair of points: bit h set where half h is left to the elimination
 };
 
 // How a solve over `units` (points, or pairs of points) is launched.
@@ -176,8 +178,7 @@ hipError_t launch_pdars_merge(int64_t P, int nn, const int32_t* no2, const int32
 hipError_t launch_init_state(const DevModel* mdl, int ns, int nq, int64_t P, const double* T, const double* mu,
                              const double* rho11, const double* ye, const double* uD, const double* uI, double a,
                              double b, double c, double* D0, double* I0, double* e0, hipStream_t s);
-hipError_t launch_adjoint(const AdjArgs& a, int nq, int ns, int num_cu, hipStream_t s);
-hipError_t launch_reduce_columns(const double* grad_pp, int64_t P, int ncol, double* partial, double* grad_theta,
-                                 hipStream_t s);
+// adds the sum over points to grad_theta (nq + 2)
+hipError_t launch_adjoint(const AdjArgs& a, int nq, int ns, int num_cu, double* grad_theta, hipStream_t s);
 
 }  // namespace nmc
