@@ -376,6 +376,8 @@ class NMCSolve(torch.autograd.Function):
         if params.fixed_matter:
             raise NotImplementedError("NMCSolve: the adjoint differentiates the coupled system; "
                                       "fixed_matter is not supported")
+        # outputs that no loss uses get no cotangent at all, rather than zeros the size of the moments
+        ctx.set_materialize_grads(False)
         out = solve(model, params, dtau, D0, I0, rho11, ye0, e0, theta)
         ctx.model, ctx.dtau, ctx.params = model, dtau, params
         ctx.out = out
@@ -388,10 +390,11 @@ class NMCSolve(torch.autograd.Function):
             if g is not None and bool(torch.any(g != 0)):
                 raise NotImplementedError(f"NMCSolve.backward: cotangents on {n} are not supported")
         theta, rho11 = ctx.saved_tensors
-        P = rho11.shape[0]
-        z = torch.zeros(P, dtype=torch.float64, device=rho11.device)
-        gE = (gLE if gLE is not None else z) - (ge if ge is not None else z)
-        gY = (gLY if gLY is not None else z) + (gYe if gYe is not None else z)
+        # dL/dL_E - dL/de and dL/dL_Y + dL/dYe; what the loss does not use is None
+        gE = gLE if ge is None else (-ge if gLE is None else gLE - ge)
+        gY = gLY if gYe is None else (gYe if gLY is None else gLY + gYe)
+        z = torch.zeros_like(rho11) if gE is None or gY is None else None
+        gE, gY = (z if g is None else g for g in (gE, gY))
         gbar = torch.stack([gE, gY], dim=1).contiguous()
         g = adjoint(ctx.model, ctx.dtau, rho11, theta, ctx.out, gbar, params=ctx.params)
         return g, None, None, None, None, None, None, None, None
