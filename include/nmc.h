@@ -181,17 +181,20 @@ typedef struct {
 
 /* Where the energy-coupling kernel matrices live during a solve, and how
  * the 32-node solve maps points to wavefronts.
- * ON_CHIP: the library's default.  32 nodes: as PAIRED; 64 nodes: as REGEN.
+ * ON_CHIP: the library's default.  32 nodes: as PAIRED; 64 nodes: row q of
+ *   the symmetric core exp(-|e - e'| / T) that all four kernels share in the
+ *   registers of lane q, formed once per outer iteration.
  * HBM: 64-node solve only, for the roofline study of precomputed kernels:
- *   Phi_in, Phi_out and Phi_ann of every point are written to the workspace
- *   once per outer iteration and re-read by every inner iteration; the
- *   workspace then needs nmc_kernel_store_bytes(m, P) more bytes after the
+ *   the core of every point is written to the workspace once per outer
+ *   iteration and re-read by every inner iteration; the workspace then needs
+ *   nmc_kernel_store_bytes(m, P) more bytes after the
  *   nmc_workspace_bytes(m, P) ones. */
 #define NMC_KERNELS_ON_CHIP 0
 #define NMC_KERNELS_HBM 1
 /* REGEN: kernel entries regenerated from per-node factors in every inner
- * iteration, nothing stored (the 64-node solve always works this way; for 32
- * nodes it is an alternative to the register-resident rows). */
+ * iteration, nothing stored (32 nodes: an alternative to the register-resident
+ * rows; the 64-node solve takes it as ON_CHIP and regenerates by itself at
+ * points too cold for its rows). */
 #define NMC_KERNELS_REGEN 2
 /* REGISTERS: 32 nodes only: the kernel rows are assembled once per outer
  * iteration (LDS tile) and held in VGPRs; the inner iterations contract them
@@ -229,7 +232,8 @@ int nmc_model_destroy(nmc_model* m);
 /* Bytes of device workspace a solve call with P points needs. */
 size_t nmc_workspace_bytes(const nmc_model* m, int64_t P);
 /* Extra workspace bytes of a solve with kernel_store = NMC_KERNELS_HBM:
- * 3 nq^2 doubles per point (0 if the model cannot use that mode). */
+ * 3 nq^2 doubles per point, of which the core takes the first nq^2 (0 if the
+ * model cannot use that mode). */
 size_t nmc_kernel_store_bytes(const nmc_model* m, int64_t P);
 
 /* Batched forward solve: Algorithm neutrinoMatterCoupling at every point.

@@ -6,34 +6,50 @@
 // occupancy, in LDS, so they are not stored at all.
 //
 // One 64-lane wavefront solves one point; lane q owns D_s[q] and I_s[q] of
-// every species.  In each inner iteration a lane regenerates row q of
-// Phi_in, Phi_out, Phi_ann and Phi_pro column by column from per-node
-// exponent splits broadcast from LDS and accumulates the four rate
-// contractions (Eqs. nesRatesNodal, pairRatesNodal) on the fly.  For column
-// j and row q, with (lo, hi) the lower / higher node of the pair:
+// every species.  All four kernels share one symmetric core: with
+// g = exp(-e / (2T)), h = g^2 and B2(q, j) = exp(-|e_q - e_j| / T),
+//   Phi_in[q][j] = A e_q e_j B2 g_q / g_j,  Phi_out[q][j] = A e_q e_j B2 g_j / g_q,
+//   Phi_ann = A' e_q e_j B2,                Phi_pro = A' e_q e_j B2 h_q h_j,
+// so a lane keeps row q of B2 (64 doubles) in VGPRs, formed once per outer
+// iteration, and every inner iteration contracts it against W e D / g,
+// g W e (1 - D), W e D and h W e (1 - D).  The vectors are redistributed with
+// v_permlane32_swap and v_permlane16_swap, so that every 16-lane row holds
+// each quarter of them, and the FMAs take column j by DPP row_newbcast: 12
+// FMAs per column for three species and no LDS.  One kind of vector is
+// contracted at a time (24 VGPRs of quarters instead of 96), which keeps two
+// waves per SIMD.  g and 1 / g are scaled by 2^+-c, c the middle of the
+// point's exponent range.  The multiply-adds' issue and, for small batches,
+// the dependent reductions bound it: 131072 points of the radial profile take
+// 3.14 ms (4.84 ms with every column regenerated from LDS in every inner
+// iteration, twice the instructions), 1001 points 122 us (233 us).
+//
+// Where the grid spans more than kDirectBits64 powers of two in g (T below
+// ~0.22 MeV) the lanes instead regenerate their rows column by column in every
+// inner iteration from per-node exponent splits broadcast from LDS (`rates`).
+// With (lo, hi) the lower / higher node of the pair:
 //   b = exp(-(e_hi - e_lo) / (2T)) = ldexp(P_lo R_hi, n_lo - n_hi),
 //   Phi_in[q][j] = A e_q e_j (j > q ? b : b^3),  Phi_out[q][j] = A e_q e_j (j > q ? b^3 : b),
 //   Phi_ann[q][j] = A' e_q e_j b^2,              Phi_pro[q][j] = A' e_q e_j G_hi,
-// with x = e log2(e) / (2T) = n + f, P = 2^f, R = 2^-f, G = exp(-2 e / T).
-// The lanes form the entries without their common factor A e_q e_j (A' e_q
-// e_j for pair), contract them against W e D and W e (1 - D) and scale the
-// row sums by A e_q (A' e_q).  Anderson sums, norms and matter integrals are
+// with x = e log2(e) / (2T) = n + f, P = 2^f, R = 2^-f, G = exp(-2 e / T):
+// every factor at most 1.  Anderson sums, norms and matter integrals are
 // full-wave register reductions.
 //
 // The PRE variant (kernel_store = HBM; the roofline study of precomputed
-// kernels) writes the scaled Phi_in, Phi_out and Phi_ann of the point to the
-// workspace once per outer iteration, laid out [matrix][column j][row q] so
-// that every access is a coalesced 512-byte wave load or store, and reads
-// them back in every inner iteration (the scaled Phi_pro is G_hi, a stored
-// per-node factor).  Each lane reads only what it wrote, so no barrier is
-// needed between the two.  Both variants perform the same floating-point
-// operations on the same values, so their results agree bit for bit.
+// kernels) writes the point's core to the workspace once per outer iteration,
+// laid out [column j][row q] so that every access is a coalesced 512-byte
+// wave load or store, and reads it back in every inner iteration.  Each lane
+// reads only what it wrote, so no barrier is needed between the two.  Both
+// variants perform the same floating-point operations on the same values, so
+// their results agree bit for bit.
 #include "nmc_wave.h"
 
 namespace nmc {
 namespace {
 
 constexpr int NQ64 = 64;
+// widest exponent range of g for the register rows: squares of the scaled
+// factors and their reciprocals stay inside the normal range
+constexpr int kDirectBits64 = 1000;
 
 template <int NS>
 struct Lds64 {
@@ -74,7 +90,7 @@ struct PointSolver64 {
   // factor A e_q e_j (A' e_q e_j for pair): e_j rides on the contracted
   // vectors and A e_q scales the row sums
   struct Row {
-    double Pq, Rq, Gq, Aeq, Apq;
+    double Pq, Rq, Gq;
     int nq;
   };
   __device__ __forceinline__ static Row row_consts(const Lds64<NS>& S, int q) {
@@ -82,10 +98,7 @@ struct PointSolver64 {
     r.Pq = S.colPR[q][0];
     r.Rq = S.colPR[q][1];
     r.Gq = S.colGE[q][0];
-    const double eq = S.m.eps[q];
     r.nq = S.coln[q];
-    r.Aeq = S.An * eq;
-    r.Apq = S.Ap * eq;
     return r;
   }
   // per-node data of column j, read from LDS one column ahead of its use
@@ -137,79 +150,84 @@ struct PointSolver64 {
     }
   }
 
-  // rates of the energy-coupling kernels for every species at the current
-  // iterate: etaN = Phi_in W D_s, outN = Phi_out W (1 - D_s),
-  // annP = Phi_ann W D_sbar, etaP = Phi_pro W (1 - D_sbar); X holds W e D
-  __device__ __forceinline__ static void rates(const Lds64<NS>& S, int q, const double* __restrict__ kst,
-                                               double (&etaN)[NS], double (&outN)[NS], double (&annP)[NS],
-                                               double (&etaP)[NS]) {
-#pragma unroll
-    for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
+  // The four contractions of every species at the current iterate, columns
+  // regenerated from the splits in LDS (X holds W e D): etaN = Phi_in W D_s,
+  // outN = Phi_out W (1 - D_s), annP = Phi_ann W D_sbar,
+  // etaP = Phi_pro W (1 - D_sbar), without the factors A e_q of the row
+  __device__ __forceinline__ static void rates(const Lds64<NS>& S, int q, double (&etaN)[NS], double (&outN)[NS],
+                                               double (&annP)[NS], double (&etaP)[NS]) {
     const Row r = row_consts(S, q);
-    auto column = [&](const Col& c, int j) __attribute__((always_inline)) {
+    auto column = [&](const Col& c) __attribute__((always_inline)) {
       double fin, fout, fann, fpro;
-      if constexpr (PRE) {
-        fin = kst[j * NQ + q];
-        fout = kst[(NQ + j) * NQ + q];
-        fann = kst[(2 * NQ + j) * NQ + q];
-        fpro = min_f64(c.G, r.Gq);
-      } else {
-        entries(c, r, fin, fout, fann, fpro);
-      }
+      entries(c, r, fin, fout, fann, fpro);
       accumulate(c, fin, fout, fann, fpro, etaN, outN, annP, etaP);
     };
     // two column buffers in turn: the reads of one overlap the work on the
     // other (the last trip re-reads column 0, unused)
     Col ca = load_col(S, 0), cb;
-#pragma unroll 2
+#pragma unroll 1
     for (int j = 0; j < NQ; j += 2) {
       cb = load_col(S, j + 1);
-      column(ca, j);
+      column(ca);
       ca = load_col(S, (j + 2) & (NQ - 1));
-      column(cb, j + 1);
-    }
-#pragma unroll
-    for (int t = 0; t < NS; ++t) {
-      etaN[t] *= r.Aeq;
-      outN[t] *= r.Aeq;
-      annP[t] *= r.Apq;
-      etaP[t] *= r.Apq;
+      column(cb);
     }
   }
 
-  // PRE: Phi_in, Phi_out, Phi_ann row q of the current temperature to HBM
-  __device__ __forceinline__ static void store_rows(const Lds64<NS>& S, int q, double* __restrict__ kst) {
-    const Row r = row_consts(S, q);
-#pragma unroll 4
-    for (int j = 0; j < NQ; ++j) {
-      double fin, fout, fann, fpro;
-      entries(load_col(S, j), r, fin, fout, fann, fpro);
-      kst[j * NQ + q] = fin;
-      kst[(NQ + j) * NQ + q] = fout;
-      kst[(2 * NQ + j) * NQ + q] = fann;
+  // v of every lane, quarter k of the nodes in V[k] of every 16-lane row
+  __device__ __forceinline__ static void quarters(double v, double& v0, double& v1, double& v2, double& v3) {
+    double lo, hi;
+    swap32(v, lo, hi);
+    swap16(lo, v0, v1);
+    swap16(hi, v2, v3);
+  }
+  // acc[t] = sum_j B2(q, j) x_t[j], the row in B (or, stored, at kst)
+  __device__ __forceinline__ static void contract(const double (&x)[NS], const double (&B)[PRE ? 1 : NQ],
+                                                  const double* __restrict__ kst, double (&acc)[NS]) {
+    double V[4][NS];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      quarters(x[t], V[0][t], V[1][t], V[2][t], V[3][t]);
+      acc[t] = 0.0;
     }
+    static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
+      constexpr int j = 4 * decltype(jj)::value;
+      if constexpr (PRE)
+        Fmac1x4<NS>::template run<j % 16>(acc, V[j / 16], kst[j * NQ], kst[(j + 1) * NQ], kst[(j + 2) * NQ],
+                                          kst[(j + 3) * NQ]);
+      else
+        Fmac1x4<NS>::template run<j % 16>(acc, V[j / 16], B[j], B[j + 1], B[j + 2], B[j + 3]);
+    });
   }
 
   // settle() is called once the point's inputs are loaded (work-queue hook)
   template <class Settle>
-  __device__ static void solve(const FwdArgs& a, int64_t p, Lds64<NS>& S, Settle&& settle) {
-    const_ptr<DevModel> md = scalar_ptr(a.mdl);
+  __device__ static void solve(int64_t p, Lds64<NS>& S, Settle&& settle) {
+    const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
+    const_ptr<DevModel> md = scalar_ptr(a->mdl);
     const ModelLdsN<NQ>& mt = S.m;
     const int lane = threadIdx.x;
     const int q0 = lane;
-    const double dtau = a.dtau;
+    const double dtau = a->dtau;
     const int64_t base = p * (int64_t)(NS * NQ);
-    const double rho = a.rho11[p];
-    const bool fixedT = a.prm.fixed_matter && a.T_fixed;
-    double* __restrict__ kst = PRE ? a.kstore + p * (int64_t)(3 * NQ * NQ) : nullptr;
+    const double rho = in_global(a->rho11)[p];
+    const bool fixedT = a->prm.fixed_matter && a->T_fixed;
+    // this lane's column of the stored core
+    double* __restrict__ kst = PRE ? a->kstore + p * (int64_t)(NQ * NQ) + lane : nullptr;
 
-    double Dst[NS], Ist[NS], D[NS], I[NS];
+    double D[NS], I[NS];
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
       const int64_t o = base + md->ext[t] * NQ + lane;
-      Dst[t] = D[t] = a.D0[o];
-      Ist[t] = I[t] = a.I0[o];
+      D[t] = in_global(a->D0)[o];
+      I[t] = in_global(a->I0)[o];
     }
+    // the old moments are read again where they are used (the outputs, which
+    // may be the same arrays, are written at the end), so that they hold no
+    // registers beside the row of the core
+    auto old = [&](const double* x, int t, const_ptr<DevModel> m) {
+      return in_global(x)[base + m->ext[t] * NQ + opaque(lane)];
+    };
 
     settle();
     if (rho < md->rho11_min) {
@@ -217,18 +235,18 @@ struct PointSolver64 {
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
         const int64_t o = base + md->ext[t] * NQ + lane;
-        a.D[o] = D[t];
-        a.I[o] = I[t];
+        in_global(a->D)[o] = D[t];
+        in_global(a->I)[o] = I[t];
       }
       if (lane == 0) {
-        const double ye_st = a.ye0[p], e_st = a.e0[p];
-        a.ye[p] = ye_st;
-        a.e[p] = e_st;
-        a.T[p] = fixedT ? a.T_fixed[p]
+        const double ye_st = in_global(a->ye0)[p], e_st = in_global(a->e0)[p];
+        in_global(a->ye)[p] = ye_st;
+        in_global(a->e)[p] = e_st;
+        in_global(a->T)[p] = fixedT ? in_global(a->T_fixed)[p]
                         : (e_st - md->eos_b * ye43(ye_st) * cbrt(rho)) / (md->eos_a * (1.0 + ye_st));
-        a.n_outer[p] = 0;
-        a.n_inner[p] = 0;
-        a.status[p] = NMC_STATUS_OK;
+        in_global(a->n_outer)[p] = 0;
+        in_global(a->n_inner)[p] = 0;
+        in_global(a->status)[p] = NMC_STATUS_OK;
       }
       return;
     }
@@ -246,11 +264,11 @@ struct PointSolver64 {
 #pragma unroll
       for (int t = 0; t < NS; ++t) S.dref[t] = s[t];
     }
-    S.ye_st = S.y[0] = a.ye0[p];
-    S.e_st = S.y[1] = a.e0[p];
-    S.chi0 = a.chi0 ? a.chi0[p] : md->chi_ref * rho;
-    if (fixedT) S.T_fix = a.T_fixed[p];
-    if (a.prm.fixed_matter && a.mu_fixed) S.mu_fix = a.mu_fixed[p];
+    S.ye_st = S.y[0] = in_global(a->ye0)[p];
+    S.e_st = S.y[1] = in_global(a->e0)[p];
+    S.chi0 = a->chi0 ? in_global(a->chi0)[p] : md->chi_ref * rho;
+    if (fixedT) S.T_fix = in_global(a->T_fixed)[p];
+    if (a->prm.fixed_matter && a->mu_fixed) S.mu_fix = in_global(a->mu_fixed)[p];
 #pragma unroll
     for (int i = 0; i < 2; ++i) S.oq[i] = S.of[i] = S.odq[i] = S.odf[i] = 0.0;
     S.T_last = 0.0;
@@ -259,16 +277,17 @@ struct PointSolver64 {
     bool fatal = false, inner_failed = false, outer_conv = false;
     int k, total_inner = 0;
 
-    for (k = 1; k <= a.prm.max_outer; ++k) {
+    for (k = 1; k <= a->prm.max_outer; ++k) {
       // per-iteration opaque copies keep lane invariants from being hoisted
       // out of this loop (and spilled)
-      const_ptr<DevModel> md = scalar_ptr(a.mdl);
+      const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
+      const_ptr<DevModel> md = scalar_ptr(a->mdl);
       const int q = opaque(q0);
       // ---- ComputeOpacities(y^[k]) --------------------------------------
       const double r3 = S.r3;
       const double y0 = S.y[0], y1 = S.y[1];
       const double T = fixedT ? S.T_fix : (y1 - md->eos_b * ye43(y0) * r3) / (md->eos_a * (1.0 + y0));
-      const double mu = (a.prm.fixed_matter && a.mu_fixed)
+      const double mu = (a->prm.fixed_matter && a->mu_fixed)
                             ? S.mu_fix
                             : md->mu_a * (y0 - md->mu_ye0) * r3 + md->mu_b * log(T / md->mu_t0);
       if (!(T > 0.0) || !(y0 >= 0.0) || !isfinite(T) || !isfinite(mu)) {
@@ -280,7 +299,8 @@ struct PointSolver64 {
       const double invT = 1.0 / T;
       // constant parts of the numerator and denominators of Q (Eqs.
       // emissivityEmAbNodal, transportOpacityNodal, implicitMomentsNodal)
-      double baseD[NS], den0D[NS], den0I[NS];
+      double baseD[NS], den0D[NS];
+      double dsig = 0.0;  // dtau sigma: 1 + dtau kappa = 1 + dtau chi + dsig
       const double epsq = mt.eps[q];
       {
         const double chi0 = S.chi0;
@@ -294,55 +314,102 @@ struct PointSolver64 {
           const double ex = exp(-fabs(x));
           const double r = rcp_nr(1.0 + ex);
           const double deq = x > 0.0 ? ex * r : r;
-          baseD[t] = Dst[t] + dtau * (chia * deq);
+          baseD[t] = old(a->D0, t, md) + dtau * (chia * deq);
           den0D[t] = 1.0 + dtau * chia;
-          den0I[t] = 1.0 + dtau * (chia + sig);
         }
+        dsig = dtau * sig;
       }
+      // row q of the core and the node's factors, or the splits in LDS
+      double B[COUPLED && !PRE ? NQ : 1];
+      double gq = 1.0, rgq = 1.0, hq = 1.0;
+      bool direct = false;  // uniform
       if constexpr (COUPLED) {
         const ExpSplit xs = exp_split(epsq, invT);
-        const double R2 = xs.R * xs.R;
-        S.colPR[q][0] = xs.P;
-        S.colPR[q][1] = xs.R;
-        S.colGE[q][0] = ldexp(R2 * R2, -4 * xs.n);  // exp(-2 e / T)
-        S.colGE[q][1] = mt.w2[q] * epsq;
-        S.coln[q] = xs.n;
-        if constexpr (PRE) {
-          __syncthreads();
-          store_rows(S, q, kst);
+        const int nlo = __builtin_amdgcn_readlane(xs.n, 0), nhi = __builtin_amdgcn_readlane(xs.n, NQ - 1);
+        direct = nhi - nlo <= kDirectBits64;
+        if (direct) {
+          const int c = (nlo + nhi) >> 1;
+          gq = ldexp(xs.R, c - xs.n);
+          rgq = ldexp(xs.P, xs.n - c);
+          hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
+          const double ht = gq * gq, rht = rgq * rgq;
+          double H[4], RH[4];
+          quarters(ht, H[0], H[1], H[2], H[3]);
+          quarters(rht, RH[0], RH[1], RH[2], RH[3]);
+          // of the two orientations h_j / h_q and h_q / h_j the smaller is B2
+          // (the other is its reciprocal, or overflows to +inf)
+          static_for<0, NQ>([&](auto jj) __attribute__((always_inline)) {
+            constexpr int j = decltype(jj)::value;
+            const double b = min_f64(row_bcast<j % 16>(H[j / 16]) * rht, ht * row_bcast<j % 16>(RH[j / 16]));
+            if constexpr (PRE) kst[j * NQ] = b;
+            else B[j] = b;
+          });
+        } else {
+          const double R2 = xs.R * xs.R;
+          S.colPR[q][0] = xs.P;
+          S.colPR[q][1] = xs.R;
+          S.colGE[q][0] = ldexp(R2 * R2, -4 * xs.n);  // exp(-2 e / T)
+          S.colGE[q][1] = mt.w2[q] * epsq;
+          S.coln[q] = xs.n;
         }
       }
 
       // ---- inner loop over moments at fixed matter ------------------------
-      const double w2q = mt.w2[q], w2eq = w2q * mt.eps[q];
+      const double w2q = mt.w2[q], w2eq = w2q * epsq;
+      const double Aeq = S.An * epsq, Apq = S.Ap * epsq;
       double G11 = 0.0;
       bool conv = false;
+      const int m_inner = held(a->prm.m_inner), max_inner = held(a->prm.max_inner);
+      const double tol2 = held(a->tol_inner2);
+      const double* I0 = held(a->I0);
       int l;
-      for (l = 1; l <= a.prm.max_inner; ++l) {
+      for (l = 1; l <= max_inner; ++l) {
         double etaN[NS], outN[NS], annP[NS], etaP[NS];
+#pragma unroll
+        for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
         if constexpr (COUPLED) {
+          if (direct) {
+            if constexpr (!PRE) {
 #pragma unroll
-          for (int t = 0; t < NS; ++t) S.X[t][q] = w2eq * D[t];
-          __syncthreads();
-          rates(S, q, kst, etaN, outN, annP, etaP);
-          __syncthreads();
-        } else {
+              for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+            }
+            double x[NS];
 #pragma unroll
-          for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
+            for (int t = 0; t < NS; ++t) x[t] = w2eq * D[t] * rgq;
+            contract(x, B, kst, etaN);
+#pragma unroll
+            for (int t = 0; t < NS; ++t) x[t] = __builtin_fma(-w2eq, D[t], w2eq) * gq;
+            contract(x, B, kst, outN);
+#pragma unroll
+            for (int t = 0; t < NS; ++t) x[t] = w2eq * D[pair_partner<NS>(t)];
+            contract(x, B, kst, annP);
+#pragma unroll
+            for (int t = 0; t < NS; ++t) x[t] = hq * __builtin_fma(-w2eq, D[pair_partner<NS>(t)], w2eq);
+            contract(x, B, kst, etaP);
+          } else {
+#pragma unroll
+            for (int t = 0; t < NS; ++t) S.X[t][q] = w2eq * D[t];
+            __syncthreads();
+            rates(S, q, etaN, outN, annP, etaP);
+            __syncthreads();
+          }
         }
         // Q and residual of both moments (owned entries x = (D_t, I_t))
         double Qx[2 * NS], Fx[2 * NS];
 #pragma unroll
         for (int t = 0; t < NS; ++t) {
-          const double eta = etaN[t] + etaP[t];
-          const double chi = (etaN[t] + outN[t]) + (etaP[t] + annP[t]);
-          Qx[t] = __builtin_fma(dtau, eta, baseD[t]) * rcp_nr(__builtin_fma(dtau, chi, den0D[t]));
-          Qx[NS + t] = Ist[t] * rcp_nr(__builtin_fma(dtau, chi, den0I[t]));
+          const double eta = __builtin_fma(Aeq * gq, etaN[t], Apq * hq * etaP[t]);
+          const double chi = __builtin_fma(Aeq * rgq, outN[t], __builtin_fma(Apq, annP[t], eta));
+          // one reciprocal of the product of the two denominators serves both
+          const double dD = __builtin_fma(dtau, chi, den0D[t]), dI = dD + dsig;
+          const double r = rcp_nr(dD * dI);
+          Qx[t] = __builtin_fma(dtau, eta, baseD[t]) * (r * dI);
+          Qx[NS + t] = old(I0, t, md) * (r * dD);
           Fx[t] = Qx[t] - D[t];
           Fx[NS + t] = Qx[NS + t] - I[t];
         }
         // Anderson step over min(l, M_inner) residuals (difference form)
-        const int mem = l < a.prm.m_inner ? l : a.prm.m_inner;
+        const int mem = l < m_inner ? l : m_inner;
         double Xn[2 * NS];
         if (mem == 1) {
           // clear the older difference column (weighted zero at the second
@@ -410,7 +477,7 @@ struct PointSolver64 {
           const int cls = lane >> 4;
           const double d0 = cls < NS ? S.dref[cls < NS ? cls : 0] : 0.0;
           const double dref2 = d0 > dn2 ? d0 : dn2;
-          conv = __builtin_amdgcn_ballot_w64(!(dm2 <= a.tol_inner2 * dref2)) == 0;
+          conv = __builtin_amdgcn_ballot_w64(!(dm2 <= tol2 * dref2)) == 0;
           if (conv && cls < NS) S.dref[cls < NS ? cls : 0] = dn2;
         }
 #pragma unroll
@@ -420,7 +487,7 @@ struct PointSolver64 {
         }
         if (conv) break;
       }
-      total_inner += (l > a.prm.max_inner ? a.prm.max_inner : l);
+      total_inner += (l > max_inner ? max_inner : l);
       if (fatal) break;
       if (!conv) {
         inner_failed = true;
@@ -431,7 +498,7 @@ struct PointSolver64 {
 #pragma unroll
         for (int t = 0; t < NS; ++t) S.dref[t] = s[t];
       }
-      if (a.prm.fixed_matter) {
+      if (a->prm.fixed_matter) {
         outer_conv = true;
         break;
       }
@@ -443,7 +510,7 @@ struct PointSolver64 {
         double mv[2] = {0.0, 0.0}, s[2];
 #pragma unroll
         for (int t = 0; t < NS; ++t) {
-          const double dd = D[t] - Dst[t];
+          const double dd = D[t] - old(a->D0, t, md);
           mv[0] += md->ig[t] * w2q * dd;
           mv[1] += md->imult[t] * w3 * dd;
         }
@@ -452,7 +519,7 @@ struct PointSolver64 {
         yq1 = S.e_st - S.K * s[1];
       }
       const double f0 = yq0 - S.y[0], f1 = yq1 - S.y[1];
-      const int omem = k < a.prm.m_outer ? k : a.prm.m_outer;
+      const int omem = k < a->prm.m_outer ? k : a->prm.m_outer;
       double yn0, yn1;
       if (omem == 1) {
         yn0 = yq0;
@@ -482,8 +549,8 @@ struct PointSolver64 {
         fatal = true;
         break;
       }
-      const bool oc = fabs(yn0 - S.y[0]) <= a.prm.tol_outer * fabs(S.ye_st) &&
-                      fabs(yn1 - S.y[1]) <= a.prm.tol_outer * fabs(S.e_st);
+      const bool oc = fabs(yn0 - S.y[0]) <= a->prm.tol_outer * fabs(S.ye_st) &&
+                      fabs(yn1 - S.y[1]) <= a->prm.tol_outer * fabs(S.e_st);
       S.y[0] = yn0;
       S.y[1] = yn1;
       if (oc) {
@@ -491,51 +558,53 @@ struct PointSolver64 {
         break;
       }
     }
-    if (k > a.prm.max_outer) k = a.prm.max_outer;
+    if (k > a->prm.max_outer) k = a->prm.max_outer;
     if (!fatal) {
       if (!outer_conv) status = NMC_STATUS_MAX_OUTER;
       else if (inner_failed) status = NMC_STATUS_MAX_INNER;
     }
 
     // ---- outputs --------------------------------------------------------
+    const_ptr<FwdArgs> ao = kernel_args<FwdArgs>();
+    const_ptr<DevModel> mo = scalar_ptr(ao->mdl);
     const double ye_st = S.ye_st, e_st = S.e_st;
     double ye_out = ye_st, e_out = e_st, T_out = S.T_last;
-    if (!a.prm.fixed_matter) {
+    if (!ao->prm.fixed_matter) {
       const double w2 = mt.w2[q0], w3 = mt.w3[q0];
       double mv[2] = {0.0, 0.0}, s[2];
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
-        const double dd = D[t] - Dst[t];
-        mv[0] += md->ig[t] * w2 * dd;
-        mv[1] += md->imult[t] * w3 * dd;
+        const double dd = D[t] - old(ao->D0, t, mo);
+        mv[0] += mo->ig[t] * w2 * dd;
+        mv[1] += mo->imult[t] * w3 * dd;
       }
       wave_sums<2>(mv, s);
       ye_out = ye_st - S.K * s[0];
       e_out = e_st - S.K * s[1];
-      T_out = (e_out - md->eos_b * ye43(ye_out) * S.r3) / (md->eos_a * (1.0 + ye_out));
+      T_out = (e_out - mo->eos_b * ye43(ye_out) * S.r3) / (mo->eos_a * (1.0 + ye_out));
     } else if (status == NMC_STATUS_EOS_DOMAIN) {
-      T_out = fixedT ? S.T_fix : (e_st - md->eos_b * ye43(ye_st) * S.r3) / (md->eos_a * (1.0 + ye_st));
+      T_out = fixedT ? S.T_fix : (e_st - mo->eos_b * ye43(ye_st) * S.r3) / (mo->eos_a * (1.0 + ye_st));
     }
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
-      const int64_t o = base + md->ext[t] * NQ + lane;
-      a.D[o] = D[t];
-      a.I[o] = I[t];
+      const int64_t o = base + mo->ext[t] * NQ + lane;
+      in_global(ao->D)[o] = D[t];
+      in_global(ao->I)[o] = I[t];
     }
     if (lane == 0) {
-      a.ye[p] = ye_out;
-      a.e[p] = e_out;
-      a.T[p] = T_out;
-      a.n_outer[p] = k;
-      a.n_inner[p] = total_inner;
-      a.status[p] = status;
+      in_global(ao->ye)[p] = ye_out;
+      in_global(ao->e)[p] = e_out;
+      in_global(ao->T)[p] = T_out;
+      in_global(ao->n_outer)[p] = k;
+      in_global(ao->n_inner)[p] = total_inner;
+      in_global(ao->status)[p] = status;
     }
     __syncthreads();
   }
 };
 
 template <int NS, bool COUPLED, bool PRE, bool QUEUE>
-__global__ __launch_bounds__(kLanes) void fwd64_kernel(FwdArgs a) {
+__global__ __launch_bounds__(kLanes, 2) void fwd64_kernel(FwdArgs a) {
   __shared__ Lds64<NS> S;
   load_model(a.mdl, a.theta, S.m);
   if constexpr (QUEUE) {
@@ -543,12 +612,12 @@ __global__ __launch_bounds__(kLanes) void fwd64_kernel(FwdArgs a) {
     for (int64_t g; (g = wq.next()) >= 0;) {
       const int64_t b0 = uniform64(g * a.chunk);
       const int64_t end = uniform64(b0 + a.chunk < a.P ? b0 + a.chunk : a.P);
-      for (int64_t p = b0; p < end; ++p) PointSolver64<NS, COUPLED, PRE>::solve(a, p, S, [&] { wq.settle(); });
+      for (int64_t p = b0; p < end; ++p) PointSolver64<NS, COUPLED, PRE>::solve(p, S, [&] { wq.settle(); });
     }
   } else {
     const int64_t b0 = (int64_t)blockIdx.x * a.chunk;
     const int64_t end = b0 + a.chunk < a.P ? b0 + a.chunk : a.P;
-    for (int64_t p = b0; p < end; ++p) PointSolver64<NS, COUPLED, PRE>::solve(a, p, S, [] {});
+    for (int64_t p = b0; p < end; ++p) PointSolver64<NS, COUPLED, PRE>::solve(p, S, [] {});
   }
 }
 

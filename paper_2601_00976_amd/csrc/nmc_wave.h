@@ -396,6 +396,72 @@ struct Fmac4<3> {
   }
 };
 
+// Four columns of one contraction for every species:
+// acc[t] += bcast(x[t], L0 + jj) * m[jj], jj = 0..3 (s_nop as above).
+template <int NS>
+struct Fmac1x4;
+
+template <>
+struct Fmac1x4<1> {
+  template <int L0>
+  __device__ __forceinline__ static void run(double (&a)[1], const double (&x)[1], double m0, double m1, double m2,
+                                             double m3) {
+    asm volatile(
+        "s_nop 1\n"
+        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n"
+        : "+v"(a[0])
+        : "v"(x[0]), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
+  }
+};
+
+template <>
+struct Fmac1x4<2> {
+  template <int L0>
+  __device__ __forceinline__ static void run(double (&a)[2], const double (&x)[2], double m0, double m1, double m2,
+                                             double m3) {
+    asm volatile(
+        "s_nop 1\n"
+        "v_fmac_f64_dpp %0, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %3, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %3, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %3, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %2, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %3, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+        : "+v"(a[0]), "+v"(a[1])
+        : "v"(x[0]), "v"(x[1]), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
+  }
+};
+
+template <>
+struct Fmac1x4<3> {
+  template <int L0>
+  __device__ __forceinline__ static void run(double (&a)[3], const double (&x)[3], double m0, double m1, double m2,
+                                             double m3) {
+    asm volatile(
+        "s_nop 1\n"
+        "v_fmac_f64_dpp %0, %3, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %4, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %2, %5, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %3, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %2, %5, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %3, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %2, %5, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %0, %3, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %1, %4, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n"
+        "v_fmac_f64_dpp %2, %5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n"
+        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2])
+        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "i"(L0), "i"(L0 + 1), "i"(L0 + 2),
+          "i"(L0 + 3));
+  }
+};
+
 // 1 / x from the hardware estimate refined by two Newton steps, for finite x
 // of normal magnitude (|x| and 1 / |x| both above the denormal range)
 __device__ __forceinline__ double rcp_nr(double x) {
