@@ -1,0 +1,486 @@
+// Forward kernel of the implicit coupling solve for 32 energy nodes and small
+// batches: one work-group per pair of points, one wavefront per species
+// (CDNA4).
+//
+// A batch that does not fill the chip takes as long as its slowest point, and
+// in the two-points-per-wavefront kernel an inner iteration is ~890
+// instructions of one wave: 384 multiply-adds of the rates, the Anderson step
+// and the convergence sums of all species one after the other.  Here wave t of
+// the work-group holds species t of both points (lane 32 h + q: node q of the
+// point of half h) and does that species' share of all of it, ~370
+// instructions; the waves of a work-group run on different SIMDs.  What
+// depends on every species goes through LDS: the number moments of the pair
+// partner (contracted into this species' rates), the Gram sums of the
+// Anderson step and the convergence flags in every inner iteration (two
+// barriers), the sums of the matter right-hand side in every outer one.
+// Everything that follows from them (EOS, Anderson coefficients, matter
+// iterate, convergence) is computed by every wave from the same values with
+// the same instructions, so the waves take every branch together.
+//
+// Same algorithm, core and orientation forms, status rules and skip rule as
+// the two-point kernel.  The sums over species add per-species sums here, so
+// the two kernels agree to rounding, not bit for bit.
+#include "nmc_fdproj.h"
+#include "nmc_pair.h"
+
+namespace nmc {
+namespace {
+
+using namespace pairk;
+
+template <int NS>
+struct SplitLds {
+  ModelLds m;
+  SplitExp E[2];             // per point: exponent splits (points that fill the tile)
+  double tile[2][NQP][NQP];  // per point: pair factors (see the two-point kernel)
+  double D[NS][kLanes];      // next number moments of every species
+  double odds[NS][kLanes];   // projected equilibrium: o = D / (1 - D)
+  alignas(16) double gram[NS][2][4];  // per species and point: Gram sums of the Anderson step
+  alignas(16) double mat[NS][2][2];   // sums of the matter right-hand side
+  int flag[NS][2];           // 1: converged, 2: a non-finite iterate
+};
+
+template <int NS, bool PROJ>
+struct SplitSolver {
+  static constexpr int NQ = NQP;
+
+  // sum over the species of what their waves left in LDS for this point
+  template <int N>
+  __device__ __forceinline__ static void species_sum(const double (&v)[NS][2][N], int h, double (&s)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) s[i] = v[0][h][i];
+#pragma unroll
+    for (int t = 1; t < NS; ++t)
+#pragma unroll
+      for (int i = 0; i < N; ++i) s[i] += v[t][h][i];
+  }
+
+  __device__ static void solve(int64_t u, SplitLds<NS>& S) {
+    const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
+    const_ptr<DevModel> md = scalar_ptr(a->mdl);
+    const ModelLds& mt = S.m;
+    const int sp = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // this wave's species (internal order)
+    const int pa = NS == 3 ? (sp < 2 ? 1 - sp : 2) : 1 - sp;          // its pair partner
+    const int lane = threadIdx.x & 63;
+    const int h = lane >> 5, q0 = lane & 31;
+    const double dtau = a->dtau;
+    // point of this half; past the end of an odd batch the half mirrors its
+    // neighbour and stores nothing
+    const int64_t p_raw = 2 * u + h;
+    const bool has_point = p_raw < a->P;
+    const int64_t p = has_point ? p_raw : p_raw - 1;
+    const int64_t o = p * (int64_t)(NS * NQ) + md->ext[sp] * NQ + q0;
+    const double rho = in_global(a->rho11)[p];
+    const bool fixedT = a->prm.fixed_matter && a->T_fixed;
+    const bool fixed_mu = a->prm.fixed_matter && a->mu_fixed;
+    const double Dst = in_global(a->D0)[o], Ist = in_global(a->I0)[o];
+    const double ye_st = in_global(a->ye0)[p], e_st = in_global(a->e0)[p];
+    const double chi0 = a->chi0 ? in_global(a->chi0)[p] : md->chi_ref * rho;
+    const double T_fix = fixedT ? in_global(a->T_fixed)[p] : 0.0;
+    const double mu_fix = fixed_mu ? in_global(a->mu_fixed)[p] : 0.0;
+    double D = Dst, I = Ist;
+    S.D[sp][lane] = D;
+
+    // coupling disabled at low density (Sec. 7.2): the state passes through
+    const bool skip = rho < md->rho11_min;
+    const double r3 = cbrt(rho), K = md->kcoup / rho;
+    const double An = (md->flags & NMC_NES) ? mt.theta[NQ] * rho : 0.0;
+    const double Ap = (md->flags & NMC_PAIR) ? mt.theta[NQ + 1] * rho : 0.0;
+    const double gsp = md->ig[sp], dsp = md->imult[sp];
+    double y0 = ye_st, y1 = e_st;
+    double oq0 = 0.0, oq1 = 0.0, of0 = 0.0, of1 = 0.0, odq0 = 0.0, odq1 = 0.0, odf0 = 0.0, odf1 = 0.0;
+    // ||D^[k,1]||_W^2 of this species
+    double dref;
+    {
+      const double v[2] = {mt.w2[q0] * D * D, 0.0};
+      double s[2];
+      half_own_sums<1>(v, s);
+      dref = s[0];
+    }
+    __syncthreads();
+    double Dp = S.D[pa][lane];  // number moment of the partner
+    __syncthreads();
+
+    int status = NMC_STATUS_OK;
+    bool fatal = false, inner_failed = false, outer_conv = false;
+    bool run = !skip;  // this half's point is still iterating the outer loop
+    int k_done = 0, total_inner = 0;
+    double T_last = 0.0;  // temperature of the last outer iteration this half ran
+
+    for (int k = 1; k <= a->prm.max_outer && __builtin_amdgcn_ballot_w64(run) != 0; ++k) {
+      const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
+      const_ptr<DevModel> md = scalar_ptr(a->mdl);
+      const int q = opaque(q0);
+      if (run) k_done = k;
+      // ---- ComputeOpacities(y^[k]) --------------------------------------
+      const double T = fixedT ? T_fix : (y1 - md->eos_b * ye43(y0) * r3) * rcp_nr(md->eos_a * (1.0 + y0));
+      const double mu =
+          fixed_mu ? mu_fix : md->mu_a * (y0 - md->mu_ye0) * r3 + md->mu_b * log_pos(T * md->inv_mu_t0);
+      if (run && (!(T > 0.0) || !(y0 >= 0.0) || !isfinite(T) || !isfinite(mu))) {
+        status = NMC_STATUS_EOS_DOMAIN;
+        fatal = true;
+        run = false;
+      }
+      T_last = run ? T : T_last;
+      // a finished half keeps a harmless temperature
+      const double Tu = run ? T : 1.0, muu = run ? mu : 0.0;
+      const double invT = rcp_nr(Tu);
+      const double epsq = mt.eps[q];
+      const ExpSplit xs = exp_split(epsq, invT);
+      const double shape = chi0 * mt.shape[q];
+      const double dsig = dtau * ((md->flags & NMC_ISO) ? md->sigma_ratio * shape : 0.0);
+      const double chia = md->iemab[sp] * ((md->flags & NMC_EMAB) ? mt.theta[q] * shape : 0.0);
+      // equilibrium, and the detailed-balance factors of this species and
+      // (h only) its partner
+      double deq, go = 1.0, rgo = 1.0, ho = 1.0, hp = 1.0;
+      if constexpr (PROJ) {
+        double pD, pC;
+        fdp::projected_node(a->mdl, q, Tu, md->imusign[sp] * muu, pD, pC);
+        deq = pD;
+        ho = pD / pC;
+        rgo = 1.0 / sqrt(ho);
+        go = ho * rgo;
+        S.odds[sp][lane] = ho;
+      } else {
+        const double x = (epsq - md->imusign[sp] * muu) * invT;
+        const double ex = exp(-fabs(x));
+        const double r = rcp_nr(1.0 + ex);
+        deq = x > 0.0 ? ex * r : r;
+      }
+      const double baseD = Dst + dtau * (chia * deq);
+      const double den0D = 1.0 + dtau * chia;
+
+      // row of pair factors: the forms and their ranges as in the two-point
+      // kernel (every wave of the work-group forms the same row)
+      double B[NQ];
+      const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
+      const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
+      const int lo1 = __builtin_amdgcn_readlane(xs.n, 32), hi1 = __builtin_amdgcn_readlane(xs.n, 63);
+      const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
+      const int c = (nlo + nhi) >> 1;
+      const bool direct = __builtin_amdgcn_ballot_w64(run && nhi - nlo > kDirectBits) == 0;
+      const bool sym = PROJ || __builtin_amdgcn_ballot_w64(run && nhi - nlo > kSymBits) == 0;
+      if (direct) {
+        const double gt = ldexp(xs.R, c - xs.n), rgt = ldexp(xs.P, xs.n - c);
+        if constexpr (!PROJ) {
+          go = gt;
+          rgo = rgt;
+        }
+        direct_row_regs(gt * gt, rgt * rgt, B);
+        if constexpr (PROJ) __syncthreads();
+      } else {
+        if constexpr (!PROJ) {
+          go = sym ? ldexp(xs.R, c - xs.n) : 1.0;
+          rgo = sym ? ldexp(xs.P, xs.n - c) : 1.0;
+        }
+        if (sp == 0) {
+          SplitExp& E = S.E[h];
+          E.P2[q] = xs.P;
+          E.R2[q] = xs.R;
+          E.n2[q] = xs.n;
+        }
+        __syncthreads();
+        double (*Tl)[NQ] = S.tile[h];
+        if (sp == 0) {
+          const SplitExp& E = S.E[h];
+          if (sym) {
+            pair_tile_rows<true>(&Tl[0][0], E.P2, E.R2, E.n2, q, xs.P, xs.R, xs.n);
+            Tl[q][q] = 1.0;
+          } else {
+            pair_tile_rows<false>(&Tl[0][0], E.P2, E.R2, E.n2, q, xs.P, xs.R, xs.n);
+            Tl[q][q] = -1.0;
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) B[j] = Tl[j][q];
+      }
+      if constexpr (PROJ) hp = S.odds[pa][lane];
+      else ho = hp = hq;
+
+      // ---- inner loop over moments at fixed matter ------------------------
+      const double w2q = mt.w2[q], w2eq = w2q * epsq;
+      const double Aeq = An * epsq, Apq = Ap * epsq;
+      const double ag = Aeq * go, arg = Aeq * rgo, aph = Apq * ho;
+      double G11 = 0.0;
+      double Qp[2] = {0.0, 0.0}, Fp[2] = {0.0, 0.0}, dQo[2] = {0.0, 0.0}, dFo[2] = {0.0, 0.0};  // Anderson history
+      const double dref0 = dref;
+      const bool ran = run;  // this half runs this outer iteration
+      bool act = run;        // this half is still iterating the inner loop
+      bool cvd = false;      // this half's inner loop converged
+      int l_done = 0;
+      const int m_inner = held(a->prm.m_inner), max_inner = held(a->prm.max_inner);
+      const double tol2 = held(a->tol_inner2);
+      for (int l = 1; l <= max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
+        if (act) l_done = l;
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+        const double xv = w2eq * D, yv = w2eq - xv;
+        const double xp = w2eq * Dp, yp = w2eq - xp;
+        double eN[1] = {0.0}, oN[1] = {0.0}, aP[1] = {0.0}, eP[1] = {0.0};
+        if (sym) {
+          double AR[2][1], BR[2][1], CR[2][1], DR[2][1];
+          swap16(xv * rgo, AR[0][0], AR[1][0]);
+          swap16(yv * go, BR[0][0], BR[1][0]);
+          swap16(xp, CR[0][0], CR[1][0]);
+          swap16(hp * yp, DR[0][0], DR[1][0]);
+          static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
+            constexpr int j = 4 * decltype(jj)::value;
+            ColSym<1>::template run<j % 16>(eN, oN, aP, eP, AR[j / 16], BR[j / 16], CR[j / 16], DR[j / 16], B[j],
+                                            B[j + 1], B[j + 2], B[j + 3]);
+          });
+        } else {
+          double XR[2][1], YR[2][1], CR[2][1], DR[2][1];
+          swap16(xv, XR[0][0], XR[1][0]);
+          swap16(yv, YR[0][0], YR[1][0]);
+          swap16(xp, CR[0][0], CR[1][0]);
+          swap16(hp * yp, DR[0][0], DR[1][0]);
+          static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
+            constexpr int j = 4 * decltype(jj)::value;
+            double fi[4], fo[4], fa[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double sb = B[j + i], b2 = sb * sb, c3 = sb * b2;
+              fi[i] = max_neg_f64(sb, c3);
+              fo[i] = max_neg_f64(c3, sb);
+              fa[i] = b2;
+            }
+            Fmac1x4<1>::template run<j % 16>(eN, XR[j / 16], fi[0], fi[1], fi[2], fi[3]);
+            Fmac1x4<1>::template run<j % 16>(oN, YR[j / 16], fo[0], fo[1], fo[2], fo[3]);
+            Fmac1x4<1>::template run<j % 16>(aP, CR[j / 16], fa[0], fa[1], fa[2], fa[3]);
+            Fmac1x4<1>::template run<j % 16>(eP, DR[j / 16], fa[0], fa[1], fa[2], fa[3]);
+          });
+        }
+        // Q and residual of both owned moments; one reciprocal of the product
+        // of the two denominators serves both
+        double Q[2], F[2], Xn[2];
+        {
+          const double eta = __builtin_fma(ag, eN[0], aph * eP[0]);
+          const double chi = __builtin_fma(arg, oN[0], __builtin_fma(Apq, aP[0], eta));
+          const double dD = __builtin_fma(dtau, chi, den0D), dI = dD + dsig;
+          const double r = rcp_nr(dD * dI);
+          Q[0] = __builtin_fma(dtau, eta, baseD) * (r * dI);
+          Q[1] = Ist * (r * dD);
+          F[0] = Q[0] - D;
+          F[1] = Q[1] - I;
+        }
+        // Anderson step over min(l, M_inner) residuals (difference form)
+        const int mem = l < m_inner ? l : m_inner;
+        if (mem == 1) {
+          Xn[0] = Q[0];
+          Xn[1] = Q[1];
+          dQo[0] = dQo[1] = dFo[0] = dFo[1] = 0.0;
+          __syncthreads();  // the flags and moments of the last iterate have been read
+        } else {
+          double dQ2[2], dF2[2], v4[4] = {0.0, 0.0, 0.0, 0.0}, own[4], gs[4];
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            dQ2[x] = Q[x] - Qp[x];
+            dF2[x] = F[x] - Fp[x];
+            v4[0] += dFo[x] * dF2[x];
+            v4[1] += dF2[x] * dF2[x];
+            v4[2] += dFo[x] * F[x];
+            v4[3] += dF2[x] * F[x];
+          }
+          half_sums4(v4, own);
+          if (q0 == 0) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) S.gram[sp][h][i] = own[i];
+          }
+          __syncthreads();
+          species_sum<4>(S.gram, h, gs);
+          double g1, g2;
+          anderson2(mem == 3, G11, gs[0], gs[1], gs[2], gs[3], g1, g2);
+#pragma unroll
+          for (int x = 0; x < 2; ++x) {
+            Xn[x] = Q[x] - g2 * dQ2[x] - g1 * dQo[x];
+            dQo[x] = dQ2[x];
+            dFo[x] = dF2[x];
+          }
+          G11 = gs[1];
+        }
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          Qp[x] = Q[x];
+          Fp[x] = F[x];
+        }
+        // Algorithm innerConverged for this species (reference guarded by the
+        // new norm, compared squared), and whether an iterate is non-finite
+        const uint64_t odd = __builtin_amdgcn_ballot_w64(!isfinite(Xn[0]) || !isfinite(Xn[1]));
+        const bool bad = (h ? odd >> 32 : odd & 0xffffffffull) != 0;
+        const double dd = Xn[0] - D, di = Xn[1] - I;
+        const double vc[4] = {w2q * dd * dd, w2q * di * di, w2q * Xn[0] * Xn[0], 0.0};
+        double sc[4];
+        half_sums4(vc, sc);
+        const double dn2 = sc[2], lim = tol2 * (dref0 > dn2 ? dref0 : dn2);
+        const bool conv1 = sc[0] <= lim && sc[1] <= lim;
+        if (q0 == 0) S.flag[sp][h] = (conv1 ? 1 : 0) | (bad ? 2 : 0);
+        S.D[sp][lane] = Xn[0];
+        __syncthreads();
+        int all = 1, any = 0;
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+          all &= S.flag[t][h];
+          any |= S.flag[t][h];
+        }
+        const double Dpn = S.D[pa][lane];
+        if ((any & 2) && act) {
+          status = NMC_STATUS_NONFINITE;
+          fatal = true;
+          act = run = false;
+        }
+        if (act) {
+          D = Xn[0];
+          I = Xn[1];
+          Dp = Dpn;
+          if (all & 1) {
+            // ||D^[k,*]|| is the reference of the next inner loop
+            dref = dn2;
+            cvd = true;
+            act = false;
+          }
+        }
+      }
+      if (ran) total_inner += l_done;
+      if (run && !cvd) inner_failed = true;
+      // matter right-hand side (Eq. implicitFluidNodal at v = 0), and the norm
+      // of the current moments where a running point's inner loop failed
+      double yq0, yq1;
+      {
+        const double dd = D - Dst;
+        const double v[4] = {gsp * w2q * dd, dsp * mt.w3[q] * dd, w2q * D * D, 0.0};
+        double s[4], m[2];
+        half_sums4(v, s);
+        dref = (run && !cvd) ? s[2] : dref;
+        __syncthreads();  // the sums of the last outer iteration have been read
+        if (q0 == 0) {
+          S.mat[sp][h][0] = s[0];
+          S.mat[sp][h][1] = s[1];
+        }
+        __syncthreads();
+        species_sum<2>(S.mat, h, m);
+        yq0 = ye_st - K * m[0];
+        yq1 = e_st - K * m[1];
+      }
+      if (a->prm.fixed_matter) {
+        if (run) outer_conv = true;
+        run = false;
+      }
+      if (run) {
+        const double f0 = yq0 - y0, f1 = yq1 - y1;
+        const int omem = k < a->prm.m_outer ? k : a->prm.m_outer;
+        double yn0, yn1;
+        if (omem == 1) {
+          yn0 = yq0;
+          yn1 = yq1;
+        } else {
+          const double dq20 = yq0 - oq0, dq21 = yq1 - oq1;
+          const double df20 = f0 - of0, df21 = f1 - of1;
+          const double G22 = df20 * df20 + df21 * df21, b2 = df20 * f0 + df21 * f1;
+          const double G11o = odf0 * odf0 + odf1 * odf1;
+          const double G12 = odf0 * df20 + odf1 * df21, b1 = odf0 * f0 + odf1 * f1;
+          double g1, g2;
+          anderson2(omem == 3, G11o, G12, G22, b1, b2, g1, g2);
+          yn0 = yq0 - g2 * dq20 - g1 * odq0;
+          yn1 = yq1 - g2 * dq21 - g1 * odq1;
+          odq0 = dq20;
+          odq1 = dq21;
+          odf0 = df20;
+          odf1 = df21;
+        }
+        oq0 = yq0;
+        oq1 = yq1;
+        of0 = f0;
+        of1 = f1;
+        if (!isfinite(yn0) || !isfinite(yn1)) {
+          status = NMC_STATUS_NONFINITE;
+          fatal = true;
+          run = false;
+        } else {
+          // Algorithm outerConverged: componentwise against y*
+          const bool oc =
+              fabs(yn0 - y0) <= a->prm.tol_outer * fabs(ye_st) && fabs(yn1 - y1) <= a->prm.tol_outer * fabs(e_st);
+          y0 = yn0;
+          y1 = yn1;
+          if (oc) {
+            outer_conv = true;
+            run = false;
+          }
+        }
+      }
+    }
+    if (!skip && !fatal) {
+      if (!outer_conv) status = NMC_STATUS_MAX_OUTER;
+      else if (inner_failed) status = NMC_STATUS_MAX_INNER;
+    }
+
+    // ---- outputs --------------------------------------------------------
+    const_ptr<FwdArgs> ao = kernel_args<FwdArgs>();
+    const_ptr<DevModel> mo = scalar_ptr(ao->mdl);
+    double ye_out = ye_st, e_out = e_st, T_out = T_last;
+    {
+      // the matter right-hand side at the final moments
+      const double dd = D - Dst;
+      const double v[2] = {gsp * mt.w2[q0] * dd, dsp * mt.w3[q0] * dd};
+      double s[2], m[2];
+      half_own_sums<1>(v, s);
+      __syncthreads();  // the loop's last sums have been read
+      if (q0 == 0) {
+        S.mat[sp][h][0] = s[0];
+        S.mat[sp][h][1] = s[1];
+      }
+      __syncthreads();
+      species_sum<2>(S.mat, h, m);
+      if (!skip && !ao->prm.fixed_matter) {
+        ye_out = ye_st - K * m[0];
+        e_out = e_st - K * m[1];
+      }
+      if (skip || !ao->prm.fixed_matter || status == NMC_STATUS_EOS_DOMAIN)
+        T_out = fixedT ? T_fix : (e_out - mo->eos_b * ye43(ye_out) * r3) / (mo->eos_a * (1.0 + ye_out));
+    }
+    if (has_point) {
+      in_global(ao->D)[o] = D;
+      in_global(ao->I)[o] = I;
+      if (threadIdx.x == (h << 5)) {  // wave 0, first lane of the half
+        in_global(ao->ye)[p] = ye_out;
+        in_global(ao->e)[p] = e_out;
+        in_global(ao->T)[p] = T_out;
+        in_global(ao->n_outer)[p] = skip ? 0 : k_done;
+        in_global(ao->n_inner)[p] = total_inner;
+        in_global(ao->status)[p] = status;
+      }
+    }
+    __syncthreads();  // LDS is free for the next pair
+  }
+};
+
+template <int NS, bool PROJ>
+__global__ __launch_bounds__(kLanes* NS, 2) void fwd_split_kernel(FwdArgs a) {
+  __shared__ SplitLds<NS> S;
+  load_model(a.mdl, a.theta, S.m);
+  const int64_t pairs = (a.P + 1) / 2;
+  for (int64_t u = blockIdx.x; u < pairs; u += gridDim.x) SplitSolver<NS, PROJ>::solve(u, S);
+}
+
+template <int NS, bool PROJ>
+hipError_t launch_split_t(const FwdArgs& a, const nmc_launch& L, int num_cu, hipStream_t s) {
+  const int64_t pairs = (a.P + 1) / 2;
+  // one work-group per pair, or as many as the caller wants resident or per
+  // chunk, each taking every gridDim.x-th pair
+  int64_t grid = pairs;
+  if (L.persistent && L.blocks_per_cu > 0) grid = (int64_t)L.blocks_per_cu * num_cu;
+  if (!L.persistent) grid = (pairs + L.chunk - 1) / L.chunk;
+  if (grid > pairs) grid = pairs;
+  hipLaunchKernelGGL((fwd_split_kernel<NS, PROJ>), dim3((unsigned)grid), dim3(kLanes * NS), 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_forward_split(const FwdArgs& a, int ns, bool proj, const nmc_launch& L, int num_cu, hipStream_t s) {
+  if (ns == 2) return proj ? launch_split_t<2, true>(a, L, num_cu, s) : launch_split_t<2, false>(a, L, num_cu, s);
+  if (ns == 3) return proj ? launch_split_t<3, true>(a, L, num_cu, s) : launch_split_t<3, false>(a, L, num_cu, s);
+  return hipErrorInvalidValue;
+}
+
+}  // namespace nmc

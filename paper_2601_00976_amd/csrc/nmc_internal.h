@@ -156,6 +156,18 @@ inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, in
   return p;
 }
 
+// Whether a batch is small enough for one wavefront per species of a pair of
+// points instead of one per pair: up to 12 such wavefronts per compute unit,
+// half as many again as are resident.  There the slowest points set the time
+// and their share of work per wavefront is what counts; beyond, the species'
+// common work (equation of state, rows) done once per wavefront costs more.
+// Three species, split against pairs: static solve of 8 points 50 against
+// 64 us, 2048 points 67 against 86 us, 4095 points 104 against 92 us.  A rule
+// of the batch alone: results do not depend on the launch shape.
+inline bool split_by_species(int64_t P, int ns, int num_cu) {
+  return ns > 1 && (P + 1) / 2 * ns <= (int64_t)12 * num_cu;
+}
+
 // launchers (defined in the kernel translation units)
 hipError_t launch_forward(const FwdArgs& a, int nq, int ns, bool coupled, bool proj, const nmc_launch& L,
                           int num_cu, hipStream_t s);
@@ -163,6 +175,7 @@ hipError_t launch_forward64(const FwdArgs& a, int ns, bool coupled, const nmc_la
                             hipStream_t s);
 hipError_t launch_forward_pair(const FwdArgs& a, int ns, bool coupled, bool proj, const nmc_launch& L,
                                int num_cu, hipStream_t s);
+hipError_t launch_forward_split(const FwdArgs& a, int ns, bool proj, const nmc_launch& L, int num_cu, hipStream_t s);
 hipError_t launch_forward_v(const FwdVArgs& a, int ns, bool coupled, bool phi1, const nmc_launch& L, int num_cu,
                             hipStream_t s);
 hipError_t launch_forward_vpair(const FwdVArgs& a, int ns, bool coupled, bool phi1, const nmc_launch& L, int num_cu,
