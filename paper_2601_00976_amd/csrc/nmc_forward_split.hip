@@ -17,22 +17,22 @@
 // iterate, convergence) is computed by every wave from the same values with
 // the same instructions, so the waves take every branch together.
 //
-// Same algorithm, core and orientation forms, status rules and skip rule as
-// the two-point kernel.  The sums over species add per-species sums here, so
-// the two kernels agree to rounding, not bit for bit.
+// Same algorithm, status rules and skip rule as the two-point kernel.  The
+// sums over species add per-species sums here, so the two kernels agree to
+// rounding, not bit for bit.
 #include "nmc_fdproj.h"
-#include "nmc_pair.h"
+#include "nmc_split.h"
 
 namespace nmc {
 namespace {
 
 using namespace pairk;
+using namespace splitk;
 
 template <int NS>
 struct SplitLds {
   ModelLds m;
-  SplitExp E[2];             // per point: exponent splits (points that fill the tile)
-  double tile[2][NQP][NQP];  // per point: pair factors (see the two-point kernel)
+  ColdLds<NS> cold;
   double D[NS][kLanes];      // next number moments of every species
   double odds[NS][kLanes];   // projected equilibrium: o = D / (1 - D)
   alignas(16) double gram[NS][2][4];  // per species and point: Gram sums of the Anderson step
@@ -43,17 +43,6 @@ struct SplitLds {
 template <int NS, bool PROJ>
 struct SplitSolver {
   static constexpr int NQ = NQP;
-
-  // sum over the species of what their waves left in LDS for this point
-  template <int N>
-  __device__ __forceinline__ static void species_sum(const double (&v)[NS][2][N], int h, double (&s)[N]) {
-#pragma unroll
-    for (int i = 0; i < N; ++i) s[i] = v[0][h][i];
-#pragma unroll
-    for (int t = 1; t < NS; ++t)
-#pragma unroll
-      for (int i = 0; i < N; ++i) s[i] += v[t][h][i];
-  }
 
   __device__ static void solve(int64_t u, SplitLds<NS>& S) {
     const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
@@ -150,8 +139,9 @@ struct SplitSolver {
       const double baseD = Dst + dtau * (chia * deq);
       const double den0D = 1.0 + dtau * chia;
 
-      // row of pair factors: the forms and their ranges as in the two-point
-      // kernel (every wave of the work-group forms the same row)
+      // row of the symmetric core with the nodes' factors g and 1 / g scaled
+      // by 2^+-c (every wave of the work-group forms the same row), where the
+      // grid spans at most kDirectBits powers of two; else the splits in LDS
       double B[NQ];
       const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
       const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
@@ -159,44 +149,19 @@ struct SplitSolver {
       const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
       const int c = (nlo + nhi) >> 1;
       const bool direct = __builtin_amdgcn_ballot_w64(run && nhi - nlo > kDirectBits) == 0;
-      const bool sym = PROJ || __builtin_amdgcn_ballot_w64(run && nhi - nlo > kSymBits) == 0;
       if (direct) {
         const double gt = ldexp(xs.R, c - xs.n), rgt = ldexp(xs.P, xs.n - c);
         if constexpr (!PROJ) {
           go = gt;
           rgo = rgt;
+          ho = hp = hq;
         }
         direct_row_regs(gt * gt, rgt * rgt, B);
         if constexpr (PROJ) __syncthreads();
       } else {
-        if constexpr (!PROJ) {
-          go = sym ? ldexp(xs.R, c - xs.n) : 1.0;
-          rgo = sym ? ldexp(xs.P, xs.n - c) : 1.0;
-        }
-        if (sp == 0) {
-          SplitExp& E = S.E[h];
-          E.P2[q] = xs.P;
-          E.R2[q] = xs.R;
-          E.n2[q] = xs.n;
-        }
-        __syncthreads();
-        double (*Tl)[NQ] = S.tile[h];
-        if (sp == 0) {
-          const SplitExp& E = S.E[h];
-          if (sym) {
-            pair_tile_rows<true>(&Tl[0][0], E.P2, E.R2, E.n2, q, xs.P, xs.R, xs.n);
-            Tl[q][q] = 1.0;
-          } else {
-            pair_tile_rows<false>(&Tl[0][0], E.P2, E.R2, E.n2, q, xs.P, xs.R, xs.n);
-            Tl[q][q] = -1.0;
-          }
-        }
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < NQ; ++j) B[j] = Tl[j][q];
+        cold_splits(S.cold, h, q, xs);
       }
       if constexpr (PROJ) hp = S.odds[pa][lane];
-      else ho = hp = hq;
 
       // ---- inner loop over moments at fixed matter ------------------------
       const double w2q = mt.w2[q], w2eq = w2q * epsq;
@@ -216,47 +181,19 @@ struct SplitSolver {
 #pragma unroll
         for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
         const double xv = w2eq * D, yv = w2eq - xv;
-        const double xp = w2eq * Dp, yp = w2eq - xp;
-        double eN[1] = {0.0}, oN[1] = {0.0}, aP[1] = {0.0}, eP[1] = {0.0};
-        if (sym) {
-          double AR[2][1], BR[2][1], CR[2][1], DR[2][1];
-          swap16(xv * rgo, AR[0][0], AR[1][0]);
-          swap16(yv * go, BR[0][0], BR[1][0]);
-          swap16(xp, CR[0][0], CR[1][0]);
-          swap16(hp * yp, DR[0][0], DR[1][0]);
-          static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-            constexpr int j = 4 * decltype(jj)::value;
-            ColSym<1>::template run<j % 16>(eN, oN, aP, eP, AR[j / 16], BR[j / 16], CR[j / 16], DR[j / 16], B[j],
-                                            B[j + 1], B[j + 2], B[j + 3]);
-          });
+        double eN, oN, aP, eP;
+        if (direct) {
+          const double xp = w2eq * Dp, yp = w2eq - xp;
+          core_contract(B, xv * rgo, yv * go, xp, hp * yp, eN, oN, aP, eP);
         } else {
-          double XR[2][1], YR[2][1], CR[2][1], DR[2][1];
-          swap16(xv, XR[0][0], XR[1][0]);
-          swap16(yv, YR[0][0], YR[1][0]);
-          swap16(xp, CR[0][0], CR[1][0]);
-          swap16(hp * yp, DR[0][0], DR[1][0]);
-          static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-            constexpr int j = 4 * decltype(jj)::value;
-            double fi[4], fo[4], fa[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              const double sb = B[j + i], b2 = sb * sb, c3 = sb * b2;
-              fi[i] = max_neg_f64(sb, c3);
-              fo[i] = max_neg_f64(c3, sb);
-              fa[i] = b2;
-            }
-            Fmac1x4<1>::template run<j % 16>(eN, XR[j / 16], fi[0], fi[1], fi[2], fi[3]);
-            Fmac1x4<1>::template run<j % 16>(oN, YR[j / 16], fo[0], fo[1], fo[2], fo[3]);
-            Fmac1x4<1>::template run<j % 16>(aP, CR[j / 16], fa[0], fa[1], fa[2], fa[3]);
-            Fmac1x4<1>::template run<j % 16>(eP, DR[j / 16], fa[0], fa[1], fa[2], fa[3]);
-          });
+          cold_contract<NS, PROJ>(S.cold, sp, pa, h, q, xv * rgo, yv * go, xv, ho * yv, eN, oN, aP, eP);
         }
         // Q and residual of both owned moments; one reciprocal of the product
         // of the two denominators serves both
         double Q[2], F[2], Xn[2];
         {
-          const double eta = __builtin_fma(ag, eN[0], aph * eP[0]);
-          const double chi = __builtin_fma(arg, oN[0], __builtin_fma(Apq, aP[0], eta));
+          const double eta = __builtin_fma(ag, eN, aph * eP);
+          const double chi = __builtin_fma(arg, oN, __builtin_fma(Apq, aP, eta));
           const double dD = __builtin_fma(dtau, chi, den0D), dI = dD + dsig;
           const double r = rcp_nr(dD * dI);
           Q[0] = __builtin_fma(dtau, eta, baseD) * (r * dI);
@@ -288,7 +225,7 @@ struct SplitSolver {
             for (int i = 0; i < 4; ++i) S.gram[sp][h][i] = own[i];
           }
           __syncthreads();
-          species_sum<4>(S.gram, h, gs);
+          species_sum<NS, 4>(S.gram, h, gs);
           double g1, g2;
           anderson2(mem == 3, G11, gs[0], gs[1], gs[2], gs[3], g1, g2);
 #pragma unroll
@@ -358,7 +295,7 @@ struct SplitSolver {
           S.mat[sp][h][1] = s[1];
         }
         __syncthreads();
-        species_sum<2>(S.mat, h, m);
+        species_sum<NS, 2>(S.mat, h, m);
         yq0 = ye_st - K * m[0];
         yq1 = e_st - K * m[1];
       }
@@ -430,7 +367,7 @@ struct SplitSolver {
         S.mat[sp][h][1] = s[1];
       }
       __syncthreads();
-      species_sum<2>(S.mat, h, m);
+      species_sum<NS, 2>(S.mat, h, m);
       if (!skip && !ao->prm.fixed_matter) {
         ye_out = ye_st - K * m[0];
         e_out = e_st - K * m[1];
@@ -464,14 +401,8 @@ __global__ __launch_bounds__(kLanes* NS, 2) void fwd_split_kernel(FwdArgs a) {
 
 template <int NS, bool PROJ>
 hipError_t launch_split_t(const FwdArgs& a, const nmc_launch& L, int num_cu, hipStream_t s) {
-  const int64_t pairs = (a.P + 1) / 2;
-  // one work-group per pair, or as many as the caller wants resident or per
-  // chunk, each taking every gridDim.x-th pair
-  int64_t grid = pairs;
-  if (L.persistent && L.blocks_per_cu > 0) grid = (int64_t)L.blocks_per_cu * num_cu;
-  if (!L.persistent) grid = (pairs + L.chunk - 1) / L.chunk;
-  if (grid > pairs) grid = pairs;
-  hipLaunchKernelGGL((fwd_split_kernel<NS, PROJ>), dim3((unsigned)grid), dim3(kLanes * NS), 0, s, a);
+  hipLaunchKernelGGL((fwd_split_kernel<NS, PROJ>), dim3((unsigned)split_grid(L, a.P, num_cu)), dim3(kLanes * NS), 0, s,
+                     a);
   return hipGetLastError();
 }
 

@@ -161,11 +161,24 @@ inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, in
 // half as many again as are resident.  There the slowest points set the time
 // and their share of work per wavefront is what counts; beyond, the species'
 // common work (equation of state, rows) done once per wavefront costs more.
-// Three species, split against pairs: static solve of 8 points 50 against
-// 64 us, 2048 points 67 against 86 us, 4095 points 104 against 92 us.  A rule
-// of the batch alone: results do not depend on the launch shape.
+// Three species, split against pairs: static solve of 8 points 47 against
+// 64 us, 2048 points 60 against 86 us, 4095 points 94 against 92 us; O(v)
+// solve of 8 points 130 against 192 us, 2048 points 219 against 232 us, 2730
+// points 275 against 233 us (with linear-order kernels 204 against 383, 351
+// against 469 and 446 against 470 us).  A rule of the batch alone: results do
+// not depend on the launch shape.
 inline bool split_by_species(int64_t P, int ns, int num_cu) {
   return ns > 1 && (P + 1) / 2 * ns <= (int64_t)12 * num_cu;
+}
+
+// its grid: one work-group per pair, or as many as the caller wants resident
+// or per chunk, each taking every gridDim.x-th pair
+inline int64_t split_grid(const nmc_launch& L, int64_t P, int num_cu) {
+  const int64_t pairs = (P + 1) / 2;
+  int64_t grid = pairs;
+  if (L.persistent && L.blocks_per_cu > 0) grid = (int64_t)L.blocks_per_cu * num_cu;
+  if (!L.persistent) grid = (pairs + L.chunk - 1) / L.chunk;
+  return grid < pairs ? grid : pairs;
 }
 
 // launchers (defined in the kernel translation units)
@@ -176,6 +189,7 @@ hipError_t launch_forward64(const FwdArgs& a, int ns, bool coupled, const nmc_la
 hipError_t launch_forward_pair(const FwdArgs& a, int ns, bool coupled, bool proj, const nmc_launch& L,
                                int num_cu, hipStream_t s);
 hipError_t launch_forward_split(const FwdArgs& a, int ns, bool proj, const nmc_launch& L, int num_cu, hipStream_t s);
+hipError_t launch_forward_vsplit(const FwdVArgs& a, int ns, bool phi1, const nmc_launch& L, int num_cu, hipStream_t s);
 hipError_t launch_forward_v(const FwdVArgs& a, int ns, bool coupled, bool phi1, const nmc_launch& L, int num_cu,
                             hipStream_t s);
 hipError_t launch_forward_vpair(const FwdVArgs& a, int ns, bool coupled, bool phi1, const nmc_launch& L, int num_cu,

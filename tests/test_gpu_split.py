@@ -4,7 +4,9 @@ status, the same iteration counts up to the rounding of the sums over species,
 moments to 1e-11 of a species' norm (both stop at the same tolerance; rounding
 of 1e-16 per sum carried through the tens of iterations of a solve).  Odd
 batches, single points, cold and skipped points next to warm ones, every
-option of the solve, the last batch that is split and the first that is not."""
+option of the solve, the last batch that is split and the first that is not.
+The two-points-per-wavefront answer is that of the same points in a batch
+large enough for it."""
 import numpy as np
 import pytest
 
@@ -31,6 +33,12 @@ def _same(a, b, w2, names):
         assert float(((a[k] - b[k]).abs() / b[k].abs().clamp_min(1e-3))[ok].max()) <= 1e-10, k
 
 
+def _in_a_large_batch(run, t, P):
+    """run(t) of the points of t repeated to at least 4096 points, the first P of the results"""
+    big = {k: v.repeat((-(-4096 // P),) + (1,) * (v.dim() - 1)) for k, v in t.items()}
+    return {k: v[:P] for k, v in run(big).items()}
+
+
 @pytest.mark.parametrize("P", [1, 2, 3, 77, 2047, 2049])
 @pytest.mark.parametrize("sp,options", [(SP3, {}), (SP2, {}), (SP3, {"fd_projection": 1}),
                                         (SP3, {"flags": N.EMAB | N.NES}), ((N.NU_X, N.NU_E_BAR, N.NU_E), {})])
@@ -41,16 +49,19 @@ def test_split_static(P, sp, options):
     d = W.radial_profile(P=P if P > 3 else 9, ns=len(sp), seed=11).take(np.arange(P) if P > 3 else np.arange(2, 2 + P))
     t = S.to_device(d)
     D0, I0, e0 = S.init_state(m, t["T"], t["rho11"], t["ye"], t["uD"], t["uI"])
-    run = lambda prm, **kw: S.solve(m, prm, W.DTAU_KM, D0, I0, t["rho11"], t["ye"], e0, m.default_theta(), **kw)
+    t = dict(D0=D0, I0=I0, rho=t["rho11"], ye=t["ye"], e0=e0)
+    run = lambda t, prm, **kw: S.solve(m, prm, W.DTAU_KM, t["D0"], t["I0"], t["rho"], t["ye"], t["e0"],
+                                       m.default_theta(), **kw)
     for prm in (S.Params(), S.Params(m_inner=1, m_outer=2), S.Params(max_inner=3)):
-        a, b = run(prm), run(prm, launch=S.LaunchConfig(kernel_store=N.KERNELS_PAIRED))
+        a, b = run(t, prm), _in_a_large_batch(lambda x: run(x, prm), t, P)
         torch.cuda.synchronize()
         _same(a, b, m.grid.w2, ("ye", "e", "T"))
-    c = run(S.Params(), launch=S.LaunchConfig(blocks_per_cu=1))
-    a = run(S.Params())
-    torch.cuda.synchronize()
-    for k in a:
-        assert torch.equal(a[k], c[k]), k
+    a = run(t, S.Params())
+    for launch in (S.LaunchConfig(blocks_per_cu=1), S.LaunchConfig(kernel_store=N.KERNELS_PAIRED)):
+        c = run(t, S.Params(), launch=launch)
+        torch.cuda.synchronize()
+        for k in a:
+            assert torch.equal(a[k], c[k]), k
 
 
 def test_split_static_cold_and_fixed_matter():
@@ -62,13 +73,13 @@ def test_split_static_cold_and_fixed_matter():
     T = np.where(np.arange(P) % 3 == 0, np.linspace(0.06, 0.4, P), np.linspace(0.5, 2.0, P))
     t = S.to_device(W.Draws(**{**d.__dict__, "T": T}))
     D0, I0, e0 = S.init_state(m, t["T"], t["rho11"], t["ye"], t["uD"], t["uI"])
-    chi0 = 8.0 * t["rho11"]
-    mu = 5.0 * torch.ones_like(chi0)
+    t = dict(D0=D0, I0=I0, rho=t["rho11"], ye=t["ye"], e0=e0, chi0=8.0 * t["rho11"], T=t["T"],
+             mu=5.0 * torch.ones_like(t["rho11"]))
     for fixed in (False, True):
-        kw = dict(T_fixed=t["T"], mu_fixed=mu) if fixed else {}
-        run = lambda L: S.solve(m, S.Params(fixed_matter=fixed), W.DTAU_KM, D0, I0, t["rho11"], t["ye"], e0,
-                                m.default_theta(), chi0=chi0, launch=L, **kw)
-        a, b = run(None), run(S.LaunchConfig(kernel_store=N.KERNELS_PAIRED))
+        run = lambda x: S.solve(m, S.Params(fixed_matter=fixed), W.DTAU_KM, x["D0"], x["I0"], x["rho"], x["ye"], x["e0"],
+                                m.default_theta(), chi0=x["chi0"],
+                                **(dict(T_fixed=x["T"], mu_fixed=x["mu"]) if fixed else {}))
+        a, b = run(t), _in_a_large_batch(run, t, P)
         torch.cuda.synchronize()
         warm = torch.as_tensor(T >= 0.5, device="cuda")
         _same({k: v[warm] for k, v in a.items()}, {k: v[warm] for k, v in b.items()}, m.grid.w2, ("ye", "e", "T"))
