@@ -460,31 +460,38 @@ constexpr double kAdjSettled = 0x1p-48;
 // point of half h, for every species.
 //
 // The contractions run on the symmetric core B2 = exp(-|e_q - e_p| / T) as in
-// the forward kernel (columns broadcast by DPP, the factors g, 1 / g and h of
-// the nodes on the vectors and the row sums).  65536 points of the radial
-// profile: 324 us, against 1488 us by elimination alone, whose steps are a
-// chain of pivot broadcasts and reciprocals; here the multiply-adds' issue at
-// two waves per SIMD bounds it, a third of them the rates and their
+// the forward kernel (columns broadcast by DPP, the other 16-lane row's share
+// by one coefficient and one exchange, the factors g, 1 / g and h of the nodes
+// on the vectors and the row sums).  Elimination alone is a chain of pivot
+// broadcasts and reciprocals, 1488 us for 65536 points of the radial profile;
+// with iterations over whole rows of 32 columns 324 us.  The narrower rows take
+// forward solve and gradient together from 872 to 672 us.  The multiply-adds'
+// issue at two waves per SIMD bounds it, a third of them the rates and their
 // derivatives.
 template <int NS>
 struct PairAdjoint {
-  // acc[t] += sum_j bcast_j(x[t]) B[j], acc2[t] likewise with f(j) (the
-  // second matrix, formed per column): Fmac4 takes four columns of the lane's
-  // 16-lane row at a time
+  // s[t] = sum_j B2(q, j) x_j[t] and d[t] = sum_j B2(q, j) f(q, j) x_j[t],
+  // f(q, j) = fj(j) over this row's columns.  f is linear in e_q and e_j on
+  // either side of the diagonal, so over the other row's columns it is
+  // f(b, j) + f1 with b the node of that row next to this one
+  // (Fmac4 takes four columns at a time).
   template <class F>
-  __device__ __forceinline__ static void contract2(const double (&x)[NS], const double (&B)[NQ], double (&s)[NS],
-                                                   double (&d)[NS], F&& f) {
-    double R[2][NS];
+  __device__ __forceinline__ static void contract2(const double (&x)[NS], const double (&B)[16], double k, double f1,
+                                                   double (&s)[NS], double (&d)[NS], F&& fj) {
+#pragma unroll
+    for (int t = 0; t < NS; ++t) s[t] = d[t] = 0.0;
+    static_for<0, 4>([&](auto jj) __attribute__((always_inline)) {
+      constexpr int j = 4 * decltype(jj)::value;
+      Fmac4<NS>::template run<j>(s, d, x, B[j], B[j + 1], B[j + 2], B[j + 3], fj(j), fj(j + 1), fj(j + 2), fj(j + 3));
+    });
+    const bool upper = threadIdx.x & 16;
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
-      swap16(x[t], R[0][t], R[1][t]);
-      s[t] = d[t] = 0.0;
+      const double ms = mirror32(s[t]), md = mirror32(d[t]);
+      const double zs = upper ? row_bcast<0>(ms) : row_bcast<15>(ms), zd = upper ? row_bcast<0>(md) : row_bcast<15>(md);
+      s[t] = __builtin_fma(k, zs, s[t]);
+      d[t] = __builtin_fma(k, __builtin_fma(f1, zs, zd), d[t]);
     }
-    static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-      constexpr int j = 4 * decltype(jj)::value;
-      Fmac4<NS>::template run<j % 16>(s, d, R[j / 16], B[j], B[j + 1], B[j + 2], B[j + 3], f(j), f(j + 1), f(j + 2),
-                                      f(j + 3));
-    });
   }
 
   // live: the half's point has terms (solved forward, not skipped).  Returns
@@ -530,34 +537,38 @@ struct PairAdjoint {
     bool act = warm && nhi - nlo <= pairk::kDirectBits;
     const double gq = ldexp(xs.R, c - xs.n), rgq = ldexp(xs.P, xs.n - c);
     const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
-    double B[NQ];
-    pairk::direct_row_regs(gq * gq, rgq * rgq, B);
+    double B[16], kx;
+    pairk::direct_row_regs(gq * gq, rgq * rgq, B, kx);
 
     // ---- rates with unit-amplitude kernels, their temperature derivatives
     // (times T^2) and the rows of dR_D / d(Ye, e, a_nes, a_pair, s_q) -------
     double dg[NS], c0[NS], c1[NS];  // diagonal of A^T, right-hand sides over it
     {
       double x[NS], en[NS], dn[NS], on[NS], dout[NS], an[NS], dan[NS], ep[NS], dpr[NS];
-      // d = e_q - e_j and its magnitude; e_q is laundered between the passes,
-      // so that they are formed again instead of held
+      // d = e_q - e_j over this row and its magnitude; e_q is laundered
+      // between the passes, so that they are formed again instead of held
+      const int r16 = q & 16;
       double ev = eq;
-      auto ad = [&](int j) { return fabs(ev - md->eps[j]); };
-      auto dl = [&](int j) { return ev - md->eps[j]; };
+      auto dl = [&](int j) { return ev - S.m.eps[r16 + j]; };
+      auto ad = [&](int j) { return fabs(dl(j)); };
+      const double eb = eq - S.m.eps[r16 ? 15 : 16];  // from the other row's node next to this row
 #pragma unroll
       for (int t = 0; t < NS; ++t) x[t] = weq * D[t] * rgq;
-      contract2(x, B, en, dn, [&](int j) { return B[j] * __builtin_fma(0.5, dl(j), ad(j)); });
+      contract2(x, B, kx, __builtin_fma(0.5, eb, fabs(eb)), en, dn,
+                [&](int j) { return B[j] * __builtin_fma(0.5, dl(j), ad(j)); });
       asm volatile("" : "+v"(ev));
 #pragma unroll
       for (int t = 0; t < NS; ++t) x[t] = weq * (1.0 - D[t]) * gq;
-      contract2(x, B, on, dout, [&](int j) { return B[j] * __builtin_fma(-0.5, dl(j), ad(j)); });
+      contract2(x, B, kx, __builtin_fma(-0.5, eb, fabs(eb)), on, dout,
+                [&](int j) { return B[j] * __builtin_fma(-0.5, dl(j), ad(j)); });
       asm volatile("" : "+v"(ev));
 #pragma unroll
       for (int t = 0; t < NS; ++t) x[t] = weq * D[pair_partner<NS>(t)];
-      contract2(x, B, an, dan, [&](int j) { return B[j] * ad(j); });
+      contract2(x, B, kx, fabs(eb), an, dan, [&](int j) { return B[j] * ad(j); });
       asm volatile("" : "+v"(ev));
 #pragma unroll
       for (int t = 0; t < NS; ++t) x[t] = weq * (1.0 - D[pair_partner<NS>(t)]) * hq;
-      contract2(x, B, ep, dpr, [&](int j) { return B[j] * (ad(j) + (ev + md->eps[j])); });
+      contract2(x, B, kx, fabs(eb) + eb, ep, dpr, [&](int j) { return B[j] * (ad(j) + (ev + S.m.eps[r16 + j])); });
       const double sc = rho * eq, scg = sc * gq, scr = sc * rgq, sch = sc * hq;
       const double shape = chi0 * S.m.shape[q], iT2 = invT * invT;
       const double wen = dtau * a_nes * sc * weq, wep = dtau * a_pair * sc * weq;
@@ -613,27 +624,22 @@ struct PairAdjoint {
     const double wn = dtau * a_nes * rho * weq, wp = dtau * a_pair * rho * weq;
     for (int it = 0; it < kAdjMaxIt && __builtin_amdgcn_ballot_w64(act) != 0; ++it) {
 #pragma unroll
-      for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+      for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(B[j]));
       bool moved = false;
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
-        double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
+        double xg[NS], yg[NS], xd[NS], hy[NS];
 #pragma unroll
         for (int t = 0; t < NS; ++t) {
-          const double ez = eq * z[k][t], xd = ez * D[t], yd = ez - xd;
-          swap16(xd * rgq, AR[0][t], AR[1][t]);
-          swap16(yd * gq, BR[0][t], BR[1][t]);
-          swap16(xd, CR[0][t], CR[1][t]);
-          swap16(yd * hq, DR[0][t], DR[1][t]);
+          const double ez = eq * z[k][t];
+          xd[t] = ez * D[t];
+          const double yd = ez - xd[t];
+          xg[t] = xd[t] * rgq;
+          yg[t] = yd * gq;
+          hy[t] = yd * hq;
         }
         double eN[NS], oN[NS], aP[NS], eP[NS];
-#pragma unroll
-        for (int t = 0; t < NS; ++t) eN[t] = oN[t] = aP[t] = eP[t] = 0.0;
-        static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-          constexpr int j = 4 * decltype(jj)::value;
-          pairk::ColSym<NS>::template run<j % 16>(eN, oN, aP, eP, AR[j / 16], BR[j / 16], CR[j / 16], DR[j / 16],
-                                                  B[j], B[j + 1], B[j + 2], B[j + 3]);
-        });
+        pairk::core_contract<NS>(B, kx, xg, yg, xd, hy, eN, oN, aP, eP);
 #pragma unroll
         for (int t = 0; t < NS; ++t) {
           const double ez = eq * z[k][t];

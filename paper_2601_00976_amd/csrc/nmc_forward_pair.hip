@@ -7,22 +7,23 @@
 // I_s[q] of every species.  Every per-point step that a one-point kernel
 // issues for a whole wave (equation of state, opacities, Anderson solves,
 // convergence tests, matter update) serves two points here, and each lane
-// contracts all 32 columns of its row:
-//   - once per outer iteration the lanes of a point fill a 32 x 32 LDS tile
-//     with its pair factors b(q, j) = exp(-|e_q - e_j| / (2T)), signed by
-//     orientation (+b where j > q, -b otherwise), each unordered pair by one
-//     lane, and every lane reads its row back into VGPRs (the tile shares
-//     LDS with the Anderson history, which is dead between inner loops);
-//   - in every inner iteration the vectors W e D and W e (1 - D) of the point
-//     are redistributed with v_permlane16_swap, so that each 16-lane row
-//     holds one half of its point's vector, and every FMA takes its column
-//     through a DPP row_newbcast operand (v_fmac_f64_dpp): the contraction
-//     reads no LDS (the moments and G_j come by broadcast from registers);
-//   - per column, with s the signed factor and c = s^3 (same sign),
-//     max(s, -c) and max(c, -s) are the Phi_in and Phi_out entries (b and
-//     b^3 in one order or the other) without compares or selects;
-//     Phi_ann = s^2 and Phi_pro = min(G_j, G_q) (G falls with energy), all
-//     without their common factor A e_q e_j.
+// contracts its row of the kernels:
+//   - all four kernels share the symmetric core B2 = exp(-|e_q - e_j| / T),
+//     the nodes' factors riding on the vectors and the row sums; once per
+//     outer iteration a lane forms the entries of its own 16-lane row's nodes
+//     and one coefficient for the other row, in registers (see nmc_pair.h);
+//   - in every inner iteration each FMA takes its column through a DPP
+//     row_newbcast operand (v_fmac_f64_dpp), and the other row's share arrives
+//     by one lane exchange per vector;
+//   - points too cold for that fill an LDS tile with their pair factors, each
+//     unordered pair by one lane, and read their entries back: the core, or
+//     signed factors b = exp(-|e_q - e_j| / (2T)) by orientation (the tile
+//     shares LDS with the Anderson history, which is dead between inner loops).
+// An inner iteration is ~690 instructions, 216 of them the multiply-adds of
+// the rates (with the whole rows of 32 columns and the vectors redistributed
+// ~890, 384 of them): 65536 points of the radial profile, two steps, 1189 us
+// (1459 us), 4095 points 78 us (91 us).  Instruction issue at two waves per
+// SIMD bounds large batches.
 // The row sums take their factors A e_q in the Q step.
 //
 // Both halves run one instruction stream.  A half whose point has finished
@@ -187,7 +188,7 @@ struct PairSolver {
         }
         dsig = dtau * sig;
       }
-      // Pair factors of this lane's row, j = 0..31.  Symmetric form (sym):
+      // Pair factors of this lane's row.  Symmetric form (sym):
       // B2(q, j) = b^2 = exp(-|e_q - e_j| / T), the core shared by all four
       // kernels: with g = exp(-e / (2T)) and h = g^2,
       //   Phi_in[q][j] = A e e' B2 g_q / g_j,  Phi_out[q][j] = A e e' B2 g_j / g_q,
@@ -199,11 +200,11 @@ struct PairSolver {
       // orientation form: +b(q, j) for j > q (q the lower node), -b(q, j)
       // otherwise, every entry a product of factors <= 1.
       // Where the grid spans at most kDirectBits powers of two in g (T above
-      // ~0.22 MeV) every lane forms its whole row from the point's scaled h
+      // ~0.22 MeV) every lane forms its entries from the point's scaled h
       // and 1 / h, broadcast from registers (direct_row_regs); otherwise the
       // lanes fill the point's LDS tile, each unordered pair once, and read
-      // their rows back.
-      double B[COUPLED ? NQ : 1];
+      // theirs back.
+      double B[16], kx = 0.0;
       double hq = 0.0;  // exp(-e_q / T)
       double gq = 1.0, rgq = 1.0;  // g_q 2^c and 2^-c / g_q (symmetric form)
       bool sym = false;  // wave-uniform
@@ -231,7 +232,7 @@ struct PairSolver {
           const double gt = PROJ ? ldexp(xs.R, c - xs.n) : gq;
           const double rgt = PROJ ? ldexp(xs.P, xs.n - c) : rgq;
           const double ht = gt * gt, rht = rgt * rgt;
-          direct_row_regs(ht, rht, B);
+          direct_row_regs(ht, rht, B, kx);
         } else {
           // pair factors of the point, each unordered pair (q, q + d mod 32)
           // once: d = 1..15 by every lane, d = 16 by lanes q < 16
@@ -244,9 +245,12 @@ struct PairSolver {
             T[q][q] = -1.0;
           }
           __syncthreads();
-          // row q of the lane: element [j][q] (consecutive lanes, consecutive words)
+          // the lane's entries: [j][q] (consecutive lanes, consecutive words)
+          // of its own row's nodes and of the other row's nearest
+          const int r16 = q & 16;
 #pragma unroll
-          for (int j = 0; j < NQ; ++j) B[j] = T[j][q];
+          for (int j = 0; j < 16; ++j) B[j] = T[r16 + j][q];
+          kx = T[r16 ? 15 : 16][q];
           __syncthreads();
         }
         if constexpr (PROJ) {
@@ -277,19 +281,16 @@ struct PairSolver {
       for (int l = 1; l <= max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
         if (act) l_done = l;
         double etaN[NS], outN[NS], annP[NS], etaP[NS];
-#pragma unroll
-        for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
         if constexpr (COUPLED) {
           // the pair factors are re-read per iteration: the per-column
           // products are not hoisted out of the inner loop (they would need
-          // four times the registers)
+          // more registers than there are)
 #pragma unroll
-          for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+          for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(B[j]));
           if (sym) {
             // W e D / g, g W e (1 - D), W e D and h W e (1 - D) of the point
-            // (g scaled by 2^c), each 16-lane row holding the half
-            // [16 R, 16 R + 16) of the nodes in [.][R][.]
-            double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
+            // (g scaled by 2^c)
+            double xg[NS], yg[NS], xv[NS], hy[NS];
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
               double rg = rgq, g = gq, hh = hq;
@@ -298,44 +299,27 @@ struct PairSolver {
                 hh = S.u.fac[1][t][lane];
                 g = hh * rg;
               }
-              const double xv = w2eq * D[t], yv = w2eq - xv;
-              swap16(xv * rg, AR[0][t], AR[1][t]);
-              swap16(yv * g, BR[0][t], BR[1][t]);
-              swap16(xv, CR[0][t], CR[1][t]);
-              swap16(hh * yv, DR[0][t], DR[1][t]);
+              xv[t] = w2eq * D[t];
+              const double yv = w2eq - xv[t];
+              xg[t] = xv[t] * rg;
+              yg[t] = yv * g;
+              hy[t] = hh * yv;
             }
-            static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-              constexpr int j = 4 * decltype(jj)::value;
-              ColSym<NS>::template run<j % 16>(etaN, outN, annP, etaP, AR[j / 16], BR[j / 16], CR[j / 16],
-                                               DR[j / 16], B[j], B[j + 1], B[j + 2], B[j + 3]);
-            });
+            core_contract<NS>(B, kx, xg, yg, xv, hy, etaN, outN, annP, etaP);
           } else {
-            // W e D, W e (1 - D) and h W e (1 - D) of the point, each 16-lane
-            // row holding the half [16 R, 16 R + 16) of the nodes in XR[.][R],
-            // YR[.][R], HR[.][R]
-            double XR[2][NS], YR[2][NS], HR[2][NS];
+            // W e D, W e (1 - D) and h W e (1 - D) of the point
+            double xv[NS], yv[NS], hy[NS];
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
-              const double xv = w2eq * D[t], yv = w2eq - xv;
-              swap16(xv, XR[0][t], XR[1][t]);
-              swap16(yv, YR[0][t], YR[1][t]);
-              swap16(hq * yv, HR[0][t], HR[1][t]);
+              xv[t] = w2eq * D[t];
+              yv[t] = w2eq - xv[t];
+              hy[t] = hq * yv[t];
             }
-            static_for<0, NQ / 2>([&](auto jj) __attribute__((always_inline)) {
-              constexpr int j0 = 2 * decltype(jj)::value;
-              static_for<0, 2>([&](auto ee) __attribute__((always_inline)) {
-                constexpr int j = j0 + decltype(ee)::value;
-                // with s = +-b and c = s^3 = +-b^3 (the same sign): max(s, -c)
-                // is b where s > 0 and b^3 where s < 0, i.e. Phi_in, and
-                // max(c, -s) is Phi_out (scaled entries), without compares or
-                // selects; Phi_ann = b^2 serves the pair production term as
-                // well (detailed balance: Phi_pro = Phi_ann h_q h_j)
-                const double sb = B[j], b2 = sb * sb, c3 = sb * b2;
-                ColFmac<NS>::template run<j % 16>(etaN, outN, annP, etaP, XR[j / 16], YR[j / 16], HR[j / 16],
-                                                  max_neg_f64(sb, c3), max_neg_f64(c3, sb), b2);
-              });
-            });
+            signed_contract<NS>(B, kx, xv, yv, hy, etaN, outN, annP, etaP);
           }
+        } else {
+#pragma unroll
+          for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
         }
         // Q and residual of both owned moments x = (D_t, I_t); the row sums
         // take their factors A e_q here, and one reciprocal of the product of

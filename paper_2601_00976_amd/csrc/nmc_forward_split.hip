@@ -3,11 +3,11 @@
 // (CDNA4).
 //
 // A batch that does not fill the chip takes as long as its slowest point, and
-// in the two-points-per-wavefront kernel an inner iteration is ~890
-// instructions of one wave: 384 multiply-adds of the rates, the Anderson step
+// in the two-points-per-wavefront kernel an inner iteration is ~690
+// instructions of one wave: 216 multiply-adds of the rates, the Anderson step
 // and the convergence sums of all species one after the other.  Here wave t of
 // the work-group holds species t of both points (lane 32 h + q: node q of the
-// point of half h) and does that species' share of all of it, ~370
+// point of half h) and does that species' share of all of it, ~330
 // instructions; the waves of a work-group run on different SIMDs.  What
 // depends on every species goes through LDS: the number moments of the pair
 // partner (contracted into this species' rates), the Gram sums of the
@@ -142,7 +142,7 @@ struct SplitSolver {
       // row of the symmetric core with the nodes' factors g and 1 / g scaled
       // by 2^+-c (every wave of the work-group forms the same row), where the
       // grid spans at most kDirectBits powers of two; else the splits in LDS
-      double B[NQ];
+      double B[16], kx;
       const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
       const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
       const int lo1 = __builtin_amdgcn_readlane(xs.n, 32), hi1 = __builtin_amdgcn_readlane(xs.n, 63);
@@ -156,7 +156,7 @@ struct SplitSolver {
           rgo = rgt;
           ho = hp = hq;
         }
-        direct_row_regs(gt * gt, rgt * rgt, B);
+        direct_row_regs(gt * gt, rgt * rgt, B, kx);
         if constexpr (PROJ) __syncthreads();
       } else {
         cold_splits(S.cold, h, q, xs);
@@ -179,21 +179,21 @@ struct SplitSolver {
       for (int l = 1; l <= max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
         if (act) l_done = l;
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+        for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(B[j]));
         const double xv = w2eq * D, yv = w2eq - xv;
-        double eN, oN, aP, eP;
+        double eN[1], oN[1], aP[1], eP[1];
         if (direct) {
-          const double xp = w2eq * Dp, yp = w2eq - xp;
-          core_contract(B, xv * rgo, yv * go, xp, hp * yp, eN, oN, aP, eP);
+          const double xp[1] = {w2eq * Dp}, hyp[1] = {hp * (w2eq - xp[0])}, xg[1] = {xv * rgo}, yg[1] = {yv * go};
+          core_contract<1>(B, kx, xg, yg, xp, hyp, eN, oN, aP, eP);
         } else {
-          cold_contract<NS, PROJ>(S.cold, sp, pa, h, q, xv * rgo, yv * go, xv, ho * yv, eN, oN, aP, eP);
+          cold_contract<NS, PROJ>(S.cold, sp, pa, h, q, xv * rgo, yv * go, xv, ho * yv, eN[0], oN[0], aP[0], eP[0]);
         }
         // Q and residual of both owned moments; one reciprocal of the product
         // of the two denominators serves both
         double Q[2], F[2], Xn[2];
         {
-          const double eta = __builtin_fma(ag, eN, aph * eP);
-          const double chi = __builtin_fma(arg, oN, __builtin_fma(Apq, aP, eta));
+          const double eta = __builtin_fma(ag, eN[0], aph * eP[0]);
+          const double chi = __builtin_fma(arg, oN[0], __builtin_fma(Apq, aP[0], eta));
           const double dD = __builtin_fma(dtau, chi, den0D), dI = dD + dsig;
           const double r = rcp_nr(dD * dI);
           Q[0] = __builtin_fma(dtau, eta, baseD) * (r * dI);

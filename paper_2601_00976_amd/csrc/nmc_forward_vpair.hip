@@ -125,44 +125,27 @@ struct VPairSolver {
   // L_pro (partner species) at node q.  Symmetric core: the g and h factors
   // ride on the vectors and the row sums as in the isotropic rates; the
   // orientation form carries the entries directly.
-  __device__ __forceinline__ static void phi1_pass(bool sym, const double (&B)[NQ], const double (&x)[NS], double gq,
-                                                   double rgq, double hq, double (&Lin)[NS], double (&Lout)[NS],
-                                                   double (&Lann)[NS], double (&Lpro)[NS]) {
-    double eN[NS], oN[NS], aP[NS], eP[NS];
+  __device__ __forceinline__ static void phi1_pass(bool sym, const double (&B)[16], double kx, const double (&x)[NS],
+                                                   double gq, double rgq, double hq, double (&Lin)[NS],
+                                                   double (&Lout)[NS], double (&Lann)[NS], double (&Lpro)[NS]) {
+    double eN[NS], oN[NS], aP[NS], eP[NS], hx[NS];
 #pragma unroll
-    for (int t = 0; t < NS; ++t) eN[t] = oN[t] = aP[t] = eP[t] = 0.0;
+    for (int t = 0; t < NS; ++t) hx[t] = hq * x[t];
     if (__builtin_expect(sym, 1)) {
-      double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
+      double xg[NS], yg[NS];
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
-        swap16(x[t] * rgq, AR[0][t], AR[1][t]);
-        swap16(x[t] * gq, BR[0][t], BR[1][t]);
-        swap16(x[t], CR[0][t], CR[1][t]);
-        swap16(hq * x[t], DR[0][t], DR[1][t]);
+        xg[t] = x[t] * rgq;
+        yg[t] = x[t] * gq;
       }
-      static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-        constexpr int j = 4 * decltype(jj)::value;
-        ColSym<NS>::template run<j % 16>(eN, oN, aP, eP, AR[j / 16], BR[j / 16], CR[j / 16], DR[j / 16], B[j],
-                                         B[j + 1], B[j + 2], B[j + 3]);
-      });
+      core_contract<NS>(B, kx, xg, yg, x, hx, eN, oN, aP, eP);
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
         Lin[t] = gq * eN[t];
         Lout[t] = rgq * oN[t];
       }
     } else {
-      double XR[2][NS], HR[2][NS];
-#pragma unroll
-      for (int t = 0; t < NS; ++t) {
-        swap16(x[t], XR[0][t], XR[1][t]);
-        swap16(hq * x[t], HR[0][t], HR[1][t]);
-      }
-      static_for<0, NQ>([&](auto jj) __attribute__((always_inline)) {
-        constexpr int j = decltype(jj)::value;
-        const double sb = B[j], b2 = sb * sb, c3 = sb * b2;
-        ColFmac<NS>::template run<j % 16>(eN, oN, aP, eP, XR[j / 16], XR[j / 16], HR[j / 16],
-                                          max_neg_f64(sb, c3), max_neg_f64(c3, sb), b2);
-      });
+      signed_contract<NS>(B, kx, x, x, hx, eN, oN, aP, eP);
 #pragma unroll
       for (int t = 0; t < NS; ++t) {
         Lin[t] = eN[t];
@@ -301,7 +284,7 @@ struct VPairSolver {
         }
       }
       // pair factors of this lane's row (as in the static two-point kernel)
-      double B[COUPLED ? NQ : 1];
+      double B[16], kx = 0.0;
       double hq = 0.0;
       double gq = 1.0, rgq = 1.0;
       bool sym = false;  // wave-uniform
@@ -324,7 +307,7 @@ struct VPairSolver {
         if (__builtin_expect(direct, 1)) {
           // rows of the symmetric core from the point's scaled h, broadcast
           // from registers
-          direct_row_regs(gq * gq, rgq * rgq, B);
+          direct_row_regs(gq * gq, rgq * rgq, B, kx);
         } else {
           double (*Tt)[NQ] = S.u.tile[h];
           if (__builtin_expect(sym, 1)) {
@@ -335,8 +318,10 @@ struct VPairSolver {
             Tt[q][q] = -1.0;
           }
           __syncthreads();
+          const int r16 = q & 16;
 #pragma unroll
-          for (int j = 0; j < NQ; ++j) B[j] = Tt[j][q];
+          for (int j = 0; j < 16; ++j) B[j] = Tt[r16 + j][q];
+          kx = Tt[r16 ? 15 : 16][q];
           __syncthreads();
         }
       }
@@ -356,47 +341,32 @@ struct VPairSolver {
       for (int l = 1; l <= max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
         if (act) l_done = l;
         double etaN[NS], outN[NS], annP[NS], etaP[NS];
-#pragma unroll
-        for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
         if constexpr (COUPLED) {
 #pragma unroll
-          for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+          for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(B[j]));
+          double xv[NS], yv[NS], hy[NS];
+#pragma unroll
+          for (int t = 0; t < NS; ++t) {
+            xv[t] = w2eq * D[t];
+            yv[t] = w2eq - xv[t];
+            hy[t] = hq * yv[t];
+          }
           // the expected form lies on the loop's straight path (placement alone
           // is worth 4% with the linear-order terms, whose passes repeat it)
           if (__builtin_expect(sym, 1)) {
-            double AR[2][NS], BR[2][NS], CR[2][NS], DR[2][NS];
+            double xg[NS], yg[NS];
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
-              const double xv = w2eq * D[t], yv = w2eq - xv;
-              swap16(xv * rgq, AR[0][t], AR[1][t]);
-              swap16(yv * gq, BR[0][t], BR[1][t]);
-              swap16(xv, CR[0][t], CR[1][t]);
-              swap16(hq * yv, DR[0][t], DR[1][t]);
+              xg[t] = xv[t] * rgq;
+              yg[t] = yv[t] * gq;
             }
-            static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-              constexpr int j = 4 * decltype(jj)::value;
-              ColSym<NS>::template run<j % 16>(etaN, outN, annP, etaP, AR[j / 16], BR[j / 16], CR[j / 16],
-                                               DR[j / 16], B[j], B[j + 1], B[j + 2], B[j + 3]);
-            });
+            core_contract<NS>(B, kx, xg, yg, xv, hy, etaN, outN, annP, etaP);
           } else {
-            double XR[2][NS], YR[2][NS], HR[2][NS];
-#pragma unroll
-            for (int t = 0; t < NS; ++t) {
-              const double xv = w2eq * D[t], yv = w2eq - xv;
-              swap16(xv, XR[0][t], XR[1][t]);
-              swap16(yv, YR[0][t], YR[1][t]);
-              swap16(hq * yv, HR[0][t], HR[1][t]);
-            }
-            static_for<0, NQ / 2>([&](auto jj) __attribute__((always_inline)) {
-              constexpr int j0 = 2 * decltype(jj)::value;
-              static_for<0, 2>([&](auto ee) __attribute__((always_inline)) {
-                constexpr int j = j0 + decltype(ee)::value;
-                const double sb = B[j], b2 = sb * sb, c3 = sb * b2;
-                ColFmac<NS>::template run<j % 16>(etaN, outN, annP, etaP, XR[j / 16], YR[j / 16], HR[j / 16],
-                                                  max_neg_f64(sb, c3), max_neg_f64(c3, sb), b2);
-              });
-            });
+            signed_contract<NS>(B, kx, xv, yv, hy, etaN, outN, annP, etaP);
           }
+        } else {
+#pragma unroll
+          for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
         }
         // linear-order corrections at the current iterate (PHI1): with
         // P = r_N L_in - r_P L_pro and R = r_N L_out - r_P L_ann per flux
@@ -411,7 +381,7 @@ struct VPairSolver {
             double x[NS], Lin[NS], Lout[NS], Lann[NS], Lpro[NS];
 #pragma unroll
             for (int t = 0; t < NS; ++t) x[t] = w2eq * I[t][i];
-            phi1_pass(sym, B, x, gq, rgq, hq, Lin, Lout, Lann, Lpro);
+            phi1_pass(sym, B, kx, x, gq, rgq, hq, Lin, Lout, Lann, Lpro);
 #pragma unroll
             for (int t = 0; t < NS; ++t) {
               Pc[t][i] = __builtin_fma(rN, Lin[t], -rP * Lpro[t]);
@@ -751,7 +721,8 @@ hipError_t launch_vpair_t(FwdVArgs a, const nmc_launch& L, int num_cu, hipStream
 
 hipError_t launch_forward_vpair(const FwdVArgs& a, int ns, bool coupled, bool phi1, const nmc_launch& L,
                                 int num_cu, hipStream_t s) {
-  if (coupled && split_by_species(a.P, ns, num_cu)) return launch_forward_vsplit(a, ns, phi1, L, num_cu, s);
+  if (coupled && split_by_species(a.P, ns, num_cu, phi1 ? kSplitWaves : kSplitWavesV))
+    return launch_forward_vsplit(a, ns, phi1, L, num_cu, s);
   if (coupled && phi1) {
     switch (ns) {
       case 1: return launch_vpair_t<1, true, true>(a, L, num_cu, s);

@@ -7,8 +7,8 @@
 // moments (D, I_1, I_2, I_3) of species t of both points, lane 32 h + q node q
 // of the point of half h.  A wave of the two-point kernel needs more than 256
 // registers for three species (one wave per SIMD, its dependent chains
-// exposed) and ~1350 instructions per inner iteration; a species' share fits
-// two waves per SIMD with its Anderson history in registers and takes ~500.
+// exposed) and ~1120 instructions per inner iteration; a species' share fits
+// two waves per SIMD with its Anderson history in registers and takes ~450.
 // Through LDS go the moments of the pair partner, the Gram sums and the
 // convergence flags (two barriers per inner iteration) and the Eulerian
 // integrals of the matter update.  What follows from them is computed by
@@ -203,7 +203,7 @@ struct VSplitSolver {
       // by 2^+-c and h (every wave of the work-group forms the same row),
       // where the grid spans at most kDirectBits powers of two; else the
       // splits in LDS, with the factors in the entries
-      double B[NQ], gq = 1.0, rgq = 1.0, hq = 1.0;
+      double B[16], kx, gq = 1.0, rgq = 1.0, hq = 1.0;
       const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
       const int lo1 = __builtin_amdgcn_readlane(xs.n, 32), hi1 = __builtin_amdgcn_readlane(xs.n, 63);
       const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
@@ -213,7 +213,7 @@ struct VSplitSolver {
         gq = ldexp(xs.R, c - xs.n);
         rgq = ldexp(xs.P, xs.n - c);
         hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
-        direct_row_regs(gq * gq, rgq * rgq, B);
+        direct_row_regs(gq * gq, rgq * rgq, B, kx);
       } else {
         cold_splits(S.cold, h, q, xs);
       }
@@ -236,15 +236,15 @@ struct VSplitSolver {
       for (int l = 1; l <= max_inner && __builtin_amdgcn_ballot_w64(act) != 0; ++l) {
         if (act) l_done = l;
 #pragma unroll
-        for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
-        double etaN, outN, annP, etaP;
+        for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(B[j]));
+        double etaN[1], outN[1], annP[1], etaP[1];
         {
           const double xv = w2eq * D, yv = w2eq - xv;
           if (direct) {
-            const double xp = w2eq * Dp, yp = w2eq - xp;
-            core_contract(B, xv * rgq, yv * gq, xp, hq * yp, etaN, outN, annP, etaP);
+            const double xp[1] = {w2eq * Dp}, hyp[1] = {hq * (w2eq - xp[0])}, xg[1] = {xv * rgq}, yg[1] = {yv * gq};
+            core_contract<1>(B, kx, xg, yg, xp, hyp, etaN, outN, annP, etaP);
           } else {
-            cold_contract<NS, false>(S.cold, sp, pa, h, q, xv, yv, xv, yv, etaN, outN, annP, etaP);
+            cold_contract<NS, false>(S.cold, sp, pa, h, q, xv, yv, xv, yv, etaN[0], outN[0], annP[0], etaP[0]);
           }
         }
         // linear-order corrections at the current iterate (see the two-point kernel)
@@ -255,15 +255,15 @@ struct VSplitSolver {
 #pragma unroll
           for (int i = 0; i < 3; ++i) {
             const double x = w2eq * I[i];
-            double eN, oN, aP, eP;
+            double eN[1], oN[1], aP[1], eP[1];
             if (direct) {
-              const double xp = w2eq * Ip[i];
-              core_contract(B, x * rgq, x * gq, xp, hq * xp, eN, oN, aP, eP);
+              const double xp[1] = {w2eq * Ip[i]}, hxp[1] = {hq * xp[0]}, xg[1] = {x * rgq}, yg[1] = {x * gq};
+              core_contract<1>(B, kx, xg, yg, xp, hxp, eN, oN, aP, eP);
             } else {
-              cold_contract<NS, false>(S.cold, sp, pa, h, q, x, x, x, x, eN, oN, aP, eP);
+              cold_contract<NS, false>(S.cold, sp, pa, h, q, x, x, x, x, eN[0], oN[0], aP[0], eP[0]);
             }
-            Pc[i] = __builtin_fma(rN, gq * eN, -rP * (hq * eP));
-            Rc[i] = __builtin_fma(rN, rgq * oN, -rP * aP);
+            Pc[i] = __builtin_fma(rN, gq * eN[0], -rP * (hq * eP[0]));
+            Rc[i] = __builtin_fma(rN, rgq * oN[0], -rP * aP[0]);
           }
           phi1_collision_flat(D, I, Pc, Rc, cN, cI);
         }
@@ -271,8 +271,8 @@ struct VSplitSolver {
         // reciprocal of the product of the two denominators serves both
         double Q[4], F[4], Xn[4];
         {
-          const double eta = __builtin_fma(ag, etaN, Apqh * etaP);
-          const double chi = __builtin_fma(arg, outN, __builtin_fma(Apq, annP, eta));
+          const double eta = __builtin_fma(ag, etaN[0], Apqh * etaP[0]);
+          const double chi = __builtin_fma(arg, outN[0], __builtin_fma(Apq, annP[0], eta));
           double vI, vK[3];
           closure_terms_flat(D, I, v, vI, vK);
           const double dD = __builtin_fma(ldt, chi, denD), dI = __builtin_fma(ldt, chi, denI);

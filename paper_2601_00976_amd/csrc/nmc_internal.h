@@ -157,18 +157,21 @@ inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, in
 }
 
 // Whether a batch is small enough for one wavefront per species of a pair of
-// points instead of one per pair: up to 12 such wavefronts per compute unit,
-// half as many again as are resident.  There the slowest points set the time
-// and their share of work per wavefront is what counts; beyond, the species'
-// common work (equation of state, rows) done once per wavefront costs more.
-// Three species, split against pairs: static solve of 8 points 47 against
-// 64 us, 2048 points 60 against 86 us, 4095 points 94 against 92 us; O(v)
-// solve of 8 points 130 against 192 us, 2048 points 219 against 232 us, 2730
-// points 275 against 233 us (with linear-order kernels 204 against 383, 351
-// against 469 and 446 against 470 us).  A rule of the batch alone: results do
-// not depend on the launch shape.
-inline bool split_by_species(int64_t P, int ns, int num_cu) {
-  return ns > 1 && (P + 1) / 2 * ns <= (int64_t)12 * num_cu;
+// points instead of one per pair: up to `waves` such wavefronts per compute
+// unit (eight are resident).  There the slowest points set the time and their
+// share of work per wavefront is what counts; beyond, the species' common work
+// (equation of state, rows) done once per wavefront costs more.  Static solve
+// and O(v) solve with linear-order kernels kSplitWaves, plain O(v) solve
+// kSplitWavesV.  Three species, split against pairs: static solve of 8 points
+// 44 against 62 us, 2048 points 60 against 75, 2730 points (16 waves) 71
+// against 76, 3400 points 83 against 78; projected equilibrium 2730 points 96
+// against 124; O(v) solve of 8 points 116 against 168, 2048 points (12 waves)
+// 189 against 216, 2730 points 238 against 216; with linear-order kernels 8
+// points 166 against 297, 2730 points 351 against 388, 4096 points 495 against
+// 403.  A rule of the batch alone: results do not depend on the launch shape.
+constexpr int kSplitWaves = 16, kSplitWavesV = 12;
+inline bool split_by_species(int64_t P, int ns, int num_cu, int waves) {
+  return ns > 1 && (P + 1) / 2 * ns <= (int64_t)waves * num_cu;
 }
 
 // its grid: one work-group per pair, or as many as the caller wants resident

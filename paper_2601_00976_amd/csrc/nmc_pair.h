@@ -20,22 +20,65 @@ constexpr int kSymBits = 1800;
 // (within 2^(+-(kDirectBits + 4)), inside the normal range)
 constexpr int kDirectBits = 1000;
 
-// Row q of the symmetric core B2(q, j) = exp(-|e_q - e_j| / T), q this
-// lane's node, from the scaled h = exp(-e / T) 2^2c of every node of the
-// point and their reciprocals, held in registers: after swap16, H[g] and
-// RH[g] carry nodes [16 g, 16 g + 16) in every 16-lane row, and column j is
-// taken from lane j % 16 of the row by DPP broadcast.  Of the two
-// orientations h_j / h_q and h_q / h_j the smaller is B2 (the other is its
-// reciprocal, or overflows to +inf).  The diagonal comes out as h_q / h_q,
-// one to within two roundings.
-__device__ __forceinline__ void direct_row_regs(double hq, double rhq, double (&B)[32]) {
-  double H[2], RH[2];
-  swap16(hq, H[0], H[1]);
-  swap16(rhq, RH[0], RH[1]);
-  static_for<0, 32>([&](auto jj) __attribute__((always_inline)) {
+// The symmetric core B2(q, j) = exp(-|e_q - e_j| / T) is semiseparable: where
+// q and j lie in different 16-lane rows of the half, with b the node of j's
+// row next to q's row, B2(q, j) = B2(q, b) B2(b, j).  So the sum over the
+// other row's columns is B2(q, b) times the value that lane b has from its own
+// row's columns, and a lane needs the 16 entries of its own row and this one
+// coefficient: 16 + 2 multiply-adds and one exchange per vector instead of 32
+// and the vector's redistribution, and half the registers.  The same holds for
+// the four kernels themselves, each an exponential on either side of the
+// diagonal.
+
+// Row q of the core, q this lane's node, from the scaled h = exp(-e / T) 2^2c
+// of the point's nodes and their reciprocals: B[i] for node i of this row
+// (column taken from lane i by DPP broadcast) and the coefficient k for the
+// other row.  Of the two orientations h_j / h_q and h_q / h_j the smaller is
+// B2 (the other is its reciprocal, or overflows to +inf).  The diagonal comes
+// out as h_q / h_q, one to within two roundings.
+__device__ __forceinline__ void direct_row_regs(double hq, double rhq, double (&B)[16], double& k) {
+  static_for<0, 16>([&](auto jj) __attribute__((always_inline)) {
     constexpr int j = decltype(jj)::value;
-    B[j] = min_f64(row_bcast<j % 16>(H[j / 16]) * rhq, hq * row_bcast<j % 16>(RH[j / 16]));
+    B[j] = min_f64(row_bcast<j>(hq) * rhq, hq * row_bcast<j>(rhq));
   });
+  // node 16 seen from the lower row, node 15 from the upper one
+  const double up = row_bcast<15>(mirror32(hq)) * rhq, down = hq * row_bcast<0>(mirror32(rhq));
+  k = (threadIdx.x & 16) ? down : up;
+}
+
+// The other row's part of the sums y, z = mirror32(y) and coefficients k:
+// lane 15 of z carries the upper row's sum at node 16 (for the lower row),
+// lane 0 the lower row's at node 15 (for the upper row).
+__device__ __forceinline__ void cross_fmac(double& y0, double& y1, double& y2, double& y3, double z0, double z1,
+                                           double z2, double z3, double k0, double k1, double k2, double k3) {
+  asm volatile(
+      "s_nop 1\n"
+      "v_fmac_f64_dpp %0, %4, %8 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %5, %9 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n"
+      "v_fmac_f64_dpp %2, %6, %10 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n"
+      "v_fmac_f64_dpp %3, %7, %11 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n"
+      "v_fmac_f64_dpp %0, %4, %8 row_newbcast:0 row_mask:0xa bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %5, %9 row_newbcast:0 row_mask:0xa bank_mask:0xf\n"
+      "v_fmac_f64_dpp %2, %6, %10 row_newbcast:0 row_mask:0xa bank_mask:0xf\n"
+      "v_fmac_f64_dpp %3, %7, %11 row_newbcast:0 row_mask:0xa bank_mask:0xf\n"
+      : "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3)
+      : "v"(z0), "v"(z1), "v"(z2), "v"(z3), "v"(k0), "v"(k1), "v"(k2), "v"(k3));
+}
+
+template <int NS>
+__device__ __forceinline__ void cross_rows(double (&eN)[NS], double (&oN)[NS], double (&aP)[NS], double (&eP)[NS],
+                                           double kN, double kO, double kP) {
+  double z[4][NS];
+#pragma unroll
+  for (int t = 0; t < NS; ++t) {
+    z[0][t] = mirror32(eN[t]);
+    z[1][t] = mirror32(oN[t]);
+    z[2][t] = mirror32(aP[t]);
+    z[3][t] = mirror32(eP[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < NS; ++t)
+    cross_fmac(eN[t], oN[t], aP[t], eP[t], z[0][t], z[1][t], z[2][t], z[3][t], kN, kO, kP, kP);
 }
 
 // Sums over the lane's half-wave of 2K values, in every lane of the half:
@@ -404,6 +447,44 @@ struct ColSym<1> {
         : "v"(a[0]), "v"(b[0]), "v"(c[0]), "v"(d[0]), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "i"(L0 + 0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
   }
 };
+
+// The contractions of the rates on the core: eN = B2 a_s, oN = B2 b_s,
+// aP = B2 c_sbar, eP = B2 d_sbar.
+template <int NS>
+__device__ __forceinline__ void core_contract(const double (&B)[16], double k, const double (&a)[NS],
+                                              const double (&b)[NS], const double (&c)[NS], const double (&d)[NS],
+                                              double (&eN)[NS], double (&oN)[NS], double (&aP)[NS], double (&eP)[NS]) {
+#pragma unroll
+  for (int t = 0; t < NS; ++t) eN[t] = oN[t] = aP[t] = eP[t] = 0.0;
+  static_for<0, 4>([&](auto jj) __attribute__((always_inline)) {
+    constexpr int j = 4 * decltype(jj)::value;
+    ColSym<NS>::template run<j>(eN, oN, aP, eP, a, b, c, d, B[j], B[j + 1], B[j + 2], B[j + 3]);
+  });
+  cross_rows<NS>(eN, oN, aP, eP, k, k, k);
+}
+
+// The same from the signed pair factors of the orientation form (+b where j
+// is the upper node, -b otherwise; B for this row, k for the node b next to
+// it): eN = Phi_in x_s, oN = Phi_out y_s, aP = Phi_ann x_sbar and
+// eP = Phi_ann (h y)_sbar.  With s = +-b and c = s^3 = +-b^3 (the same sign):
+// max(s, -c) is b where s > 0 and b^3 where s < 0, i.e. Phi_in, and max(c, -s)
+// is Phi_out (scaled entries), without compares or selects; Phi_ann = b^2
+// serves the pair production term as well (detailed balance:
+// Phi_pro = Phi_ann h_q h_j).
+template <int NS>
+__device__ __forceinline__ void signed_contract(const double (&B)[16], double k, const double (&x)[NS],
+                                                const double (&y)[NS], const double (&hy)[NS], double (&eN)[NS],
+                                                double (&oN)[NS], double (&aP)[NS], double (&eP)[NS]) {
+#pragma unroll
+  for (int t = 0; t < NS; ++t) eN[t] = oN[t] = aP[t] = eP[t] = 0.0;
+  static_for<0, 16>([&](auto jj) __attribute__((always_inline)) {
+    constexpr int j = decltype(jj)::value;
+    const double sb = B[j], b2 = sb * sb, c3 = sb * b2;
+    ColFmac<NS>::template run<j>(eN, oN, aP, eP, x, y, hy, max_neg_f64(sb, c3), max_neg_f64(c3, sb), b2);
+  });
+  const double k2 = k * k, k3 = k * k2;
+  cross_rows<NS>(eN, oN, aP, eP, max_neg_f64(k, k3), max_neg_f64(k3, k), k2);
+}
 
 }  // namespace pairk
 }  // namespace nmc

@@ -26,30 +26,9 @@ __device__ __forceinline__ void species_sum(const double (&v)[NS][2][M], int h, 
     for (int i = 0; i < N; ++i) s[i] += v[t][h][i];
 }
 
-// The four contractions of a species' rates on its row B of the symmetric
-// core: eN = B2 a, oN = B2 b over its own vectors and aP = B2 c, eP = B2 d
-// over its pair partner's, columns broadcast by DPP.
-__device__ __forceinline__ void core_contract(const double (&B)[32], double a, double b, double c, double d,
-                                              double& eN, double& oN, double& aP, double& eP) {
-  double e[1] = {0.0}, o[1] = {0.0}, x[1] = {0.0}, p[1] = {0.0};
-  double AR[2][1], BR[2][1], CR[2][1], DR[2][1];
-  swap16(a, AR[0][0], AR[1][0]);
-  swap16(b, BR[0][0], BR[1][0]);
-  swap16(c, CR[0][0], CR[1][0]);
-  swap16(d, DR[0][0], DR[1][0]);
-  static_for<0, 8>([&](auto jj) __attribute__((always_inline)) {
-    constexpr int j = 4 * decltype(jj)::value;
-    pairk::ColSym<1>::template run<j % 16>(e, o, x, p, AR[j / 16], BR[j / 16], CR[j / 16], DR[j / 16], B[j], B[j + 1],
-                                           B[j + 2], B[j + 3]);
-  });
-  eN = e[0];
-  oN = o[0];
-  aP = x[0];
-  eP = p[0];
-}
-
-// The same at a point whose grid spans too many powers of two for the row:
-// entries regenerated column by column from the splits in LDS, in a rolled
+// The four contractions of a species' rates (core_contract, c and d of its
+// pair partner) at a point whose grid spans too many powers of two for the
+// row: entries regenerated column by column from the splits in LDS, in a rolled
 // loop that needs few registers (such points are rare, and rows held for them
 // would cost the others a wave per SIMD).  CORE: every entry is
 // b^2 = exp(-|e_q - e_j| / T) and the factors are on the vectors; otherwise

@@ -50,6 +50,12 @@ __device__ __forceinline__ void swap16(double v, double& first, double& second) 
   second = mk64(a[1], b[1]);
 }
 
+// the value of lane 31 - i of this 32-lane half (ds_swizzle: no LDS memory)
+__device__ __forceinline__ double mirror32(double v) {
+  return mk64((uint32_t)__builtin_amdgcn_ds_swizzle((int)lo32(v), 0x7C1F),
+              (uint32_t)__builtin_amdgcn_ds_swizzle((int)hi32(v), 0x7C1F));
+}
+
 // v_permlane32_swap(v, v): first = lanes 0..31 of v in both halves, second = lanes 32..63
 __device__ __forceinline__ void swap32(double v, double& first, double& second) {
   auto a = __builtin_amdgcn_permlane32_swap(lo32(v), lo32(v), false, false);

@@ -34,12 +34,12 @@ def _same(a, b, w2, names):
 
 
 def _in_a_large_batch(run, t, P):
-    """run(t) of the points of t repeated to at least 4096 points, the first P of the results"""
-    big = {k: v.repeat((-(-4096 // P),) + (1,) * (v.dim() - 1)) for k, v in t.items()}
+    """run(t) of the points of t repeated to at least 8192 points, the first P of the results"""
+    big = {k: v.repeat((-(-8192 // P),) + (1,) * (v.dim() - 1)) for k, v in t.items()}
     return {k: v[:P] for k, v in run(big).items()}
 
 
-@pytest.mark.parametrize("P", [1, 2, 3, 77, 2047, 2049])
+@pytest.mark.parametrize("P", [1, 2, 3, 77, 2047, 2730, 2731])
 @pytest.mark.parametrize("sp,options", [(SP3, {}), (SP2, {}), (SP3, {"fd_projection": 1}),
                                         (SP3, {"flags": N.EMAB | N.NES}), ((N.NU_X, N.NU_E_BAR, N.NU_E), {})])
 def test_split_static(P, sp, options):

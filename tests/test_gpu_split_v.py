@@ -48,8 +48,8 @@ def _state(m, d):
 
 
 def _in_a_large_batch(run, t, P):
-    """run(t) of the points of t repeated to at least 4096 points, the first P of the results"""
-    big = {k: v.repeat((-(-4096 // P),) + (1,) * (v.dim() - 1)) for k, v in t.items()}
+    """run(t) of the points of t repeated to at least 8192 points, the first P of the results"""
+    big = {k: v.repeat((-(-8192 // P),) + (1,) * (v.dim() - 1)) for k, v in t.items()}
     return {k: v[:P] for k, v in run(big).items()}
 
 
