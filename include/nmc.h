@@ -181,11 +181,13 @@ typedef struct {
 
 /* Where the energy-coupling kernel matrices live during a solve, and how
  * the 32-node solve maps points to wavefronts.
- * ON_CHIP: the library's default.  32 nodes: as PAIRED; 64 nodes: row q of
- *   the symmetric core exp(-|e - e'| / T) that all four kernels share in the
- *   registers of lane q, formed once per outer iteration.
+ * ON_CHIP: the library's default.  32 nodes: as PAIRED; 64 nodes: of row q
+ *   of the symmetric core exp(-|e - e'| / T) that all four kernels share, the
+ *   entries of the lane's 16 nodes and the coefficients through which the
+ *   other nodes' sums enter, in the registers of lane q, formed once per outer
+ *   iteration.
  * HBM: 64-node solve only, for the roofline study of precomputed kernels:
- *   the core of every point is written to the workspace once per outer
+ *   these entries of every point are written to the workspace once per outer
  *   iteration and re-read by every inner iteration; the workspace then needs
  *   nmc_kernel_store_bytes(m, P) more bytes after the
  *   nmc_workspace_bytes(m, P) ones. */
@@ -201,10 +203,11 @@ typedef struct {
  * with DPP row broadcasts. */
 #define NMC_KERNELS_REGISTERS 3
 /* PAIRED: 32 nodes only: two points per wavefront, one per half; each lane
- * owns one node of its point (both moments) and contracts all 32 columns of
- * its row, the columns broadcast from registers (DPP); the lane's pair
- * factors exp(-|e - e'| / (2T)) are computed once per outer iteration and
- * kept in VGPRs. */
+ * owns one node of its point (every moment of every species) and contracts
+ * the columns of its 16-lane row, broadcast from registers (DPP), the other
+ * row's share entering by one coefficient; these factors are computed once per
+ * outer iteration and kept in VGPRs.  Batches too small to fill the chip run
+ * one wavefront per species of a pair of points instead. */
 #define NMC_KERNELS_PAIRED 4
 /* WAVE: 32 nodes only: one point per wavefront, the two lane halves owning
  * the number and flux moments and splitting the 32 columns; the lane's 16
@@ -232,8 +235,8 @@ int nmc_model_destroy(nmc_model* m);
 /* Bytes of device workspace a solve call with P points needs. */
 size_t nmc_workspace_bytes(const nmc_model* m, int64_t P);
 /* Extra workspace bytes of a solve with kernel_store = NMC_KERNELS_HBM:
- * 3 nq^2 doubles per point, of which the core takes the first nq^2 (0 if the
- * model cannot use that mode). */
+ * 3 nq^2 doubles per point, of which the solve uses 18 nq (0 if the model
+ * cannot use that mode). */
 size_t nmc_kernel_store_bytes(const nmc_model* m, int64_t P);
 
 /* Batched forward solve: Algorithm neutrinoMatterCoupling at every point.
@@ -330,8 +333,9 @@ typedef struct {
 /* Batched O(v) forward solve.  32-node grids only (NMC_E_UNSUPPORTED
  * otherwise).  launch->kernel_store NMC_KERNELS_ON_CHIP (default) or
  * NMC_KERNELS_PAIRED: two points per wavefront, each lane owning the four
- * moments of its node; NMC_KERNELS_WAVE: one point per wavefront.  Both
- * carry the linear-order corrections when phi1_nes or phi1_pair is nonzero.
+ * moments of its node (small batches: one wavefront per species of a pair of
+ * points); NMC_KERNELS_WAVE: one point per wavefront.  All carry the
+ * linear-order corrections when phi1_nes or phi1_pair is nonzero.
  * Other modes return NMC_E_UNSUPPORTED.  Workspace, launch, stream and error
  * rules as for nmc_solve_batch; dtau must be positive. */
 int nmc_solve_batch_v(const nmc_model* m, const nmc_solver_params* prm, int64_t P, double dtau,

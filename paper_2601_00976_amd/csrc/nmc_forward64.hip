@@ -10,18 +10,20 @@
 // g = exp(-e / (2T)), h = g^2 and B2(q, j) = exp(-|e_q - e_j| / T),
 //   Phi_in[q][j] = A e_q e_j B2 g_q / g_j,  Phi_out[q][j] = A e_q e_j B2 g_j / g_q,
 //   Phi_ann = A' e_q e_j B2,                Phi_pro = A' e_q e_j B2 h_q h_j,
-// so a lane keeps row q of B2 (64 doubles) in VGPRs, formed once per outer
-// iteration, and every inner iteration contracts it against W e D / g,
-// g W e (1 - D), W e D and h W e (1 - D).  The vectors are redistributed with
-// v_permlane32_swap and v_permlane16_swap, so that every 16-lane row holds
-// each quarter of them, and the FMAs take column j by DPP row_newbcast: 12
-// FMAs per column for three species and no LDS.  One kind of vector is
-// contracted at a time (24 VGPRs of quarters instead of 96), which keeps two
-// waves per SIMD.  g and 1 / g are scaled by 2^+-c, c the middle of the
-// point's exponent range.  The multiply-adds' issue and, for small batches,
-// the dependent reductions bound it: 131072 points of the radial profile take
-// 3.14 ms (4.84 ms with every column regenerated from LDS in every inner
-// iteration, twice the instructions), 1001 points 122 us (233 us).
+// and every inner iteration contracts B2 against W e D / g, g W e (1 - D),
+// W e D and h W e (1 - D).  B2 is semiseparable: for q and j in different
+// blocks of nodes, with b the node of j's block next to q's, B2(q, j) =
+// B2(q, b) B2(b, j).  A lane keeps the 16 entries of its own 16-lane row (FMAs
+// that take column j by DPP row_newbcast), one coefficient for the other row
+// of its half and one for the other half, formed once per outer iteration; the
+// sums at the neighbouring nodes arrive by one lane exchange each
+// (ds_swizzle, ds_bpermute).  19 multiply-adds and two exchanges per vector
+// instead of 64 and the vector's redistribution.  g and 1 / g are scaled by
+// 2^+-c, c the middle of the point's exponent range.  Instruction issue at two
+// waves per SIMD and, for small batches, the dependent reductions bound it:
+// 131072 points of the radial profile take 1.73 ms (3.10 ms with rows of 64
+// entries in registers, 4.84 ms with every column regenerated from LDS in
+// every inner iteration), 1001 points 72 us (124 us, 233 us).
 //
 // Where the grid spans more than kDirectBits64 powers of two in g (T below
 // ~0.22 MeV) the lanes instead regenerate their rows column by column in every
@@ -35,13 +37,13 @@
 // full-wave register reductions.
 //
 // The PRE variant (kernel_store = HBM; the roofline study of precomputed
-// kernels) writes the point's core to the workspace once per outer iteration,
-// laid out [column j][row q] so that every access is a coalesced 512-byte
-// wave load or store, and reads it back in every inner iteration.  Each lane
+// kernels) writes the entries and coefficients to the workspace once per outer
+// iteration, laid out [entry][lane] so that every access is a coalesced
+// 512-byte wave load or store, and reads them back in every inner iteration.  Each lane
 // reads only what it wrote, so no barrier is needed between the two.  Both
 // variants perform the same floating-point operations on the same values, so
 // their results agree bit for bit.
-#include "nmc_wave.h"
+#include "nmc_pair.h"
 
 namespace nmc {
 namespace {
@@ -50,6 +52,9 @@ constexpr int NQ64 = 64;
 // widest exponent range of g for the register rows: squares of the scaled
 // factors and their reciprocals stay inside the normal range
 constexpr int kDirectBits64 = 1000;
+// per lane: the entries of its 16-lane row, the other row's coefficient, the
+// other half's
+constexpr int kCore = 18;
 
 template <int NS>
 struct Lds64 {
@@ -174,30 +179,37 @@ struct PointSolver64 {
     }
   }
 
-  // v of every lane, quarter k of the nodes in V[k] of every 16-lane row
-  __device__ __forceinline__ static void quarters(double v, double& v0, double& v1, double& v2, double& v3) {
-    double lo, hi;
-    swap32(v, lo, hi);
-    swap16(lo, v0, v1);
-    swap16(hi, v2, v3);
-  }
-  // acc[t] = sum_j B2(q, j) x_t[j], the row in B (or, stored, at kst)
-  __device__ __forceinline__ static void contract(const double (&x)[NS], const double (&B)[PRE ? 1 : NQ],
-                                                  const double* __restrict__ kst, double (&acc)[NS]) {
-    double V[4][NS];
+  // The four contractions of every species on the core: the lane's half as in
+  // the 32-node kernels, then the other half's columns by the sum that its
+  // node next to this half has (node 32 for the lower half, 31 for the upper)
+  __device__ __forceinline__ static void contract(const double (&C)[kCore], const double (&a)[NS],
+                                                  const double (&b)[NS], const double (&c)[NS], const double (&d)[NS],
+                                                  double (&eN)[NS], double (&oN)[NS], double (&aP)[NS],
+                                                  double (&eP)[NS]) {
+    double B[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) B[j] = C[j];
+    pairk::core_contract<NS>(B, C[16], a, b, c, d, eN, oN, aP, eP);
+    const int from = (threadIdx.x & 32) ? 31 * 4 : 32 * 4;
+    auto other = [&](double v) {
+      return mk64((uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)lo32(v)),
+                  (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)hi32(v)));
+    };
+    double z[4][NS];
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
-      quarters(x[t], V[0][t], V[1][t], V[2][t], V[3][t]);
-      acc[t] = 0.0;
+      z[0][t] = other(eN[t]);
+      z[1][t] = other(oN[t]);
+      z[2][t] = other(aP[t]);
+      z[3][t] = other(eP[t]);
     }
-    static_for<0, NQ / 4>([&](auto jj) __attribute__((always_inline)) {
-      constexpr int j = 4 * decltype(jj)::value;
-      if constexpr (PRE)
-        Fmac1x4<NS>::template run<j % 16>(acc, V[j / 16], kst[j * NQ], kst[(j + 1) * NQ], kst[(j + 2) * NQ],
-                                          kst[(j + 3) * NQ]);
-      else
-        Fmac1x4<NS>::template run<j % 16>(acc, V[j / 16], B[j], B[j + 1], B[j + 2], B[j + 3]);
-    });
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      eN[t] = __builtin_fma(C[17], z[0][t], eN[t]);
+      oN[t] = __builtin_fma(C[17], z[1][t], oN[t]);
+      aP[t] = __builtin_fma(C[17], z[2][t], aP[t]);
+      eP[t] = __builtin_fma(C[17], z[3][t], eP[t]);
+    }
   }
 
   // settle() is called once the point's inputs are loaded (work-queue hook)
@@ -212,8 +224,8 @@ struct PointSolver64 {
     const int64_t base = p * (int64_t)(NS * NQ);
     const double rho = in_global(a->rho11)[p];
     const bool fixedT = a->prm.fixed_matter && a->T_fixed;
-    // this lane's column of the stored core
-    double* __restrict__ kst = PRE ? a->kstore + p * (int64_t)(NQ * NQ) + lane : nullptr;
+    // this lane's entries of the stored core
+    double* __restrict__ kst = PRE ? a->kstore + p * (int64_t)(kCore * NQ) + lane : nullptr;
 
     double D[NS], I[NS];
 #pragma unroll
@@ -319,8 +331,9 @@ struct PointSolver64 {
         }
         dsig = dtau * sig;
       }
-      // row q of the core and the node's factors, or the splits in LDS
-      double B[COUPLED && !PRE ? NQ : 1];
+      // the lane's entries of the core and the node's factors, or the splits
+      // in LDS
+      double C[COUPLED && !PRE ? kCore : 1];
       double gq = 1.0, rgq = 1.0, hq = 1.0;
       bool direct = false;  // uniform
       if constexpr (COUPLED) {
@@ -333,17 +346,16 @@ struct PointSolver64 {
           rgq = ldexp(xs.P, xs.n - c);
           hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
           const double ht = gq * gq, rht = rgq * rgq;
-          double H[4], RH[4];
-          quarters(ht, H[0], H[1], H[2], H[3]);
-          quarters(rht, RH[0], RH[1], RH[2], RH[3]);
-          // of the two orientations h_j / h_q and h_q / h_j the smaller is B2
-          // (the other is its reciprocal, or overflows to +inf)
-          static_for<0, NQ>([&](auto jj) __attribute__((always_inline)) {
-            constexpr int j = decltype(jj)::value;
-            const double b = min_f64(row_bcast<j % 16>(H[j / 16]) * rht, ht * row_bcast<j % 16>(RH[j / 16]));
+          double B[16], kx;
+          pairk::direct_row_regs(ht, rht, B, kx);
+          const double up = readlane(ht, 32) * rht, down = ht * readlane(rht, 31);
+          const double core[2] = {kx, (q & 32) ? down : up};
+#pragma unroll
+          for (int j = 0; j < kCore; ++j) {
+            const double b = j < 16 ? B[j < 16 ? j : 0] : core[j < 16 ? 0 : j - 16];
             if constexpr (PRE) kst[j * NQ] = b;
-            else B[j] = b;
-          });
+            else C[j] = b;
+          }
         } else {
           const double R2 = xs.R * xs.R;
           S.colPR[q][0] = xs.P;
@@ -369,23 +381,26 @@ struct PointSolver64 {
         for (int t = 0; t < NS; ++t) etaN[t] = outN[t] = annP[t] = etaP[t] = 0.0;
         if constexpr (COUPLED) {
           if (direct) {
-            if constexpr (!PRE) {
+            double c[kCore];
 #pragma unroll
-              for (int j = 0; j < NQ; ++j) asm volatile("" : "+v"(B[j]));
+            for (int j = 0; j < kCore; ++j) {
+              if constexpr (PRE) {
+                c[j] = kst[j * NQ];
+              } else {
+                asm volatile("" : "+v"(C[j]));
+                c[j] = C[j];
+              }
             }
-            double x[NS];
+            double xg[NS], yg[NS], xv[NS], hy[NS];
 #pragma unroll
-            for (int t = 0; t < NS; ++t) x[t] = w2eq * D[t] * rgq;
-            contract(x, B, kst, etaN);
-#pragma unroll
-            for (int t = 0; t < NS; ++t) x[t] = __builtin_fma(-w2eq, D[t], w2eq) * gq;
-            contract(x, B, kst, outN);
-#pragma unroll
-            for (int t = 0; t < NS; ++t) x[t] = w2eq * D[pair_partner<NS>(t)];
-            contract(x, B, kst, annP);
-#pragma unroll
-            for (int t = 0; t < NS; ++t) x[t] = hq * __builtin_fma(-w2eq, D[pair_partner<NS>(t)], w2eq);
-            contract(x, B, kst, etaP);
+            for (int t = 0; t < NS; ++t) {
+              xv[t] = w2eq * D[t];
+              const double yv = __builtin_fma(-w2eq, D[t], w2eq);
+              xg[t] = xv[t] * rgq;
+              yg[t] = yv * gq;
+              hy[t] = hq * yv;
+            }
+            contract(c, xg, yg, xv, hy, etaN, outN, annP, etaP);
           } else {
 #pragma unroll
             for (int t = 0; t < NS; ++t) S.X[t][q] = w2eq * D[t];

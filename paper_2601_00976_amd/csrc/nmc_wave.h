@@ -50,6 +50,11 @@ __device__ __forceinline__ void swap16(double v, double& first, double& second) 
   second = mk64(a[1], b[1]);
 }
 
+// the value of lane i, uniform
+__device__ __forceinline__ double readlane(double v, int i) {
+  return mk64((uint32_t)__builtin_amdgcn_readlane((int)lo32(v), i), (uint32_t)__builtin_amdgcn_readlane((int)hi32(v), i));
+}
+
 // the value of lane 31 - i of this 32-lane half (ds_swizzle: no LDS memory)
 __device__ __forceinline__ double mirror32(double v) {
   return mk64((uint32_t)__builtin_amdgcn_ds_swizzle((int)lo32(v), 0x7C1F),
@@ -399,72 +404,6 @@ struct Fmac4<3> {
         : "+v"(a1[0]), "+v"(a1[1]), "+v"(a1[2]), "+v"(a2[0]), "+v"(a2[1]), "+v"(a2[2])
         : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(m10), "v"(m11), "v"(m12), "v"(m13), "v"(m20), "v"(m21), "v"(m22),
           "v"(m23), "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
-  }
-};
-
-// Four columns of one contraction for every species:
-// acc[t] += bcast(x[t], L0 + jj) * m[jj], jj = 0..3 (s_nop as above).
-template <int NS>
-struct Fmac1x4;
-
-template <>
-struct Fmac1x4<1> {
-  template <int L0>
-  __device__ __forceinline__ static void run(double (&a)[1], const double (&x)[1], double m0, double m1, double m2,
-                                             double m3) {
-    asm volatile(
-        "s_nop 1\n"
-        "v_fmac_f64_dpp %0, %1, %2 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %1, %3 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %1, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %1, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n"
-        : "+v"(a[0])
-        : "v"(x[0]), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
-  }
-};
-
-template <>
-struct Fmac1x4<2> {
-  template <int L0>
-  __device__ __forceinline__ static void run(double (&a)[2], const double (&x)[2], double m0, double m1, double m2,
-                                             double m3) {
-    asm volatile(
-        "s_nop 1\n"
-        "v_fmac_f64_dpp %0, %2, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %3, %4 row_newbcast:%8 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %2, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %3, %5 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %2, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %3, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %2, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %3, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
-        : "+v"(a[0]), "+v"(a[1])
-        : "v"(x[0]), "v"(x[1]), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
-  }
-};
-
-template <>
-struct Fmac1x4<3> {
-  template <int L0>
-  __device__ __forceinline__ static void run(double (&a)[3], const double (&x)[3], double m0, double m1, double m2,
-                                             double m3) {
-    asm volatile(
-        "s_nop 1\n"
-        "v_fmac_f64_dpp %0, %3, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %4, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %2, %5, %6 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %3, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %4, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %2, %5, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %3, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %2, %5, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %0, %3, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %1, %4, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n"
-        "v_fmac_f64_dpp %2, %5, %9 row_newbcast:%13 row_mask:0xf bank_mask:0xf\n"
-        : "+v"(a[0]), "+v"(a[1]), "+v"(a[2])
-        : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(m0), "v"(m1), "v"(m2), "v"(m3), "i"(L0), "i"(L0 + 1), "i"(L0 + 2),
-          "i"(L0 + 3));
   }
 };
 
