@@ -105,9 +105,11 @@ template <int NS, bool COUPLED, bool PHI1>
 struct VPairSolver {
   static constexpr int NQ = NQP;
   static constexpr int NM = 4 * NS;            // owned moments per lane
-  // the inner Anderson history in registers (the coupled isotropic kernel
-  // runs one wave per SIMD and has the registers to spare); otherwise in LDS
-  static constexpr bool HREG = COUPLED && !PHI1;
+  // the inner Anderson history in registers (the coupled kernel runs one wave
+  // per SIMD, which leaves them to spare and no other wave to cover LDS
+  // reads: 16384 points 784 us against 899 us from LDS, 32768 points with the
+  // linear-order terms 2548 against 2769 us); otherwise in LDS
+  static constexpr bool HREG = COUPLED;
 
   // matter right-hand side q(M, y) of Eq. implicitFluidNodal from the
   // integrals X of the current moments
