@@ -59,7 +59,7 @@ constexpr int kCore = 18;
 template <int NS>
 struct Lds64 {
   ModelLdsN<NQ64> m;
-  double hist[4][2 * NS][kLanes];  // Anderson history per owned moment: Q_prev, F_prev, dQ_old, dF_old
+  double hist[2][2 * NS][kLanes];  // Anderson history per owned moment: Q_prev, F_prev
   double colPR[kLanes][2];         // per node: P, R of the exponent split at the current T
   double colGE[kLanes][2];         // per node: G = exp(-2 e / T), W e
   int coln[kLanes];                // per node: integer part n of the split
@@ -370,6 +370,7 @@ struct PointSolver64 {
       const double w2q = mt.w2[q], w2eq = w2q * epsq;
       const double Aeq = S.An * epsq, Apq = S.Ap * epsq;
       double G11 = 0.0;
+      double H[2][2 * NS];  // Anderson history: dQ_old, dF_old per owned moment (the previous Q and F in LDS)
       bool conv = false;
       const int m_inner = held(a->prm.m_inner), max_inner = held(a->prm.max_inner);
       const double tol2 = held(a->tol_inner2);
@@ -428,12 +429,12 @@ struct PointSolver64 {
         double Xn[2 * NS];
         if (mem == 1) {
           // clear the older difference column (weighted zero at the second
-          // iterate), so that no stale LDS word enters that product
+          // iterate), so that no stale value enters that product
 #pragma unroll
           for (int x = 0; x < 2 * NS; ++x) {
             Xn[x] = Qx[x];
-            S.hist[2][x][lane] = 0.0;
-            S.hist[3][x][lane] = 0.0;
+            H[0][x] = 0.0;
+            H[1][x] = 0.0;
           }
         } else {
           const double use1 = (mem == 3) ? 1.0 : 0.0;
@@ -443,7 +444,7 @@ struct PointSolver64 {
           for (int x = 0; x < 2 * NS; ++x) {
             dQ2[x] = Qx[x] - S.hist[0][x][lane];
             dF2[x] = Fx[x] - S.hist[1][x][lane];
-            const double dF1 = use1 * S.hist[3][x][lane];
+            const double dF1 = use1 * H[1][x];
             v4[0] += dF1 * dF2[x];
             v4[1] += dF2[x] * dF2[x];
             v4[2] += dF1 * Fx[x];
@@ -456,9 +457,9 @@ struct PointSolver64 {
           anderson2(mem == 3, G11, G12, G22, b1, b2, g1, g2);
 #pragma unroll
           for (int x = 0; x < 2 * NS; ++x) {
-            Xn[x] = Qx[x] - g2 * dQ2[x] - g1 * S.hist[2][x][lane];
-            S.hist[2][x][lane] = dQ2[x];
-            S.hist[3][x][lane] = dF2[x];
+            Xn[x] = Qx[x] - g2 * dQ2[x] - g1 * H[0][x];
+            H[0][x] = dQ2[x];
+            H[1][x] = dF2[x];
           }
           G11 = G22;
         }

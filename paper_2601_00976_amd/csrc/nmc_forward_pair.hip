@@ -21,9 +21,10 @@
 //     shares LDS with the Anderson history, which is dead between inner loops).
 // An inner iteration is ~690 instructions, 216 of them the multiply-adds of
 // the rates (with the whole rows of 32 columns and the vectors redistributed
-// ~890, 384 of them): 65536 points of the radial profile, two steps, 1189 us
-// (1459 us), 4095 points 78 us (91 us).  Instruction issue at two waves per
-// SIMD bounds large batches.
+// ~890, 384 of them): 65536 points of the radial profile, two steps, 1180 us
+// (1459 us).  Half of the Anderson history stays in registers, as far as two
+// waves per SIMD leave room: 1149 us (4095 points 78 us, 82 us with all of it
+// in LDS).  Instruction issue at two waves per SIMD bounds large batches.
 // The row sums take their factors A e_q in the Q step.
 //
 // Both halves run one instruction stream.  A half whose point has finished
@@ -45,7 +46,7 @@ struct PairLds {
   SplitExp E[2];                   // per point: exponent splits at its current temperature
   union {
     struct {
-      double hist[4][2 * NS][kLanes];  // Anderson history per lane and owned moment: Q_prev, F_prev, dQ_old, dF_old
+      double hist[2][2 * NS][kLanes];  // Anderson history per lane and owned moment: Q_prev, F_prev
       double fac[2][NS][kLanes];       // projected equilibrium: 1 / sqrt(o) and o per species (o = D / (1 - D))
     };
     double tile[2][NQP][NQP];        // per point, signed pair factors: [j][q] = +b if j > q, else -b
@@ -269,6 +270,7 @@ struct PairSolver {
       const double Aeq = pt.An * epsq, Apq = pt.Ap * epsq, Apqh = Apq * hq;
 
       double G11 = 0.0;
+      double H[2][2 * NS];  // Anderson history: dQ_old, dF_old per owned moment (the previous Q and F in LDS)
       // the reference norm of this inner loop (constant within the loop: a
       // converged loop sets the next loop's and ends)
       const double dref0 = dref;
@@ -348,13 +350,13 @@ struct PairSolver {
         double Xn[2 * NS];
         if (mem == 1) {
           // the older difference column is weighted zero at the second
-          // iterate: clear it, so that no stale LDS word (a NaN pattern left
-          // by another point or kernel) enters that product
+          // iterate: clear it, so that no stale value (a NaN pattern) enters
+          // that product
 #pragma unroll
           for (int x = 0; x < 2 * NS; ++x) {
             Xn[x] = Qx[x];
-            S.u.hist[2][x][lane] = 0.0;
-            S.u.hist[3][x][lane] = 0.0;
+            H[0][x] = 0.0;
+            H[1][x] = 0.0;
           }
         } else {
           double dQ2[2 * NS], dF2[2 * NS];
@@ -363,7 +365,7 @@ struct PairSolver {
           for (int x = 0; x < 2 * NS; ++x) {
             dQ2[x] = Qx[x] - S.u.hist[0][x][lane];
             dF2[x] = Fx[x] - S.u.hist[1][x][lane];
-            const double dF1 = S.u.hist[3][x][lane];
+            const double dF1 = H[1][x];
             v4[0] += dF1 * dF2[x];
             v4[1] += dF2[x] * dF2[x];
             v4[2] += dF1 * Fx[x];
@@ -375,9 +377,9 @@ struct PairSolver {
           anderson2(mem == 3, G11, gs[0], gs[1], gs[2], gs[3], g1, g2);
 #pragma unroll
           for (int x = 0; x < 2 * NS; ++x) {
-            Xn[x] = Qx[x] - g2 * dQ2[x] - g1 * S.u.hist[2][x][lane];
-            S.u.hist[2][x][lane] = dQ2[x];
-            S.u.hist[3][x][lane] = dF2[x];
+            Xn[x] = Qx[x] - g2 * dQ2[x] - g1 * H[0][x];
+            H[0][x] = dQ2[x];
+            H[1][x] = dF2[x];
           }
           G11 = gs[1];
         }
