@@ -35,25 +35,30 @@ __device__ __forceinline__ void closure_terms(double D, const double (&I)[3], co
   closure_from_norm(D, I, v, Imag, [&] { return Imag > 0.0 ? rcp_nr(Imag) : 0.0; }, vI, vK);
 }
 
+// sqrt(s) and 1 / sqrt(s) of a positive s from one reciprocal square root
+// estimate y, refined by two coupled Newton steps on (g, h) -> (sqrt(s),
+// 1 / (2 sqrt(s))) and a last correction of g.
+__device__ __forceinline__ void sqrt_pair(double s, double& root, double& inv) {
+  const double y = __builtin_amdgcn_rsq(s);
+  double g = s * y, hh = 0.5 * y;
+  double e = __builtin_fma(-g, hh, 0.5);
+  g = __builtin_fma(g, e, g);
+  hh = __builtin_fma(hh, e, hh);
+  e = __builtin_fma(-g, hh, 0.5);
+  g = __builtin_fma(g, e, g);
+  hh = __builtin_fma(hh, e, hh);
+  root = __builtin_fma(__builtin_fma(-g, g, s), hh, g);
+  inv = 2.0 * hh;
+}
+
 // The same for moments of order one (a flux whose squared norm is at least
-// 2^-1000, else the square root above): |I| and 1 / |I| from one reciprocal
-// square root estimate y of s = |I|^2, refined by two coupled Newton steps on
-// (g, h) -> (sqrt(s), 1 / (2 sqrt(s))) and a last correction of g.
+// 2^-1000, else the square root above).
 __device__ __forceinline__ void closure_terms_unit(double D, const double (&I)[3], const double (&v)[3], double& vI,
                                                    double (&vK)[3]) {
   const double s = I[0] * I[0] + I[1] * I[1] + I[2] * I[2];
   double Imag, rI;
   if (s >= 0x1p-1000 && s <= 0x1p+1000) {
-    const double y = __builtin_amdgcn_rsq(s);
-    double g = s * y, hh = 0.5 * y;
-    double e = __builtin_fma(-g, hh, 0.5);
-    g = __builtin_fma(g, e, g);
-    hh = __builtin_fma(hh, e, hh);
-    e = __builtin_fma(-g, hh, 0.5);
-    g = __builtin_fma(g, e, g);
-    hh = __builtin_fma(hh, e, hh);
-    Imag = __builtin_fma(__builtin_fma(-g, g, s), hh, g);
-    rI = 2.0 * hh;
+    sqrt_pair(s, Imag, rI);
   } else {
     Imag = sqrt(s);
     rI = Imag > 0.0 ? rcp_nr(Imag) : 0.0;
@@ -65,20 +70,25 @@ __device__ __forceinline__ void closure_terms_unit(double D, const double (&I)[3
 // one node: a divergent `if` per species makes each species' square root and
 // reciprocals a block of its own, and at one wave per SIMD their dependent
 // chains then run one after the other; as selects in one block they overlap
-// (O(v) solve of 16384 points 945 -> 889 us,
-// most of it from the integrals of the matter update).
+// (O(v) solve of 16384 points 945 -> 889 us, most of it from the integrals of
+// the matter update).  |I| and 1 / |I| come from one estimate, which takes
+// half the chain of a square root and a reciprocal after it (2000 points 185.3
+// -> 181.4 us, 32768 points with the linear-order terms 2548 -> 2515 us; 16384
+// points without them stay at 782 us).
 struct Minerbo {
   double a, b;        // K_ij = D (a delta_ij + b n_i n_j)
   double n0, n1, n2;  // I / |I|, 0 without flux
 };
 __device__ __forceinline__ Minerbo minerbo_flat(double D, const double (&I)[3]) {
-  const double Imag = sqrt(I[0] * I[0] + I[1] * I[1] + I[2] * I[2]);
+  const double s = I[0] * I[0] + I[1] * I[1] + I[2] * I[2];
+  double Imag, r;
+  const bool some = s > 0.0;
+  sqrt_pair(some ? s : 1.0, Imag, r);
   // Imag < D keeps D normal where its reciprocal is taken (closure_from_norm)
-  const bool some = Imag > 0.0, inside = some && Imag < D;
+  const bool inside = some && Imag < D;
   const double hr = Imag * rcp_nr(inside ? D : 1.0);
   const double h = inside ? hr : (some ? 1.0 : 0.0);
   const double psi = 1.0 / 3.0 + (2.0 / 15.0) * (3.0 - h + 3.0 * h * h) * h * h;
-  const double r = rcp_nr(some ? Imag : 1.0);
   const double rI = some ? r : 0.0;
   Minerbo m;
   m.a = 0.5 * (1.0 - psi);
