@@ -30,24 +30,25 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 COPY_BYTES = 1 << 28  # 256 MiB calibration copy
+# by the leading part of the kernel's name (a last template argument tells queued from direct launches)
 KERNELS = {
-    "fwd_pair_kernel<3, true, false>": ("fwd_pair_kernel_nq32_ns3", "radial profile, 2^16 points, 32 nodes, step 1"),
-    "fwd_pair_kernel<3, true, true>": ("fwd_pair_kernel_nq32_ns3_proj", "radial profile, 2^16 points, 32 nodes, "
+    "fwd_pair_kernel<3, true, false,": ("fwd_pair_kernel_nq32_ns3", "radial profile, 2^16 points, 32 nodes, step 1"),
+    "fwd_pair_kernel<3, true, true,": ("fwd_pair_kernel_nq32_ns3_proj", "radial profile, 2^16 points, 32 nodes, "
                                        "step 1, projected equilibrium"),
-    "fwd_kernel<3, 32, true, 2>": ("fwd_kernel_nq32_ns3", "radial profile, 2^16 points, 32 nodes, step 1, "
+    "fwd_kernel<3, 32, true, 2,": ("fwd_kernel_nq32_ns3", "radial profile, 2^16 points, 32 nodes, step 1, "
                                    "one point per wavefront"),
     "adj_kernel<3>": ("adj_kernel_nq32_ns3", "radial profile, 2^16 points, 32 nodes, step 1"),
-    "fwd_v_kernel<3, true, false>": ("fwd_v_kernel_nq32_ns3", "moving radial profile (O(v) solve), 2^16 points, "
+    "fwd_v_kernel<3, true, false,": ("fwd_v_kernel_nq32_ns3", "moving radial profile (O(v) solve), 2^16 points, "
                                      "32 nodes, step 1, one point per wavefront"),
-    "fwd_vpair_kernel<3, true, false>": ("fwd_vpair_kernel_nq32_ns3", "moving radial profile (O(v) solve), 2^16 "
+    "fwd_vpair_kernel<3, true, false,": ("fwd_vpair_kernel_nq32_ns3", "moving radial profile (O(v) solve), 2^16 "
                                   "points, 32 nodes, step 1, two points per wavefront"),
-    "fwd_vpair_kernel<3, true, true>": ("fwd_vpair_kernel_nq32_ns3_phi1", "moving radial profile (O(v) solve "
+    "fwd_vpair_kernel<3, true, true,": ("fwd_vpair_kernel_nq32_ns3_phi1", "moving radial profile (O(v) solve "
                                         "with the Phi_1 corrections), 2^16 points, 32 nodes, step 1, two points "
                                         "per wavefront"),
     "c2p_kernel": ("c2p_kernel_nq32_ns3", "primitive recovery of every node of the moving radial profile, "
                    "2^16 points x 3 species x 32 nodes"),
-    "fwd64_kernel<3, true, false>": ("fwd64_kernel_nq64_ns3", "radial profile, 2^18 points, 64 nodes, step 1"),
-    "fwd64_kernel<3, true, true>": ("fwd64_kernel_nq64_ns3_hbm",
+    "fwd64_kernel<3, true, false,": ("fwd64_kernel_nq64_ns3", "radial profile, 2^18 points, 64 nodes, step 1"),
+    "fwd64_kernel<3, true, true,": ("fwd64_kernel_nq64_ns3_hbm",
                                     "radial profile, 2^18 points, 64 nodes, step 1, kernels in HBM"),
 }
 
@@ -161,7 +162,7 @@ def summarize(fetch_db, write_db):
         total = (vf * sf + vw * sw) * 1024.0
         path = os.path.join(ROOT, "profiles", f"traffic_{tag}.txt")
         with open(path, "w") as o:
-            o.write(f"# HBM traffic of {key} ({what})\n")
+            o.write(f"# HBM traffic of {key.rstrip(',') + ('>' if key.endswith(',') else '')} ({what})\n")
             o.write("# commands (GPU host, from the repository root; source_hash = code-only hash of csrc/, "
                     "see autotune.kernel_source_hash):\n")
             o.write("#   cd /tmp && export TMPDIR=/tmp\n")
