@@ -707,7 +707,7 @@ __global__ __launch_bounds__(kLanes, COUPLED ? 1 : 2) void fwd_vpair_kernel(FwdV
 
 template <int NS, bool COUPLED, bool PHI1>
 hipError_t launch_vpair_t(FwdVArgs a, const nmc_launch& L, int num_cu, hipStream_t s) {
-  const LaunchPlan lp = plan_launch(L, (a.P + 1) / 2, COUPLED ? 4 : 8, num_cu);
+  const LaunchPlan lp = plan_launch(L, (a.P + 1) / 2, COUPLED ? 4 : 8, num_cu, COUPLED ? kDirectRoundsV : kDirectRounds);
   a.chunk = lp.chunk;
   auto kern = fwd_vpair_kernel<NS, COUPLED, PHI1, false>;
   if (lp.queue) {

@@ -125,7 +125,7 @@ struct LaunchPlan {
 
 // Plan of a solve kernel that keeps `per_cu` work-groups resident per compute
 // unit.  A persistent launch takes its units from the work queue once the
-// batch is longer than kDirectRounds rounds of the resident work-groups.
+// batch is longer than `rounds` rounds of the resident work-groups.
 // Below that every unit gets a work-group of its own and the hardware
 // dispatcher is the queue: it starts the next unit wherever one ends, with no
 // counters to reset and no ticket to wait for (a caller that limits
@@ -133,15 +133,21 @@ struct LaunchPlan {
 // against queue: static solve of 8192 points (2 rounds) 97 against 107 us,
 // 65536 points (16 rounds) 515 against 525 us, 131072 points (32 rounds) 1035
 // against 1024 us; 64 nodes, 131072 points (64 rounds) 4.90 against 4.84 ms.
+// The coupled O(v) kernel, alone on its SIMD, has no other wave to cover the
+// start of a work-group (model tables, inputs), and a queue's waves load the
+// tables once: 4096 points (2 rounds) 226 against 233 us, 8192 points (4
+// rounds) 410 against 404, 16384 points 777 against 756; with linear-order
+// kernels 8192 points 662 against 675, 32768 points 2510 against 2467.
 // A grab takes at most 1/64 of a work-group's even share of the batch,
 // whatever chunk allows, so that no work-group is left with several units
 // when the others are done (4 pairs per grab: 4095 points 320 us, one: 95 us).
-constexpr int64_t kDirectRounds = 16;
-inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, int num_cu) {
+constexpr int64_t kDirectRounds = 16, kDirectRoundsV = 4;
+inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, int num_cu,
+                              int64_t rounds = kDirectRounds) {
   LaunchPlan p = {0, L.chunk, false};
   if (L.persistent) {
     const int64_t slots = (int64_t)per_cu * num_cu;
-    p.queue = L.blocks_per_cu > 0 || units > kDirectRounds * slots;
+    p.queue = L.blocks_per_cu > 0 || units > rounds * slots;
     const int64_t share = p.queue ? units / (64 * slots) : 1;
     if (p.chunk > share) p.chunk = share > 1 ? (int)share : 1;
   }

@@ -34,7 +34,7 @@ def test_direct_and_queued_launches_bitwise(n_elem, P):
             assert torch.equal(ref[k], got[k]), (launch, k)
 
 
-@pytest.mark.parametrize("P", [1, 2 * 16 * 4 * 256 - 1, 2 * 16 * 4 * 256 + 1])
+@pytest.mark.parametrize("P", [1, 2 * 4 * 4 * 256 - 1, 2 * 4 * 4 * 256 + 1])
 def test_direct_and_queued_launches_bitwise_v(P):
     import torch
     print(f"[case] launch plan, O(v), P={P}", flush=True)
