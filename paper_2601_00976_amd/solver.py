@@ -380,7 +380,9 @@ class NMCSolve(torch.autograd.Function):
         ctx.set_materialize_grads(False)
         out = solve(model, params, dtau, D0, I0, rho11, ye0, e0, theta)
         ctx.model, ctx.dtau, ctx.params = model, dtau, params
-        ctx.out = out
+        # detached aliases of what is returned: the outputs themselves will hold this node, and the two would keep each
+        # other, and every pass's moments, alive for good
+        ctx.out = {**out, **{k: out[k].detach() for k in ("D", "I", "ye", "e")}}
         ctx.save_for_backward(theta, rho11)
         return out["D"], out["I"], out["ye"], out["e"], e0 - out["e"], out["ye"] - ye0
 
