@@ -21,9 +21,9 @@
 // instead of 64 and the vector's redistribution.  g and 1 / g are scaled by
 // 2^+-c, c the middle of the point's exponent range.  Instruction issue at two
 // waves per SIMD and, for small batches, the dependent reductions bound it:
-// 131072 points of the radial profile take 1.73 ms (3.10 ms with rows of 64
+// 131072 points of the radial profile take 1.69 ms (3.10 ms with rows of 64
 // entries in registers, 4.84 ms with every column regenerated from LDS in
-// every inner iteration), 1001 points 72 us (124 us, 233 us).
+// every inner iteration), 1001 points 71 us (124 us, 233 us).
 //
 // Where the grid spans more than kDirectBits64 powers of two in g (T below
 // ~0.22 MeV) the lanes instead regenerate their rows column by column in every
@@ -296,19 +296,22 @@ struct PointSolver64 {
       const_ptr<DevModel> md = scalar_ptr(a->mdl);
       const int q = opaque(q0);
       // ---- ComputeOpacities(y^[k]) --------------------------------------
+      // (refined reciprocals as at 32 nodes: 131072 points 1732 -> 1689 us, 1001
+      // points 72.2 -> 70.8 us; the series logarithm issues less but its chain is
+      // longer: 1659 and 73.4 us)
       const double r3 = S.r3;
       const double y0 = S.y[0], y1 = S.y[1];
-      const double T = fixedT ? S.T_fix : (y1 - md->eos_b * ye43(y0) * r3) / (md->eos_a * (1.0 + y0));
+      const double T = fixedT ? S.T_fix : (y1 - md->eos_b * ye43(y0) * r3) * rcp_nr(md->eos_a * (1.0 + y0));
       const double mu = (a->prm.fixed_matter && a->mu_fixed)
                             ? S.mu_fix
-                            : md->mu_a * (y0 - md->mu_ye0) * r3 + md->mu_b * log(T / md->mu_t0);
+                            : md->mu_a * (y0 - md->mu_ye0) * r3 + md->mu_b * log(T * md->inv_mu_t0);
       if (!(T > 0.0) || !(y0 >= 0.0) || !isfinite(T) || !isfinite(mu)) {
         status = NMC_STATUS_EOS_DOMAIN;
         fatal = true;
         break;
       }
       S.T_last = T;
-      const double invT = 1.0 / T;
+      const double invT = rcp_nr(T);
       // constant parts of the numerator and denominators of Q (Eqs.
       // emissivityEmAbNodal, transportOpacityNodal, implicitMomentsNodal)
       double baseD[NS], den0D[NS];
@@ -322,10 +325,15 @@ struct PointSolver64 {
 #pragma unroll
         for (int t = 0; t < NS; ++t) {
           const double chia = md->iemab[t] * emab_q;
-          const double x = (epsq - md->imusign[t] * mu) * invT;
-          const double ex = exp(-fabs(x));
-          const double r = rcp_nr(1.0 + ex);
-          const double deq = x > 0.0 ? ex * r : r;
+          double deq = 0.0;
+          if (!(NS == 3 && t == 2)) {
+            // three species are nu_e, anti-nu_e, nu_x in this order, and nu_x
+            // has no emission or absorption (chia = 0): no equilibrium
+            const double x = (epsq - md->imusign[t] * mu) * invT;
+            const double ex = exp(-fabs(x));
+            const double r = rcp_nr(1.0 + ex);
+            deq = x > 0.0 ? ex * r : r;
+          }
           baseD[t] = old(a->D0, t, md) + dtau * (chia * deq);
           den0D[t] = 1.0 + dtau * chia;
         }
