@@ -130,9 +130,10 @@ struct LaunchPlan {
 // dispatcher is the queue: it starts the next unit wherever one ends, with no
 // counters to reset and no ticket to wait for (a caller that limits
 // blocks_per_cu keeps the queue).  Measured, one unit per grab, direct
-// against queue: static solve of 8192 points (2 rounds) 97 against 107 us,
-// 65536 points (16 rounds) 515 against 525 us, 131072 points (32 rounds) 1035
-// against 1024 us; 64 nodes, 131072 points (64 rounds) 4.90 against 4.84 ms.
+// against queue: static solve of 4095 points (1 round) 74 against 80 us, 16384
+// points (4 rounds) 115 against 141 us, 65536 points (16 rounds) 398 against
+// 409 us; 64 nodes, 8192 points (4 rounds) 125 against 150 us, 32768 points (16
+// rounds) 434 against 450 us, 131072 points (64 rounds) 1726 against 1728 us.
 // The coupled O(v) kernel, alone on its SIMD, has no other wave to cover the
 // start of a work-group (model tables, inputs), and a queue's waves load the
 // tables once: 4096 points (2 rounds) 226 against 233 us, 8192 points (4
