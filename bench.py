@@ -11,7 +11,7 @@ persistent work-queue kernel over all points, output feeding the next step).
 Metric: implicit point-solves per second (points below 1e7 g/cm^3, where the
 coupling is switched off and the state passes through, are not counted).
 The JSON line also carries the roofline of the solve kernel (FP64 vector ALU
-bound; algorithmic FLOPs per launch / kernel time from HIP events captured
+bound; FLOPs performed per launch / kernel time from HIP events captured
 around each launch in the graph) and the CPU oracle timed on a bounded
 sample of the same workload.
 """
