@@ -32,7 +32,7 @@ using namespace splitk;
 template <int NS>
 struct SplitLds {
   ModelLds m;
-  ColdLds<NS> cold;
+  SplitExp E[2];             // per point: exponent splits (points too cold for scaled factors)
   double D[NS][kLanes];      // next number moments of every species
   double odds[NS][kLanes];   // projected equilibrium: o = D / (1 - D)
   alignas(16) double gram[NS][2][4];  // per species and point: Gram sums of the Anderson step
@@ -154,14 +154,14 @@ struct SplitSolver {
         if constexpr (!PROJ) {
           go = gt;
           rgo = rgt;
-          ho = hp = hq;
         }
         direct_row_regs(gt * gt, rgt * rgt, B, kx);
         if constexpr (PROJ) __syncthreads();
       } else {
-        cold_splits(S.cold, h, q, xs);
+        cold_rows<PROJ>(S.E[h], q, xs, B, kx);
       }
       if constexpr (PROJ) hp = S.odds[pa][lane];
+      else ho = hp = hq;
 
       // ---- inner loop over moments at fixed matter ------------------------
       const double w2q = mt.w2[q], w2eq = w2q * epsq;
@@ -182,11 +182,12 @@ struct SplitSolver {
         for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(B[j]));
         const double xv = w2eq * D, yv = w2eq - xv;
         double eN[1], oN[1], aP[1], eP[1];
-        if (direct) {
-          const double xp[1] = {w2eq * Dp}, hyp[1] = {hp * (w2eq - xp[0])}, xg[1] = {xv * rgo}, yg[1] = {yv * go};
+        const double xp[1] = {w2eq * Dp}, hyp[1] = {hp * (w2eq - xp[0])};
+        if (PROJ || direct) {
+          const double xg[1] = {xv * rgo}, yg[1] = {yv * go};
           core_contract<1>(B, kx, xg, yg, xp, hyp, eN, oN, aP, eP);
         } else {
-          cold_contract<NS, PROJ>(S.cold, sp, pa, h, q, xv * rgo, yv * go, xv, ho * yv, eN[0], oN[0], aP[0], eP[0]);
+          signed_split(B, kx, xv, yv, xp[0], hyp[0], eN[0], oN[0], aP[0], eP[0]);
         }
         // Q and residual of both owned moments; one reciprocal of the product
         // of the two denominators serves both

@@ -27,7 +27,7 @@ constexpr double kMuC2s = 931.49410242;  // atomic mass unit rest energy [MeV]
 template <int NS, bool PHI1>
 struct VSplitLds {
   ModelLds m;
-  ColdLds<NS> cold;
+  SplitExp E[2];                       // per point: exponent splits (points too cold for scaled factors)
   double M[NS][PHI1 ? 4 : 1][kLanes];  // next moments of every species (the flux for the linear-order terms)
   alignas(16) double gram[NS][2][4];   // per species and point: Gram sums of the Anderson step
   alignas(16) double mat[NS][2][6];    // Eulerian integrals (N, E, F_1, F_2, F_3)
@@ -203,7 +203,8 @@ struct VSplitSolver {
       // by 2^+-c and h (every wave of the work-group forms the same row),
       // where the grid spans at most kDirectBits powers of two; else the
       // splits in LDS, with the factors in the entries
-      double B[16], kx, gq = 1.0, rgq = 1.0, hq = 1.0;
+      double B[16], kx, gq = 1.0, rgq = 1.0;
+      const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
       const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
       const int lo1 = __builtin_amdgcn_readlane(xs.n, 32), hi1 = __builtin_amdgcn_readlane(xs.n, 63);
       const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
@@ -212,10 +213,9 @@ struct VSplitSolver {
       if (direct) {
         gq = ldexp(xs.R, c - xs.n);
         rgq = ldexp(xs.P, xs.n - c);
-        hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
         direct_row_regs(gq * gq, rgq * rgq, B, kx);
       } else {
-        cold_splits(S.cold, h, q, xs);
+        cold_rows<false>(S.E[h], q, xs, B, kx);
       }
 
       // ---- inner loop over moments at fixed matter (M^[k,1] = M^[k-1,*]) --
@@ -240,11 +240,12 @@ struct VSplitSolver {
         double etaN[1], outN[1], annP[1], etaP[1];
         {
           const double xv = w2eq * D, yv = w2eq - xv;
+          const double xp[1] = {w2eq * Dp}, hyp[1] = {hq * (w2eq - xp[0])};
           if (direct) {
-            const double xp[1] = {w2eq * Dp}, hyp[1] = {hq * (w2eq - xp[0])}, xg[1] = {xv * rgq}, yg[1] = {yv * gq};
+            const double xg[1] = {xv * rgq}, yg[1] = {yv * gq};
             core_contract<1>(B, kx, xg, yg, xp, hyp, etaN, outN, annP, etaP);
           } else {
-            cold_contract<NS, false>(S.cold, sp, pa, h, q, xv, yv, xv, yv, etaN[0], outN[0], annP[0], etaP[0]);
+            signed_split(B, kx, xv, yv, xp[0], hyp[0], etaN[0], outN[0], annP[0], etaP[0]);
           }
         }
         // linear-order corrections at the current iterate (see the two-point kernel)
@@ -256,11 +257,12 @@ struct VSplitSolver {
           for (int i = 0; i < 3; ++i) {
             const double x = w2eq * I[i];
             double eN[1], oN[1], aP[1], eP[1];
+            const double xp[1] = {w2eq * Ip[i]}, hxp[1] = {hq * xp[0]};
             if (direct) {
-              const double xp[1] = {w2eq * Ip[i]}, hxp[1] = {hq * xp[0]}, xg[1] = {x * rgq}, yg[1] = {x * gq};
+              const double xg[1] = {x * rgq}, yg[1] = {x * gq};
               core_contract<1>(B, kx, xg, yg, xp, hxp, eN, oN, aP, eP);
             } else {
-              cold_contract<NS, false>(S.cold, sp, pa, h, q, x, x, x, x, eN[0], oN[0], aP[0], eP[0]);
+              signed_split(B, kx, x, x, xp[0], hxp[0], eN[0], oN[0], aP[0], eP[0]);
             }
             Pc[i] = __builtin_fma(rN, gq * eN[0], -rP * (hq * eP[0]));
             Rc[i] = __builtin_fma(rN, rgq * oN[0], -rP * aP[0]);

@@ -7,14 +7,6 @@
 namespace nmc {
 namespace splitk {
 
-// What the waves of a work-group contract at points too cold for the rows in
-// registers: the nodes' exponent splits and the vectors of every species.
-template <int NS>
-struct ColdLds {
-  SplitExp E[2];             // per point
-  double X[NS][4][kLanes];   // per species: the vectors a, b, c, d (see cold_contract)
-};
-
 // sum over the species of what their waves left in LDS for point h
 template <int NS, int N, int M>
 __device__ __forceinline__ void species_sum(const double (&v)[NS][2][M], int h, double (&s)[N]) {
@@ -26,56 +18,60 @@ __device__ __forceinline__ void species_sum(const double (&v)[NS][2][M], int h, 
     for (int i = 0; i < N; ++i) s[i] += v[t][h][i];
 }
 
-// The four contractions of a species' rates (core_contract, c and d of its
-// pair partner) at a point whose grid spans too many powers of two for the
-// row: entries regenerated column by column from the splits in LDS, in a rolled
-// loop that needs few registers (such points are rare, and rows held for them
-// would cost the others a wave per SIMD).  CORE: every entry is
-// b^2 = exp(-|e_q - e_j| / T) and the factors are on the vectors; otherwise
-// the four kernels' entries without their factor A e_q e_j, every one at most
-// 1 (u = 2^(x_q - x_j) and v = 2^(x_j - x_q): the one not above 1 is b, the
-// other its reciprocal or +inf; Phi_in = min(u, v^3), Phi_out = min(u^3, v),
-// Phi_ann = min(u^2, v^2) and Phi_pro = G of the higher node).  The work-group
-// calls it together; a, b, c, d are this wave's own vectors.
-template <int NS, bool CORE>
-__device__ __forceinline__ void cold_contract(ColdLds<NS>& S, int sp, int pa, int h, int q, double a, double b,
-                                              double c, double d, double& eN, double& oN, double& aP, double& eP) {
-  const int lane = 32 * h + q;
-  S.X[sp][0][lane] = a;
-  S.X[sp][1][lane] = b;
-  S.X[sp][2][lane] = c;
-  S.X[sp][3][lane] = d;
-  __syncthreads();
-  const SplitExp& E = S.E[h];
-  const double Pq = E.P2[q], Rq = E.R2[q], Gq = E.G[q];
-  const int nq = E.n2[q];
-  eN = oN = aP = eP = 0.0;
-#pragma unroll 1
-  for (int j = 0; j < 32; ++j) {
-    const int e = nq - E.n2[j];
-    const double u = ldexp(Pq * E.R2[j], e), v = ldexp(E.P2[j] * Rq, -e);
-    const double u2 = u * u, v2 = v * v, fa = min_f64(u2, v2);
-    const double fi = CORE ? fa : min_f64(u, v2 * v), fo = CORE ? fa : min_f64(u2 * u, v);
-    const double fp = CORE ? fa : min_f64(E.G[j], Gq);
-    const int l = 32 * h + j;
-    eN = __builtin_fma(fi, S.X[sp][0][l], eN);
-    oN = __builtin_fma(fo, S.X[sp][1][l], oN);
-    aP = __builtin_fma(fa, S.X[pa][2][l], aP);
-    eP = __builtin_fma(fp, S.X[pa][3][l], eP);
-  }
-  __syncthreads();
-}
-
-// the point's splits at its current temperature (every wave writes the same)
-template <int NS>
-__device__ __forceinline__ void cold_splits(ColdLds<NS>& S, int h, int q, const ExpSplit& xs) {
-  SplitExp& E = S.E[h];
+// The lane's pair factors at a point whose grid spans too many powers of two
+// for scaled factors (direct_row_regs), from the point's exponent splits in
+// LDS: of the two orientations 2^(x_q - x_j) and 2^(x_j - x_q) the smaller is
+// b = exp(-|e_q - e_j| / (2T)).  CORE: b^2; otherwise signed as in
+// signed_contract (+b where j is the upper node).  The work-group calls it
+// together, every wave with the same values.  2048 points of 0.13-0.2 MeV take
+// 128 us so, 435 us with every column regenerated in every inner iteration.
+template <bool CORE>
+__device__ __forceinline__ void cold_rows(SplitExp& E, int q, const ExpSplit& xs, double (&B)[16], double& k) {
   E.P2[q] = xs.P;
   E.R2[q] = xs.R;
   E.n2[q] = xs.n;
-  const double R2 = xs.R * xs.R;
-  E.G[q] = ldexp(R2 * R2, -4 * xs.n);  // exp(-2 e / T)
   __syncthreads();
+  auto entry = [&](int j) {
+    const int e = xs.n - E.n2[j];
+    const double b = min_f64(ldexp(xs.P * E.R2[j], e), ldexp(E.P2[j] * xs.R, -e));
+    return CORE ? b * b : (j > q ? b : -b);
+  };
+  const int r16 = q & 16;
+#pragma unroll
+  for (int j = 0; j < 16; ++j) B[j] = entry(r16 + j);
+  k = entry(r16 ? 15 : 16);
+  __syncthreads();
+}
+
+// One column of signed_split (lane L of the 16-lane row).
+template <int L>
+__device__ __forceinline__ void signed_column(double& eN, double& oN, double& aP, double& eP, double x, double y,
+                                              double xp, double hyp, double fi, double fo, double fa) {
+  asm volatile(
+      "s_nop 1\n"
+      "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %1, %5, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %2, %6, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      "v_fmac_f64_dpp %3, %7, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n"
+      : "+v"(eN), "+v"(oN), "+v"(aP), "+v"(eP)
+      : "v"(x), "v"(y), "v"(xp), "v"(hyp), "v"(fi), "v"(fo), "v"(fa), "i"(L));
+}
+
+// signed_contract with the pair partner's vectors apart: eN = Phi_in x,
+// oN = Phi_out y, aP = Phi_ann xp, eP = Phi_ann hyp
+__device__ __forceinline__ void signed_split(const double (&B)[16], double k, double x, double y, double xp, double hyp,
+                                             double& eN, double& oN, double& aP, double& eP) {
+  eN = oN = aP = eP = 0.0;
+  static_for<0, 16>([&](auto jj) __attribute__((always_inline)) {
+    constexpr int j = decltype(jj)::value;
+    double sb = B[j];
+    asm volatile("" : "+v"(sb));  // the products are not shared between calls (48 more registers)
+    const double b2 = sb * sb, c3 = sb * b2;
+    signed_column<j>(eN, oN, aP, eP, x, y, xp, hyp, pairk::max_neg_f64(sb, c3), pairk::max_neg_f64(c3, sb), b2);
+  });
+  const double k2 = k * k, k3 = k * k2, kN = pairk::max_neg_f64(k, k3), kO = pairk::max_neg_f64(k3, k);
+  const double z0 = mirror32(eN), z1 = mirror32(oN), z2 = mirror32(aP), z3 = mirror32(eP);
+  pairk::cross_fmac(eN, oN, aP, eP, z0, z1, z2, z3, kN, kO, k2, k2);
 }
 
 }  // namespace splitk
