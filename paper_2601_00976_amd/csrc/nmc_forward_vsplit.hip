@@ -200,9 +200,9 @@ struct VSplitSolver {
       const double denD = 1.0 + ldt * chia, denI = 1.0 + ldt * (chia + sig);
 
       // row of the symmetric core with the nodes' factors g and 1 / g scaled
-      // by 2^+-c and h (every wave of the work-group forms the same row),
-      // where the grid spans at most kDirectBits powers of two; else the
-      // splits in LDS, with the factors in the entries
+      // by 2^+-c (every wave of the work-group forms the same row), where the
+      // grid spans at most kDirectBits powers of two; else from the exponent
+      // splits in LDS, signed (cold_rows)
       double B[16], kx, gq = 1.0, rgq = 1.0;
       const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
       const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
