@@ -56,7 +56,7 @@ __device__ __forceinline__ double temperature_v(const_ptr<DevModel> md, const do
 
 // The lane's contributions to the Eulerian integrals (N, E, F_1, F_2, F_3) of
 // its node's moments at velocity v
-template <int NS, bool FLAT>
+template <int NS>
 __device__ __forceinline__ void eulerian_node(const_ptr<DevModel> md, double w2, double w3, const double (&D)[NS],
                                               const double (&I)[NS][3], const double (&v)[3], double (&acc)[5]) {
 #pragma unroll
@@ -64,8 +64,7 @@ __device__ __forceinline__ void eulerian_node(const_ptr<DevModel> md, double w2,
 #pragma unroll
   for (int t = 0; t < NS; ++t) {
     double vI, vK[3];
-    if constexpr (FLAT) closure_terms_flat(D[t], I[t], v, vI, vK);
-    else closure_terms(D[t], I[t], v, vI, vK);
+    closure_terms_flat(D[t], I[t], v, vI, vK);
     acc[0] += md->ig[t] * w2 * (D[t] + vI);
     acc[1] += md->imult[t] * w3 * (D[t] + 2.0 * vI);
 #pragma unroll
@@ -74,15 +73,14 @@ __device__ __forceinline__ void eulerian_node(const_ptr<DevModel> md, double w2,
 }
 
 // Eulerian integrals (N, E, F_1, F_2, F_3) of the half's point, in every lane
-// of the half; one reduction shape for every caller, so that equal moments
-// give bitwise equal integrals.  FLAT: the closure by selects; the old state's
-// integrals keep the branching one, whose values the compiler shares with N*
-// and G*
-template <int NS, bool FLAT = true>
+// of the half; one closure and one reduction shape for every caller, so that
+// equal moments give bitwise equal integrals and a point whose moments do not
+// change keeps its matter
+template <int NS>
 __device__ __forceinline__ void eulerian_point(const_ptr<DevModel> md, double w2, double w3, const double (&D)[NS],
                                                const double (&I)[NS][3], const double (&v)[3], double (&X)[5]) {
   double acc[5], s[6];
-  eulerian_node<NS, FLAT>(md, w2, w3, D, I, v, acc);
+  eulerian_node<NS>(md, w2, w3, D, I, v, acc);
   const double vv[6] = {acc[0], acc[1], acc[2], acc[3], acc[4], 0.0};
   half_own_sums<3>(vv, s);
 #pragma unroll
@@ -223,7 +221,7 @@ struct VPairSolver {
         for (int j = 0; j < 3; ++j) Gst[t][j] = I[t][j] + vK[j];
       }
       double X0[5], n0[NS];
-      eulerian_point<NS, false>(md, mt.w2[q0], mt.w3[q0], D, I, vs, X0);
+      eulerian_point<NS>(md, mt.w2[q0], mt.w3[q0], D, I, vs, X0);
       dnorms<NS>(mt.w2[q0], D, n0);
 #pragma unroll
       for (int t = 0; t < NS; ++t) pt.dref[t] = n0[t];
