@@ -88,6 +88,7 @@ __device__ __forceinline__ double quotient(double a, double b, double rb) {
 // Tail integrals at x for k = 2, 3: sgn = +1 gives int_x^inf eps^k f, sgn = -1
 // gives int_-inf^x eps^k (1 - f).  |x - mu| / T is the distance from mu.
 __device__ __forceinline__ void tails(double x, double mu, double T, double invT, double sgn, double& t2, double& t3) {
+#pragma clang fp contract(off)
   const double z = exp(-quotient(fabs(x - mu), T, invT));
   double F0 = 0.0, F1 = 0.0, F2 = 0.0, F3 = 0.0, zp = 1.0;
 #pragma unroll
@@ -98,9 +99,11 @@ __device__ __forceinline__ void tails(double x, double mu, double T, double invT
     F2 = __builtin_fma(kTail.c[2][k], zp, F2);
     F3 = __builtin_fma(kTail.c[3][k], zp, F3);
   }
-  const double s = sgn * T;
-  t2 = T * (x * x * F0 + 2.0 * x * s * F1 + 2.0 * s * s * F2);
-  t3 = T * (x * x * x * F0 + 3.0 * x * x * s * F1 + 6.0 * x * s * s * F2 + 6.0 * s * s * s * F3);
+  // x^2 F0 + 2 x s F1 + 2 s^2 F2 and x^3 F0 + 3 x^2 s F1 + 6 x s^2 F2 + 6 s^3 F3
+  const double s = sgn * T, x2 = x * x, xs = x * s, s2 = s * s;
+  t2 = T * __builtin_fma(2.0 * s2, F2, __builtin_fma(2.0 * xs, F1, x2 * F0));
+  t3 = T * __builtin_fma(6.0 * s2 * s, F3,
+                         __builtin_fma(6.0 * xs * s, F2, __builtin_fma(3.0 * x2 * s, F1, x2 * x * F0)));
 }
 
 // This lane's share of the moments (k = 2, 3) over [a, b] of f (above = true,
@@ -108,6 +111,7 @@ __device__ __forceinline__ void tails(double x, double mu, double T, double invT
 // element holds the rest.  side = 0 or 1 within the element.
 __device__ __forceinline__ void part_share(double a, double b, double mu, double T, double invT, bool above, int side,
                                            double& m2, double& m3) {
+#pragma clang fp contract(off)
   m2 = m3 = 0.0;
   if (!(b > a)) return;
   if (b - a <= 1.5 * T) {
@@ -122,7 +126,7 @@ __device__ __forceinline__ void part_share(double a, double b, double mu, double
       const double v = quotient(ex, 1.0 + ex, rcp_nr(1.0 + ex));
       const double w = r * kGw[g] * e * e * v;
       m2 += w;
-      m3 += w * e;
+      m3 = __builtin_fma(w, e, m3);
     }
   } else {
     double t2, t3;
@@ -141,6 +145,7 @@ __device__ __forceinline__ void part_share(double a, double b, double mu, double
 // Every lane of the wave calls it (the partner exchange is a quad_perm DPP).
 __device__ __forceinline__ void projected_node(const DevModel* __restrict__ mg, int q, double T, double mu,
                                                double& D, double& C) {
+#pragma clang fp contract(off)
   const int side = q & 1;
   const double lo = mg->pelo[q], hi = mg->pehi[q];
   // parts of the element above and below mu: only the element that holds mu
@@ -160,19 +165,20 @@ __device__ __forceinline__ void projected_node(const DevModel* __restrict__ mg, 
   sB2 += dpp<0xB1>(sB2);
   sB3 += dpp<0xB1>(sB3);
   // polynomial moments of the two parts
-  const double pA2 = hi > aA ? (hi * hi * hi - aA * aA * aA) * (1.0 / 3.0) : 0.0;
-  const double pA3 = hi > aA ? (hi * hi * hi * hi - aA * aA * aA * aA) * 0.25 : 0.0;
-  const double pB2 = bB > lo ? (bB * bB * bB - lo * lo * lo) * (1.0 / 3.0) : 0.0;
-  const double pB3 = bB > lo ? (bB * bB * bB * bB - lo * lo * lo * lo) * 0.25 : 0.0;
+  const double h3 = hi * hi * hi, l3 = lo * lo * lo;
+  const double pA2 = hi > aA ? __builtin_fma(-(aA * aA), aA, h3) * (1.0 / 3.0) : 0.0;
+  const double pA3 = hi > aA ? __builtin_fma(-(aA * aA * aA), aA, h3 * hi) * 0.25 : 0.0;
+  const double pB2 = bB > lo ? __builtin_fma(bB * bB, bB, -l3) * (1.0 / 3.0) : 0.0;
+  const double pB3 = bB > lo ? __builtin_fma(bB * bB * bB, bB, -(l3 * lo)) * 0.25 : 0.0;
   const double F2 = sA2 + (pB2 - sB2), F3 = sA3 + (pB3 - sB3);
   const double C2 = (pA2 - sA2) + sB2, C3 = (pA3 - sA3) + sB3;
   // b_a = int l_a eps^2 g with l_a eps^2 = u_a eps^3 + v_a eps^2 (host tables)
   const double u1 = mg->pl[q][0], v1 = mg->pl[q][1], u2 = mg->pl[q][2], v2 = mg->pl[q][3];
-  const double bf1 = u1 * F3 + v1 * F2, bf2 = u2 * F3 + v2 * F2;
-  const double bc1 = u1 * C3 + v1 * C2, bc2 = u2 * C3 + v2 * C2;
+  const double bf1 = __builtin_fma(u1, F3, v1 * F2), bf2 = __builtin_fma(u2, F3, v2 * F2);
+  const double bc1 = __builtin_fma(u1, C3, v1 * C2), bc2 = __builtin_fma(u2, C3, v2 * C2);
   // row of the inverse mass matrix for this node
   const double r0 = mg->pinv[q][0], r1 = mg->pinv[q][1];
-  const double dt = r0 * bf1 + r1 * bf2, ct = r0 * bc1 + r1 * bc2;
+  const double dt = __builtin_fma(r0, bf1, r1 * bf2), ct = __builtin_fma(r0, bc1, r1 * bc2);
   const double rm0 = mg->prm0[q];
   const double dbar = F2 * rm0, cbar = C2 * rm0;
   // values at the nodes and the element edges (l_own at lo and hi from the host)

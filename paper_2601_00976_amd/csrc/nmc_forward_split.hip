@@ -7,19 +7,22 @@
 // instructions of one wave: 216 multiply-adds of the rates, the Anderson step
 // and the convergence sums of all species one after the other.  Here wave t of
 // the work-group holds species t of both points (lane 32 h + q: node q of the
-// point of half h) and does that species' share of all of it, ~330
+// point of half h) and does that species' share of all of it, ~340
 // instructions; the waves of a work-group run on different SIMDs.  What
-// depends on every species goes through LDS: the number moments of the pair
-// partner (contracted into this species' rates), the Gram sums of the
-// Anderson step and the convergence flags in every inner iteration (two
-// barriers), the sums of the matter right-hand side in every outer one.
-// Everything that follows from them (EOS, Anderson coefficients, matter
-// iterate, convergence) is computed by every wave from the same values with
-// the same instructions, so the waves take every branch together.
+// depends on every species goes through LDS: the residuals (whose Gram sums the
+// Anderson step needs), the number moments of the pair partner (contracted into
+// this species' rates) and the convergence flags in every inner iteration (two
+// barriers), the changes that the matter right-hand side sums in every outer
+// one.  Everything that follows from them (Gram sums, EOS, Anderson
+// coefficients, matter iterate, convergence) is computed by every wave from the
+// same values with the same instructions, so the waves take every branch
+// together.
 //
-// Same algorithm, status rules and skip rule as the two-point kernel.  The
-// sums over species add per-species sums here, so the two kernels agree to
-// rounding, not bit for bit.
+// Same algorithm, status rules and skip rule as the two-point kernel, and the
+// same bits: every sum over species adds the lane's terms in that kernel's
+// order before the lanes are summed, and the sums of one species take its
+// reduction tree.  So a point's result does not depend on the size of its
+// batch.
 #include "nmc_fdproj.h"
 #include "nmc_split.h"
 
@@ -35,14 +38,31 @@ struct SplitLds {
   SplitExp E[2];             // per point: exponent splits (points too cold for scaled factors)
   double D[NS][kLanes];      // next number moments of every species
   double odds[NS][kLanes];   // projected equilibrium: o = D / (1 - D)
-  alignas(16) double gram[NS][2][4];  // per species and point: Gram sums of the Anderson step
-  alignas(16) double mat[NS][2][2];   // sums of the matter right-hand side
+  alignas(16) double F[NS][kLanes][2];  // residuals of the moments of every species
+  double dd[NS][kLanes];     // change of the number moments since the old state
   int flag[NS][2];           // 1: converged, 2: a non-finite iterate
 };
 
 template <int NS, bool PROJ>
 struct SplitSolver {
   static constexpr int NQ = NQP;
+
+  // the lane's terms of the matter right-hand side, added over the species in
+  // the two-point kernel's order, summed over the half
+  __device__ __forceinline__ static void matter_sums(SplitLds<NS>& S, const_ptr<DevModel> md, int sp, int lane,
+                                                     double w2, double w3, double dd, double (&m)[2]) {
+    __syncthreads();  // the last changes have been read
+    S.dd[sp][lane] = dd;
+    __syncthreads();
+    double v[2] = {0.0, 0.0};
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      const double d = S.dd[t][lane];
+      v[0] += md->ig[t] * w2 * d;
+      v[1] += md->imult[t] * w3 * d;
+    }
+    half_own_sums<1>(v, m);
+  }
 
   __device__ static void solve(int64_t u, SplitLds<NS>& S) {
     const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
@@ -75,17 +95,18 @@ struct SplitSolver {
     const double r3 = cbrt(rho), K = md->kcoup / rho;
     const double An = (md->flags & NMC_NES) ? mt.theta[NQ] * rho : 0.0;
     const double Ap = (md->flags & NMC_PAIR) ? mt.theta[NQ + 1] * rho : 0.0;
-    const double gsp = md->ig[sp], dsp = md->imult[sp];
     double y0 = ye_st, y1 = e_st;
     double oq0 = 0.0, oq1 = 0.0, of0 = 0.0, of1 = 0.0, odq0 = 0.0, odq1 = 0.0, odf0 = 0.0, odf1 = 0.0;
-    // ||D^[k,1]||_W^2 of this species
-    double dref;
-    {
-      const double v[2] = {mt.w2[q0] * D * D, 0.0};
+    // ||D^[k,1]||_W^2 of this species in the lanes that spread_conv_sums gives
+    // its class, 0 in the others
+    const bool own = spread_class(lane) == 0;
+    auto norm = [&](double w2) {
+      const double v[2] = {w2 * D * D, 0.0};
       double s[2];
       half_own_sums<1>(v, s);
-      dref = s[0];
-    }
+      return own ? s[0] : 0.0;
+    };
+    double dref = norm(mt.w2[q0]);
     __syncthreads();
     double Dp = S.D[pa][lane];  // number moment of the partner
     __syncthreads();
@@ -142,7 +163,8 @@ struct SplitSolver {
       // row of the symmetric core with the nodes' factors g and 1 / g scaled
       // by 2^+-c (every wave of the work-group forms the same row), where the
       // grid spans at most kDirectBits powers of two; else from the exponent
-      // splits in LDS, signed (cold_rows)
+      // splits in LDS (cold_rows), signed beyond kSymBits: the forms and the
+      // lines between them are the two-point kernel's
       double B[16], kx;
       const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
       const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
@@ -150,16 +172,19 @@ struct SplitSolver {
       const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
       const int c = (nlo + nhi) >> 1;
       const bool direct = __builtin_amdgcn_ballot_w64(run && nhi - nlo > kDirectBits) == 0;
+      const bool sym = PROJ || __builtin_amdgcn_ballot_w64(run && nhi - nlo > kSymBits) == 0;
+      const double gt = ldexp(xs.R, c - xs.n), rgt = ldexp(xs.P, xs.n - c);
+      if constexpr (!PROJ) {
+        go = sym ? gt : 1.0;
+        rgo = sym ? rgt : 1.0;
+      }
       if (direct) {
-        const double gt = ldexp(xs.R, c - xs.n), rgt = ldexp(xs.P, xs.n - c);
-        if constexpr (!PROJ) {
-          go = gt;
-          rgo = rgt;
-        }
         direct_row_regs(gt * gt, rgt * rgt, B, kx);
         if constexpr (PROJ) __syncthreads();
+      } else if (sym) {
+        cold_rows<true>(S.E[h], q, xs, B, kx);
       } else {
-        cold_rows<PROJ>(S.E[h], q, xs, B, kx);
+        cold_rows<false>(S.E[h], q, xs, B, kx);
       }
       if constexpr (PROJ) hp = S.odds[pa][lane];
       else ho = hp = hq;
@@ -169,7 +194,10 @@ struct SplitSolver {
       const double Aeq = An * epsq, Apq = Ap * epsq;
       const double ag = Aeq * go, arg = Aeq * rgo, aph = Apq * ho;
       double G11 = 0.0;
-      double Qp[2] = {0.0, 0.0}, Fp[2] = {0.0, 0.0}, dQo[2] = {0.0, 0.0}, dFo[2] = {0.0, 0.0};  // Anderson history
+      // Anderson history: Q of this species, residuals of every species
+      double Qp[2] = {0.0, 0.0}, dQo[2] = {0.0, 0.0}, Fp[2 * NS], dFo[2 * NS];
+#pragma unroll
+      for (int x = 0; x < 2 * NS; ++x) Fp[x] = dFo[x] = 0.0;
       const double dref0 = dref;
       const bool ran = run;  // this half runs this outer iteration
       bool act = run;        // this half is still iterating the inner loop
@@ -184,7 +212,7 @@ struct SplitSolver {
         const double xv = w2eq * D, yv = w2eq - xv;
         double eN[1], oN[1], aP[1], eP[1];
         const double xp[1] = {w2eq * Dp}, hyp[1] = {hp * (w2eq - xp[0])};
-        if (PROJ || direct) {
+        if (sym) {
           const double xg[1] = {xv * rgo}, yg[1] = {yv * go};
           core_contract<1>(B, kx, xg, yg, xp, hyp, eN, oN, aP, eP);
         } else {
@@ -192,7 +220,7 @@ struct SplitSolver {
         }
         // Q and residual of both owned moments; one reciprocal of the product
         // of the two denominators serves both
-        double Q[2], F[2], Xn[2];
+        double Q[2], Xn[2];
         {
           const double eta = __builtin_fma(ag, eN[0], aph * eP[0]);
           const double chi = __builtin_fma(arg, oN[0], __builtin_fma(Apq, aP[0], eta));
@@ -200,59 +228,59 @@ struct SplitSolver {
           const double r = rcp_nr(dD * dI);
           Q[0] = __builtin_fma(dtau, eta, baseD) * (r * dI);
           Q[1] = Ist * (r * dD);
-          F[0] = Q[0] - D;
-          F[1] = Q[1] - I;
+          S.F[sp][lane][0] = Q[0] - D;
+          S.F[sp][lane][1] = Q[1] - I;
+        }
+        __syncthreads();  // and the flags and moments of the last iterate have been read
+        double F[2 * NS];  // in the two-point kernel's order: D of every species, then I
+#pragma unroll
+        for (int t = 0; t < NS; ++t) {
+          F[t] = S.F[t][lane][0];
+          F[NS + t] = S.F[t][lane][1];
         }
         // Anderson step over min(l, M_inner) residuals (difference form)
         const int mem = l < m_inner ? l : m_inner;
         if (mem == 1) {
           Xn[0] = Q[0];
           Xn[1] = Q[1];
-          dQo[0] = dQo[1] = dFo[0] = dFo[1] = 0.0;
-          __syncthreads();  // the flags and moments of the last iterate have been read
+          dQo[0] = dQo[1] = 0.0;
+#pragma unroll
+          for (int x = 0; x < 2 * NS; ++x) dFo[x] = 0.0;
         } else {
-          double dQ2[2], dF2[2], v4[4] = {0.0, 0.0, 0.0, 0.0}, own[4], gs[4];
+          double v4[4] = {0.0, 0.0, 0.0, 0.0}, gs[4];
 #pragma unroll
-          for (int x = 0; x < 2; ++x) {
-            dQ2[x] = Q[x] - Qp[x];
-            dF2[x] = F[x] - Fp[x];
-            v4[0] += dFo[x] * dF2[x];
-            v4[1] += dF2[x] * dF2[x];
+          for (int x = 0; x < 2 * NS; ++x) {
+            const double dF2 = F[x] - Fp[x];
+            v4[0] += dFo[x] * dF2;
+            v4[1] += dF2 * dF2;
             v4[2] += dFo[x] * F[x];
-            v4[3] += dF2[x] * F[x];
+            v4[3] += dF2 * F[x];
+            dFo[x] = dF2;
           }
-          half_sums4(v4, own);
-          if (q0 == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) S.gram[sp][h][i] = own[i];
-          }
-          __syncthreads();
-          species_sum<NS, 4>(S.gram, h, gs);
+          half_sums4(v4, gs);
           double g1, g2;
           anderson2(mem == 3, G11, gs[0], gs[1], gs[2], gs[3], g1, g2);
 #pragma unroll
           for (int x = 0; x < 2; ++x) {
-            Xn[x] = Q[x] - g2 * dQ2[x] - g1 * dQo[x];
-            dQo[x] = dQ2[x];
-            dFo[x] = dF2[x];
+            const double dQ2 = Q[x] - Qp[x];
+            Xn[x] = Q[x] - g2 * dQ2 - g1 * dQo[x];
+            dQo[x] = dQ2;
           }
           G11 = gs[1];
         }
+        Qp[0] = Q[0];
+        Qp[1] = Q[1];
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {
-          Qp[x] = Q[x];
-          Fp[x] = F[x];
-        }
+        for (int x = 0; x < 2 * NS; ++x) Fp[x] = F[x];
         // Algorithm innerConverged for this species (reference guarded by the
         // new norm, compared squared), and whether an iterate is non-finite
-        const uint64_t odd = __builtin_amdgcn_ballot_w64(!isfinite(Xn[0]) || !isfinite(Xn[1]));
-        const bool bad = (h ? odd >> 32 : odd & 0xffffffffull) != 0;
+        const bool bad = half_any(!isfinite(Xn[0]) || !isfinite(Xn[1]), h);
         const double dd = Xn[0] - D, di = Xn[1] - I;
-        const double vc[4] = {w2q * dd * dd, w2q * di * di, w2q * Xn[0] * Xn[0], 0.0};
-        double sc[4];
-        half_sums4(vc, sc);
-        const double dn2 = sc[2], lim = tol2 * (dref0 > dn2 ? dref0 : dn2);
-        const bool conv1 = sc[0] <= lim && sc[1] <= lim;
+        const double vm[2][1] = {{w2q * dd * dd}, {w2q * di * di}}, vn[1] = {w2q * Xn[0] * Xn[0]};
+        double dm2[1], dn2;
+        spread_conv_sums<1, 2>(vm, vn, dm2, dn2);
+        const double dref2 = dref0 > dn2 ? dref0 : dn2;
+        const bool conv1 = !half_any(!(dm2[0] <= tol2 * dref2), h);
         if (q0 == 0) S.flag[sp][h] = (conv1 ? 1 : 0) | (bad ? 2 : 0);
         S.D[sp][lane] = Xn[0];
         __syncthreads();
@@ -284,23 +312,13 @@ struct SplitSolver {
       if (run && !cvd) inner_failed = true;
       // matter right-hand side (Eq. implicitFluidNodal at v = 0), and the norm
       // of the current moments where a running point's inner loop failed
-      double yq0, yq1;
-      {
-        const double dd = D - Dst;
-        const double v[4] = {gsp * w2q * dd, dsp * mt.w3[q] * dd, w2q * D * D, 0.0};
-        double s[4], m[2];
-        half_sums4(v, s);
-        dref = (run && !cvd) ? s[2] : dref;
-        __syncthreads();  // the sums of the last outer iteration have been read
-        if (q0 == 0) {
-          S.mat[sp][h][0] = s[0];
-          S.mat[sp][h][1] = s[1];
-        }
-        __syncthreads();
-        species_sum<NS, 2>(S.mat, h, m);
-        yq0 = ye_st - K * m[0];
-        yq1 = e_st - K * m[1];
+      if (__builtin_amdgcn_ballot_w64(run && !cvd) != 0) {
+        const double n = norm(w2q);
+        dref = (run && !cvd) ? n : dref;
       }
+      double m[2];
+      matter_sums(S, md, sp, lane, w2q, mt.w3[q], D - Dst, m);
+      const double yq0 = ye_st - K * m[0], yq1 = e_st - K * m[1];
       if (a->prm.fixed_matter) {
         if (run) outer_conv = true;
         run = false;
@@ -359,17 +377,8 @@ struct SplitSolver {
     double ye_out = ye_st, e_out = e_st, T_out = T_last;
     {
       // the matter right-hand side at the final moments
-      const double dd = D - Dst;
-      const double v[2] = {gsp * mt.w2[q0] * dd, dsp * mt.w3[q0] * dd};
-      double s[2], m[2];
-      half_own_sums<1>(v, s);
-      __syncthreads();  // the loop's last sums have been read
-      if (q0 == 0) {
-        S.mat[sp][h][0] = s[0];
-        S.mat[sp][h][1] = s[1];
-      }
-      __syncthreads();
-      species_sum<NS, 2>(S.mat, h, m);
+      double m[2];
+      matter_sums(S, mo, sp, lane, mt.w2[q0], mt.w3[q0], D - Dst, m);
       if (!skip && !ao->prm.fixed_matter) {
         ye_out = ye_st - K * m[0];
         e_out = e_st - K * m[1];

@@ -18,12 +18,19 @@ __device__ __forceinline__ void species_sum(const double (&v)[NS][2][M], int h, 
     for (int i = 0; i < N; ++i) s[i] += v[t][h][i];
 }
 
+// any lane of half h of this wave
+__device__ __forceinline__ bool half_any(bool b, int h) {
+  const uint64_t m = __builtin_amdgcn_ballot_w64(b);
+  return (h ? m >> 32 : m & 0xffffffffull) != 0;
+}
+
 // The lane's pair factors at a point whose grid spans too many powers of two
 // for scaled factors (direct_row_regs), from the point's exponent splits in
 // LDS: of the two orientations 2^(x_q - x_j) and 2^(x_j - x_q) the smaller is
 // b = exp(-|e_q - e_j| / (2T)).  CORE: b^2; otherwise signed as in
-// signed_contract (+b where j is the upper node).  The work-group calls it
-// together, every wave with the same values.  2048 points of 0.13-0.2 MeV take
+// signed_contract (+b where j is the upper node); the values of
+// pair_tile_rows, the diagonal written as its callers do.  The work-group calls
+// it together, every wave with the same values.  2048 points of 0.13-0.2 MeV take
 // 128 us so, 435 us with every column regenerated in every inner iteration.
 template <bool CORE>
 __device__ __forceinline__ void cold_rows(SplitExp& E, int q, const ExpSplit& xs, double (&B)[16], double& k) {
@@ -34,7 +41,7 @@ __device__ __forceinline__ void cold_rows(SplitExp& E, int q, const ExpSplit& xs
   auto entry = [&](int j) {
     const int e = xs.n - E.n2[j];
     const double b = min_f64(ldexp(xs.P * E.R2[j], e), ldexp(E.P2[j] * xs.R, -e));
-    return CORE ? b * b : (j > q ? b : -b);
+    return CORE ? (j == q ? 1.0 : b * b) : (j > q ? b : j == q ? -1.0 : -b);
   };
   const int r16 = q & 16;
 #pragma unroll
