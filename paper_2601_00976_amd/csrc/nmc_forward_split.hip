@@ -97,14 +97,12 @@ struct SplitSolver {
     const double Ap = (md->flags & NMC_PAIR) ? mt.theta[NQ + 1] * rho : 0.0;
     double y0 = ye_st, y1 = e_st;
     double oq0 = 0.0, oq1 = 0.0, of0 = 0.0, of1 = 0.0, odq0 = 0.0, odq1 = 0.0, odf0 = 0.0, odf1 = 0.0;
-    // ||D^[k,1]||_W^2 of this species in the lanes that spread_conv_sums gives
-    // its class, 0 in the others
-    const bool own = spread_class(lane) == 0;
+    // ||D^[k,1]||_W^2 of this species
     auto norm = [&](double w2) {
       const double v[2] = {w2 * D * D, 0.0};
       double s[2];
       half_own_sums<1>(v, s);
-      return own ? s[0] : 0.0;
+      return s[0];
     };
     double dref = norm(mt.w2[q0]);
     __syncthreads();
@@ -276,11 +274,10 @@ struct SplitSolver {
         // new norm, compared squared), and whether an iterate is non-finite
         const bool bad = half_any(!isfinite(Xn[0]) || !isfinite(Xn[1]), h);
         const double dd = Xn[0] - D, di = Xn[1] - I;
-        const double vm[2][1] = {{w2q * dd * dd}, {w2q * di * di}}, vn[1] = {w2q * Xn[0] * Xn[0]};
-        double dm2[1], dn2;
-        spread_conv_sums<1, 2>(vm, vn, dm2, dn2);
-        const double dref2 = dref0 > dn2 ? dref0 : dn2;
-        const bool conv1 = !half_any(!(dm2[0] <= tol2 * dref2), h);
+        const double vm[2] = {w2q * dd * dd, w2q * di * di};
+        double dm2, dn2;
+        conv_sums(vm, w2q * Xn[0] * Xn[0], dm2, dn2);
+        const bool conv1 = !half_any(!(dm2 <= tol2 * (dref0 > dn2 ? dref0 : dn2)), h);
         if (q0 == 0) S.flag[sp][h] = (conv1 ? 1 : 0) | (bad ? 2 : 0);
         S.D[sp][lane] = Xn[0];
         __syncthreads();

@@ -421,7 +421,9 @@ struct VPairSolver {
         const int mem = l < m_inner ? l : m_inner;
         double Xn[NM];
         if constexpr (HREG) {
-          // history in registers
+          // history in registers; differences are taken from the rounded Q (not
+          // fused with its last product where that is formed beside them)
+#pragma clang fp contract(off)
           if (mem == 1) {
             // the older difference column is weighted zero at the second
             // iterate: clear it, so that no stale value enters that product
@@ -432,16 +434,20 @@ struct VPairSolver {
               H[3][x] = 0.0;
             }
           } else {
+            // per species, then over the species (the small-batch kernel, whose
+            // waves have one species each, adds in the same order)
             double v4[4] = {0.0, 0.0, 0.0, 0.0}, dF2[NM];
 #pragma unroll
-            for (int x = 0; x < NM; ++x) {
-              const double Fx = Qx[x] - cur(x);
-              dF2[x] = Fx - H[1][x];
-              const double dF1 = H[3][x];
-              v4[0] += dF1 * dF2[x];
-              v4[1] += dF2[x] * dF2[x];
-              v4[2] += dF1 * Fx;
-              v4[3] += dF2[x] * Fx;
+            for (int t = 0; t < NS; ++t) {
+              double p4[4];
+#pragma unroll
+              for (int x = 4 * t; x < 4 * t + 4; ++x) {
+                const double Fx = Qx[x] - cur(x);
+                dF2[x] = Fx - H[1][x];
+                gram_terms(x & 3, H[3][x], dF2[x], Fx, p4);
+              }
+#pragma unroll
+              for (int i = 0; i < 4; ++i) v4[i] = t ? v4[i] + p4[i] : p4[i];
             }
             double gs[4];
             half_sums4(v4, gs);
@@ -450,7 +456,7 @@ struct VPairSolver {
 #pragma unroll
             for (int x = 0; x < NM; ++x) {
               const double dQ2 = Qx[x] - H[0][x];
-              Xn[x] = Qx[x] - g2 * dQ2 - g1 * H[2][x];
+              Xn[x] = __builtin_fma(-g1, H[2][x], __builtin_fma(-g2, dQ2, Qx[x]));
               H[2][x] = dQ2;
               H[3][x] = dF2[x];
             }

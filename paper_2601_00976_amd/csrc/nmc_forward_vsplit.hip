@@ -8,11 +8,15 @@
 // of the point of half h.  A wave of the two-point kernel needs more than 256
 // registers for three species (one wave per SIMD, its dependent chains
 // exposed) and ~1120 instructions per inner iteration; a species' share fits
-// two waves per SIMD with its Anderson history in registers and takes ~450.
-// Through LDS go the moments of the pair partner, the Gram sums and the
-// convergence flags (two barriers per inner iteration) and the Eulerian
-// integrals of the matter update.  What follows from them is computed by
-// every wave from the same values, so the waves take every branch together.
+// two waves per SIMD with its Anderson history in registers and takes ~470.
+// Through LDS go the lane's terms of the Gram sums of the Anderson step, the
+// moments of the pair partner and the convergence flags (two barriers per inner
+// iteration) and the lane's terms of the Eulerian integrals of the matter
+// update.  What
+// follows from them is computed by every wave from the same values, so the
+// waves take every branch together.  Sums over species add the lane's terms in
+// the two-point kernel's order and the sums of one species take its reduction
+// tree, so the two kernels give the same bits.
 #include "nmc_closure.h"
 #include "nmc_split.h"
 
@@ -29,8 +33,8 @@ struct VSplitLds {
   ModelLds m;
   SplitExp E[2];                       // per point: exponent splits (points too cold for scaled factors)
   double M[NS][PHI1 ? 4 : 1][kLanes];  // next moments of every species (the flux for the linear-order terms)
-  alignas(16) double gram[NS][2][4];   // per species and point: Gram sums of the Anderson step
-  alignas(16) double mat[NS][2][6];    // Eulerian integrals (N, E, F_1, F_2, F_3)
+  alignas(16) double gram[NS][kLanes][4];   // the lane's terms of the Gram sums of the Anderson step
+  double X[NS][5][kLanes];                  // the lane's terms of the Eulerian integrals (N, E, F_1, F_2, F_3)
   int flag[NS][2];           // 1: converged, 2: a non-finite iterate
   struct Pt {                // state of the outer (matter) loop: every wave keeps its own copy
     double y[5], yst[5], yused[5], X0[5];
@@ -51,29 +55,29 @@ struct VSplitSolver {
   }
 
   // Eulerian integrals (N, E, F_1, F_2, F_3) of the half's point at velocity
-  // v, in every lane, and the W norm of this species' D; one form for every
-  // caller, so that equal moments give bitwise equal integrals
-  __device__ __forceinline__ static void eulerian(Lds& S, int sp, int h, int q, double g, double mult, double D,
-                                                  const double (&I)[3], const double (&v)[3], double (&X)[5],
-                                                  double& norm) {
+  // v, in every lane; one form for every caller, so that equal moments give
+  // bitwise equal integrals
+  __device__ __forceinline__ static void eulerian(Lds& S, const_ptr<DevModel> md, int sp, int lane, int q, double D,
+                                                  const double (&I)[3], const double (&v)[3], double (&X)[5]) {
     const double w2 = S.m.w2[q], w3 = S.m.w3[q];
-    double vI, vK[3], s[6];
+    double vI, vK[3];
     closure_terms_flat(D, I, v, vI, vK);
-    double acc[6];
-    acc[0] = g * w2 * (D + vI);
-    acc[1] = mult * w3 * (D + 2.0 * vI);
+    __syncthreads();  // the last terms have been read
+    S.X[sp][0][lane] = D + vI;
+    S.X[sp][1][lane] = D + 2.0 * vI;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) acc[2 + j] = mult * w3 * (I[j] + v[j] * D + vK[j]);
-    acc[5] = w2 * D * D;
-    half_own_sums<3>(acc, s);
-    norm = s[5];
-    __syncthreads();  // the last integrals have been read
-    if (q == 0) {
-#pragma unroll
-      for (int i = 0; i < 5; ++i) S.mat[sp][h][i] = s[i];
-    }
+    for (int j = 0; j < 3; ++j) S.X[sp][2 + j][lane] = I[j] + v[j] * D + vK[j];
     __syncthreads();
-    species_sum<NS, 5>(S.mat, h, X);
+    double acc[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0}, s[6];
+#pragma unroll
+    for (int t = 0; t < NS; ++t) {
+      acc[0] += md->ig[t] * w2 * S.X[t][0][lane];
+#pragma unroll
+      for (int i = 1; i < 5; ++i) acc[i] += md->imult[t] * w3 * S.X[t][i][lane];
+    }
+    half_own_sums<3>(acc, s);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) X[i] = s[i];
   }
 
   // matter right-hand side q(M, y) of Eq. implicitFluidNodal from the
@@ -126,7 +130,6 @@ struct VSplitSolver {
     const double An = (md->flags & NMC_NES) ? mt.theta[NQ] * rho : 0.0;
     const double Ap = (md->flags & NMC_PAIR) ? mt.theta[NQ + 1] * rho : 0.0;
     const double chi0 = a->chi0 ? in_global(a->chi0)[p] : md->chi_ref * rho;
-    const double gsp = md->ig[sp], dsp = md->imult[sp];
 #pragma unroll
     for (int i = 0; i < 5; ++i) {
       pt.yst[i] = pt.y[i] = pt.yused[i] = yst[i];
@@ -136,15 +139,22 @@ struct VSplitSolver {
 
     // old conserved moments N* = D* + v*.I*, G*_j = I*_j + v*^i K*_ij, the old
     // Eulerian integrals and ||D*||_W^2
-    double Nst, Gst[3], dref;
+    double Nst, Gst[3];
+    auto norm = [&](double w2) {
+      const double v[2] = {w2 * D * D, 0.0};
+      double s[2];
+      half_own_sums<1>(v, s);
+      return s[0];
+    };
+    double dref = norm(mt.w2[q0]);
     {
       const double vs[3] = {yst[2], yst[3], yst[4]};
       double vI, vK[3], X0[5];
-      closure_terms_flat(D, I, vs, vI, vK);
+      closure_terms(D, I, vs, vI, vK);
       Nst = D + vI;
 #pragma unroll
       for (int j = 0; j < 3; ++j) Gst[j] = I[j] + vK[j];
-      eulerian(S, sp, h, q0, gsp, dsp, D, I, vs, X0, dref);
+      eulerian(S, md, sp, lane, q0, D, I, vs, X0);
 #pragma unroll
       for (int i = 0; i < 5; ++i) pt.X0[i] = X0[i];
     }
@@ -202,7 +212,7 @@ struct VSplitSolver {
       // row of the symmetric core with the nodes' factors g and 1 / g scaled
       // by 2^+-c (every wave of the work-group forms the same row), where the
       // grid spans at most kDirectBits powers of two; else from the exponent
-      // splits in LDS, signed (cold_rows)
+      // splits in LDS (cold_rows), signed beyond kSymBits
       double B[16], kx, gq = 1.0, rgq = 1.0;
       const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
       const int lo0 = __builtin_amdgcn_readlane(xs.n, 0), hi0 = __builtin_amdgcn_readlane(xs.n, 31);
@@ -210,10 +220,15 @@ struct VSplitSolver {
       const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
       const int c = (nlo + nhi) >> 1;
       const bool direct = __builtin_amdgcn_ballot_w64(run && nhi - nlo > kDirectBits) == 0;
-      if (direct) {
+      const bool sym = __builtin_amdgcn_ballot_w64(run && nhi - nlo > kSymBits) == 0;
+      if (sym) {
         gq = ldexp(xs.R, c - xs.n);
         rgq = ldexp(xs.P, xs.n - c);
+      }
+      if (direct) {
         direct_row_regs(gq * gq, rgq * rgq, B, kx);
+      } else if (sym) {
+        cold_rows<true>(S.E[h], q, xs, B, kx);
       } else {
         cold_rows<false>(S.E[h], q, xs, B, kx);
       }
@@ -241,7 +256,7 @@ struct VSplitSolver {
         {
           const double xv = w2eq * D, yv = w2eq - xv;
           const double xp[1] = {w2eq * Dp}, hyp[1] = {hq * (w2eq - xp[0])};
-          if (direct) {
+          if (sym) {
             const double xg[1] = {xv * rgq}, yg[1] = {yv * gq};
             core_contract<1>(B, kx, xg, yg, xp, hyp, etaN, outN, annP, etaP);
           } else {
@@ -258,7 +273,7 @@ struct VSplitSolver {
             const double x = w2eq * I[i];
             double eN[1], oN[1], aP[1], eP[1];
             const double xp[1] = {w2eq * Ip[i]}, hxp[1] = {hq * xp[0]};
-            if (direct) {
+            if (sym) {
               const double xg[1] = {x * rgq}, yg[1] = {x * gq};
               core_contract<1>(B, kx, xg, yg, xp, hxp, eN, oN, aP, eP);
             } else {
@@ -282,13 +297,16 @@ struct VSplitSolver {
           double nD = __builtin_fma(oml, D, baseD) - lam * vI + ldt * eta;
           if constexpr (PHI1) nD = __builtin_fma(ldt, cN, nD);
           Q[0] = nD * (r * dI);
-          F[0] = Q[0] - D;
 #pragma unroll
           for (int j = 0; j < 3; ++j) {
             double nI = __builtin_fma(oml, I[j], lam * Gst[j]) - lam * vK[j];
             if constexpr (PHI1) nI = __builtin_fma(ldt, cI[j], nI);
             Q[1 + j] = nI * (r * dD);
-            F[1 + j] = Q[1 + j] - I[j];
+          }
+#pragma unroll
+          for (int x = 0; x < 4; ++x) {
+#pragma clang fp contract(off)
+            F[x] = Q[x] - (x ? I[x ? x - 1 : 0] : D);  // from the rounded Q, not fused with its last product
           }
         }
         // Anderson step over min(l, M_inner) residuals (difference form)
@@ -301,30 +319,31 @@ struct VSplitSolver {
           }
           __syncthreads();  // the flags and moments of the last iterate have been read
         } else {
-          double dQ2[4], dF2[4], v4[4] = {0.0, 0.0, 0.0, 0.0}, own[4], gs[4];
+          double p4[4], v4[4], gs[4];
 #pragma unroll
           for (int x = 0; x < 4; ++x) {
-            dQ2[x] = Q[x] - Qp[x];
-            dF2[x] = F[x] - Fp[x];
-            v4[0] += dFo[x] * dF2[x];
-            v4[1] += dF2[x] * dF2[x];
-            v4[2] += dFo[x] * F[x];
-            v4[3] += dF2[x] * F[x];
+            const double dF2 = F[x] - Fp[x];
+            gram_terms(x, dFo[x], dF2, F[x], p4);
+            dFo[x] = dF2;
           }
-          half_sums4(v4, own);
-          if (q0 == 0) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) S.gram[sp][h][i] = own[i];
-          }
+          for (int i = 0; i < 4; ++i) S.gram[sp][lane][i] = p4[i];
           __syncthreads();
-          species_sum<NS, 4>(S.gram, h, gs);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) v4[i] = S.gram[0][lane][i];
+#pragma unroll
+          for (int t = 1; t < NS; ++t)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v4[i] += S.gram[t][lane][i];
+          half_sums4(v4, gs);
           double g1, g2;
           anderson2(mem == 3, G11, gs[0], gs[1], gs[2], gs[3], g1, g2);
 #pragma unroll
           for (int x = 0; x < 4; ++x) {
-            Xn[x] = Q[x] - g2 * dQ2[x] - g1 * dQo[x];
-            dQo[x] = dQ2[x];
-            dFo[x] = dF2[x];
+#pragma clang fp contract(off)
+            const double dQ2 = Q[x] - Qp[x];
+            Xn[x] = __builtin_fma(-g1, dQo[x], __builtin_fma(-g2, dQ2, Q[x]));
+            dQo[x] = dQ2;
           }
           G11 = gs[1];
         }
@@ -338,18 +357,15 @@ struct VSplitSolver {
         bool odd = false;
 #pragma unroll
         for (int x = 0; x < 4; ++x) odd = odd || !isfinite(Xn[x]);
-        const uint64_t odds = __builtin_amdgcn_ballot_w64(odd);
-        const bool bad = (h ? odds >> 32 : odds & 0xffffffffull) != 0;
-        double vc[4], sc[4], vn[2] = {w2q * Xn[0] * Xn[0], 0.0}, sn[2];
+        const bool bad = half_any(odd, h);
+        double vm[4], dm2, dn2;
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
           const double d = Xn[x] - (x ? I[x ? x - 1 : 0] : D);
-          vc[x] = w2q * d * d;
+          vm[x] = w2q * d * d;
         }
-        half_sums4(vc, sc);
-        half_own_sums<1>(vn, sn);
-        const double lim = tol2 * (dref0 > sn[0] ? dref0 : sn[0]);
-        const bool conv1 = sc[0] <= lim && sc[1] <= lim && sc[2] <= lim && sc[3] <= lim;
+        conv_sums(vm, w2q * Xn[0] * Xn[0], dm2, dn2);
+        const bool conv1 = !half_any(!(dm2 <= tol2 * (dref0 > dn2 ? dref0 : dn2)), h);
         if (q0 == 0) S.flag[sp][h] = (conv1 ? 1 : 0) | (bad ? 2 : 0);
 #pragma unroll
         for (int x = 0; x < (PHI1 ? 4 : 1); ++x) S.M[sp][x][lane] = Xn[x];
@@ -382,7 +398,7 @@ struct VSplitSolver {
           }
           if (all & 1) {
             // ||D^[k,*]|| is the reference of the next inner loop
-            dref = sn[0];
+            dref = dn2;
             cvd = true;
             act = false;
           }
@@ -392,9 +408,12 @@ struct VSplitSolver {
       if (run && !cvd) inner_failed = true;
       // the Eulerian integrals of the current moments at the matter iterate,
       // and after a failed loop the norm of the current moments
-      double X[5], norm;
-      eulerian(S, sp, h, q0, gsp, dsp, D, I, v, X, norm);
-      dref = (run && !cvd) ? norm : dref;
+      if (__builtin_amdgcn_ballot_w64(run && !cvd) != 0) {
+        const double n = norm(w2q);
+        dref = (run && !cvd) ? n : dref;
+      }
+      double X[5];
+      eulerian(S, md, sp, lane, q, D, I, v, X);
       if (a->prm.fixed_matter) {
         if (run) outer_conv = true;
         run = false;
@@ -475,8 +494,8 @@ struct VSplitSolver {
     double yout[5], T_out;
     {
       const double vu[3] = {pt.yused[2], pt.yused[3], pt.yused[4]};
-      double X[5], norm;
-      eulerian(S, sp, h, q0, gsp, dsp, D, I, vu, X, norm);
+      double X[5];
+      eulerian(S, mo, sp, lane, q0, D, I, vu, X);
       matter_rhs(pt, K, X, yout);
     }
     if (skip || ao->prm.fixed_matter) {

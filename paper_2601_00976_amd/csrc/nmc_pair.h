@@ -52,7 +52,7 @@ __device__ __forceinline__ void direct_row_regs(double hq, double rhq, double (&
 __device__ __forceinline__ void cross_fmac(double& y0, double& y1, double& y2, double& y3, double z0, double z1,
                                            double z2, double z3, double k0, double k1, double k2, double k3) {
   asm volatile(
-      "s_nop 1\n"
+      "s_nop 1\n.p2align 3\n"
       "v_fmac_f64_dpp %0, %4, %8 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n"
       "v_fmac_f64_dpp %1, %5, %9 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n"
       "v_fmac_f64_dpp %2, %6, %10 row_newbcast:15 row_mask:0x5 bank_mask:0xf\n"
@@ -173,6 +173,15 @@ __device__ __forceinline__ void half_sums4(const double (&v)[4], double (&s)[4])
   s[3] = row_bcast<12>(z);
 }
 
+// Adds moment x's terms to the Gram sums of an Anderson step (x = 0 sets them):
+// the fused products spelled out, so that every kernel rounds alike.
+__device__ __forceinline__ void gram_terms(int x, double dF1, double dF2, double F, double (&g)[4]) {
+  g[0] = x ? __builtin_fma(dF1, dF2, g[0]) : dF1 * dF2;
+  g[1] = x ? __builtin_fma(dF2, dF2, g[1]) : dF2 * dF2;
+  g[2] = x ? __builtin_fma(dF1, F, g[2]) : dF1 * F;
+  g[3] = x ? __builtin_fma(dF2, F, g[3]) : dF2 * F;
+}
+
 // max(a, -b) of two non-NaN values as one v_max_f64 with a negated operand
 __device__ __forceinline__ double max_neg_f64(double a, double b) {
   double r;
@@ -235,6 +244,10 @@ __device__ __forceinline__ bool half_any(bool b) {
 // by detailed balance once the row sum is scaled by h_q (h = exp(-e / T)).
 // The leading s_nop covers the VALU-write to DPP-read distance for registers
 // written just before.
+// The 8-byte instructions of the blocks start on 8 bytes: with one wave per
+// SIMD the kernels' speed follows where they fall, whatever other code moves
+// them (coupled O(v) solve of 4096 points, 1152 us so and 1190 us four bytes
+// off; 65536 points 3410 and 3500 us).
 template <int NS>
 struct ColFmac;
 
@@ -245,7 +258,7 @@ struct ColFmac<3> {
                                              const double (&x)[3], const double (&y)[3], const double (&hy)[3],
                                              double fi, double fo, double fa) {
     asm volatile(
-        "s_nop 1\n"
+        "s_nop 1\n.p2align 3\n"
         "v_fmac_f64_dpp %0, %12, %21 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %1, %13, %21 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %2, %14, %21 row_newbcast:%24 row_mask:0xf bank_mask:0xf\n"
@@ -272,7 +285,7 @@ struct ColFmac<2> {
                                              const double (&x)[2], const double (&y)[2], const double (&hy)[2],
                                              double fi, double fo, double fa) {
     asm volatile(
-        "s_nop 1\n"
+        "s_nop 1\n.p2align 3\n"
         "v_fmac_f64_dpp %0, %8, %14 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %1, %9, %14 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %2, %10, %15 row_newbcast:%17 row_mask:0xf bank_mask:0xf\n"
@@ -293,7 +306,7 @@ struct ColFmac<1> {
                                              const double (&x)[1], const double (&y)[1], const double (&hy)[1],
                                              double fi, double fo, double fa) {
     asm volatile(
-        "s_nop 1\n"
+        "s_nop 1\n.p2align 3\n"
         "v_fmac_f64_dpp %0, %4, %7 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %2, %4, %9 row_newbcast:%10 row_mask:0xf bank_mask:0xf\n"
@@ -320,7 +333,7 @@ struct ColSym<3> {
                                              const double (&a)[3], const double (&b)[3], const double (&c)[3],
                                              const double (&d)[3], double m0, double m1, double m2, double m3) {
     asm volatile(
-        "s_nop 1\n"
+        "s_nop 1\n.p2align 3\n"
         "v_fmac_f64_dpp %0, %12, %24 row_newbcast:%28 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %1, %13, %24 row_newbcast:%28 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %2, %14, %24 row_newbcast:%28 row_mask:0xf bank_mask:0xf\n"
@@ -381,7 +394,7 @@ struct ColSym<2> {
                                              const double (&a)[2], const double (&b)[2], const double (&c)[2],
                                              const double (&d)[2], double m0, double m1, double m2, double m3) {
     asm volatile(
-        "s_nop 1\n"
+        "s_nop 1\n.p2align 3\n"
         "v_fmac_f64_dpp %0, %8, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %1, %9, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %2, %10, %16 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n"
@@ -426,7 +439,7 @@ struct ColSym<1> {
                                              const double (&a)[1], const double (&b)[1], const double (&c)[1],
                                              const double (&d)[1], double m0, double m1, double m2, double m3) {
     asm volatile(
-        "s_nop 1\n"
+        "s_nop 1\n.p2align 3\n"
         "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %1, %5, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"
         "v_fmac_f64_dpp %2, %6, %8 row_newbcast:%12 row_mask:0xf bank_mask:0xf\n"

@@ -7,15 +7,25 @@
 namespace nmc {
 namespace splitk {
 
-// sum over the species of what their waves left in LDS for point h
-template <int NS, int N, int M>
-__device__ __forceinline__ void species_sum(const double (&v)[NS][2][M], int h, double (&s)[N]) {
-#pragma unroll
-  for (int i = 0; i < N; ++i) s[i] = v[0][h][i];
-#pragma unroll
-  for (int t = 1; t < NS; ++t)
-#pragma unroll
-    for (int i = 0; i < N; ++i) s[i] += v[t][h][i];
+// Sums over the half-wave of the inner convergence test for the one species of
+// a wave, by the tree of spread_conv_sums (mirrored lanes add the same pairs):
+// the squared changes of its moments, two or four of them, spread over the
+// lanes (every lane has one), and the squared new D in every lane.
+__device__ __forceinline__ double conv_tail(double x) {
+  x += dpp<0x141>(x);  // row_half_mirror
+  x += dpp<0xB1>(x);   // quad_perm [1,0,3,2]
+  x += dpp<0x4E>(x);   // quad_perm [2,3,0,1]
+  return x;
+}
+__device__ __forceinline__ void conv_sums(const double (&d)[2], double xn, double& y, double& n) {
+  const double a = halve16(d[0], d[1]), b = halve16(xn, xn);
+  y = conv_tail(a + dpp<0x140>(a));  // row_mirror
+  n = conv_tail(b + dpp<0x140>(b));
+}
+__device__ __forceinline__ void conv_sums(const double (&d)[4], double xn, double& y, double& n) {
+  const double b = halve16(xn, xn);
+  y = conv_tail(fold_pair<0x140, 0x3>(halve16(d[0], d[2]), halve16(d[1], d[3])));
+  n = conv_tail(b + dpp<0x140>(b));
 }
 
 // any lane of half h of this wave

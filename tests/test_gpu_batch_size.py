@@ -88,3 +88,54 @@ def test_static_cold_failing_and_fixed(options):
     assert out["status"][[3, 40]].tolist() == [N.STATUS_EOS_DOMAIN] * 2
     assert out["status"][[7, 20]].tolist() == [N.STATUS_NONFINITE] * 2
     assert int(out["n_outer"][11]) == 0 and int(out["status"][11]) == 0
+
+
+PRM = dict(tol_inner=1e-12, tol_outer=1e-10)
+PHI1 = dict(phi1_nes=0.3, phi1_pair=-0.25)
+
+
+def _moving(m, d):
+    t = S.to_device(d)
+    D0, I0, ef0 = S.init_state_v(m, t)
+    return dict(D0=D0, I0=I0, rho=t["rho11"], ye=t["ye"], ef=ef0, v=t["v"])
+
+
+def _solve_v(m, prm):
+    return lambda t: S.solve_v(m, prm, W.DTAU_KM, t["D0"], t["I0"], t["rho"], t["ye"], t["ef"], t["v"],
+                               m.default_theta())
+
+
+@pytest.mark.parametrize("P", [1, 2, 77, "line", "line + 1"])
+@pytest.mark.parametrize("sp,options", [(SP3, {}), (SP2, {}), (SP3, PHI1), (SP2, PHI1),
+                                        (SP3, {"flags": N.EMAB | N.NES}), ((N.NU_X, N.NU_E_BAR, N.NU_E), {})])
+def test_moving(P, sp, options):
+    P = P if isinstance(P, int) else _line(len(sp), 16 if options == PHI1 else 12) + (P != "line")
+    print(f"[case] O(v) solve by batch size, P={P} species {sp} {options}", flush=True)
+    m = S.Model(S.Grid(16), species=sp, **options)
+    t = _moving(m, W.radial_profile_v(P=1 << 16, ns=len(sp)).take(np.linspace(4000, 55000, P).astype(np.int64)))
+    for prm in (S.Params(**PRM), S.Params(m_inner=1, m_outer=2, max_outer=4, **PRM), S.Params(m_inner=2, max_inner=3, **PRM),
+                S.Params(fixed_matter=True, **PRM)):
+        _same_bits(_solve_v(m, prm), t, P)
+
+
+@pytest.mark.parametrize("options", [{}, PHI1])
+def test_moving_cold_and_failing(options):
+    import torch
+    print(f"[case] O(v) solve by batch size, cold and failing points, {options}", flush=True)
+    m = S.Model(S.Grid(16), **options)
+    P = 96
+    d = W.radial_profile_v(P=1 << 16).take(np.linspace(20000, 44000, P).astype(np.int64))
+    T = np.random.default_rng(5).permutation(np.concatenate([np.geomspace(0.05, 0.3, P // 2), np.geomspace(0.3, 2.0, P // 2)]))
+    t = _moving(m, W.Draws(**{**d.__dict__, "T": T}))
+    fixed = _same_bits(_solve_v(m, S.Params(fixed_matter=True, **PRM)), t, P)
+    assert bool((fixed["status"] == 0).any())
+    _same_bits(_solve_v(m, S.Params(max_outer=5, **PRM)), t, P)
+    t["ef"][3] = t["ef"][40] = -1.0  # no temperature
+    t["D0"][7, 0, 5] = t["I0"][20, 2, 1, 31] = float("nan")
+    t["rho"][11] = 1e-6  # uncoupled
+    t["I0"][12] = 0.0
+    t["v"][13] = 0.0
+    out = _same_bits(_solve_v(m, S.Params(max_outer=5, **PRM)), t, P)
+    assert out["status"][[3, 40]].tolist() == [N.STATUS_EOS_DOMAIN] * 2
+    assert out["status"][[7, 20]].tolist() == [N.STATUS_NONFINITE] * 2
+    assert int(out["n_outer"][11]) == 0 and int(out["status"][11]) == 0
