@@ -181,11 +181,13 @@ typedef struct {
 
 /* Where the energy-coupling kernel matrices live during a solve, and how
  * the 32-node solve maps points to wavefronts.
- * ON_CHIP: the library's default.  32 nodes: as PAIRED; 64 nodes: of row q
- *   of the symmetric core exp(-|e - e'| / T) that all four kernels share, the
- *   entries of the lane's 16 nodes and the coefficients through which the
- *   other nodes' sums enter, in the registers of lane q, formed once per outer
- *   iteration.
+ * ON_CHIP: the library's default.  32 nodes: as PAIRED; batches too small to
+ *   fill the chip run one wavefront per species of a pair of points instead, with
+ *   the same bits, so that a pair's results depend neither on the size of its
+ *   batch nor on the launch shape.  64 nodes: of row q of the symmetric core
+ *   exp(-|e - e'| / T) that all four kernels share, the entries of the lane's 16
+ *   nodes and the coefficients through which the other nodes' sums enter, in the
+ *   registers of lane q, formed once per outer iteration.
  * HBM: 64-node solve only, for the roofline study of precomputed kernels:
  *   these entries of every point are written to the workspace once per outer
  *   iteration and re-read by every inner iteration; the workspace then needs
@@ -206,8 +208,7 @@ typedef struct {
  * owns one node of its point (every moment of every species) and contracts
  * the columns of its 16-lane row, broadcast from registers (DPP), the other
  * row's share entering by one coefficient; these factors are computed once per
- * outer iteration and kept in VGPRs.  Batches too small to fill the chip run
- * one wavefront per species of a pair of points instead. */
+ * outer iteration and kept in VGPRs. */
 #define NMC_KERNELS_PAIRED 4
 /* WAVE: 32 nodes only: one point per wavefront, the two lane halves owning
  * the number and flux moments and splitting the 32 columns; the lane's 16
@@ -333,8 +334,8 @@ typedef struct {
 /* Batched O(v) forward solve.  32-node grids only (NMC_E_UNSUPPORTED
  * otherwise).  launch->kernel_store NMC_KERNELS_ON_CHIP (default) or
  * NMC_KERNELS_PAIRED: two points per wavefront, each lane owning the four
- * moments of its node (small batches: one wavefront per species of a pair of
- * points); NMC_KERNELS_WAVE: one point per wavefront.  All carry the
+ * moments of its node (ON_CHIP, small batches: one wavefront per species of a
+ * pair of points, with the same bits); NMC_KERNELS_WAVE: one point per wavefront.  All carry the
  * linear-order corrections when phi1_nes or phi1_pair is nonzero.
  * Other modes return NMC_E_UNSUPPORTED.  Workspace, launch, stream and error
  * rules as for nmc_solve_batch; dtau must be positive. */

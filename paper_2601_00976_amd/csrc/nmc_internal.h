@@ -175,10 +175,11 @@ inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, in
 // against 124; O(v) solve of 8 points 116 against 168, 2048 points (12 waves)
 // 189 against 216, 2730 points 238 against 216; with linear-order kernels 8
 // points 166 against 297, 2730 points 351 against 388, 4096 points 495 against
-// 403.  A rule of the batch alone: results do not depend on the launch shape.
+// 403.  The two kernels give the same bits, so results do not depend on the
+// batch; kernel_store = PAIRED keeps the two-point kernel.
 constexpr int kSplitWaves = 16, kSplitWavesV = 12;
-inline bool split_by_species(int64_t P, int ns, int num_cu, int waves) {
-  return ns > 1 && (P + 1) / 2 * ns <= (int64_t)waves * num_cu;
+inline bool split_by_species(const nmc_launch& L, int64_t P, int ns, int num_cu, int waves) {
+  return L.kernel_store == NMC_KERNELS_ON_CHIP && ns > 1 && (P + 1) / 2 * ns <= (int64_t)waves * num_cu;
 }
 
 // its grid: one work-group per pair, or as many as the caller wants resident
