@@ -628,7 +628,7 @@ hipError_t launch_forward(const FwdArgs& a, int nq, int ns, bool coupled, bool p
                           int num_cu, hipStream_t s) {
   if (nq == 32) {
     if (L.kernel_store == NMC_KERNELS_ON_CHIP || L.kernel_store == NMC_KERNELS_PAIRED)
-      return coupled && split_by_species(L, a.P, ns, num_cu, kSplitWaves)
+      return coupled && split_by_species(L, a.P, ns, num_cu, split_waves(ns))
                  ? launch_forward_split(a, ns, proj, L, num_cu, s)
                  : launch_forward_pair(a, ns, coupled, proj, L, num_cu, s);
     if (proj) return hipErrorInvalidValue;

@@ -727,7 +727,7 @@ hipError_t launch_vpair_t(FwdVArgs a, const nmc_launch& L, int num_cu, hipStream
 
 hipError_t launch_forward_vpair(const FwdVArgs& a, int ns, bool coupled, bool phi1, const nmc_launch& L,
                                 int num_cu, hipStream_t s) {
-  if (coupled && split_by_species(L, a.P, ns, num_cu, phi1 ? kSplitWaves : kSplitWavesV))
+  if (coupled && split_by_species(L, a.P, ns, num_cu, split_waves_v(ns, phi1)))
     return launch_forward_vsplit(a, ns, phi1, L, num_cu, s);
   if (coupled && phi1) {
     switch (ns) {

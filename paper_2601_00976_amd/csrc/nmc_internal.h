@@ -167,17 +167,23 @@ inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, in
 // points instead of one per pair: up to `waves` such wavefronts per compute
 // unit (eight are resident).  There the slowest points set the time and their
 // share of work per wavefront is what counts; beyond, the species' common work
-// (equation of state, rows) done once per wavefront costs more.  Static solve
-// and O(v) solve with linear-order kernels kSplitWaves, plain O(v) solve
-// kSplitWavesV.  Three species, split against pairs: static solve of 8 points
-// 44 against 62 us, 2048 points 60 against 75, 2730 points (16 waves) 71
-// against 76, 3400 points 83 against 78; projected equilibrium 2730 points 96
-// against 124; O(v) solve of 8 points 116 against 168, 2048 points (12 waves)
-// 189 against 216, 2730 points 238 against 216; with linear-order kernels 8
-// points 166 against 297, 2730 points 351 against 388, 4096 points 495 against
-// 403.  The two kernels give the same bits, so results do not depend on the
-// batch; kernel_store = PAIRED keeps the two-point kernel.
-constexpr int kSplitWaves = 16, kSplitWavesV = 12;
+// (equation of state, rows) done once per wavefront costs more.  Each number of
+// species has a line of its own: with two, a pair's wave has less to share out.
+// Mean us over six draws, split against pairs, at the line and beyond it:
+// static solve of three species, 3413 points (20 waves) 75 against 77, 4096
+// points 87 against 81; projected equilibrium 111 against 122 and 130 against
+// 122; two species 4096 points (16 waves) 54 against 54 and projected 79 against
+// 82, 4352 points 58 against 55 and 86 against 83.  O(v) solve of three species,
+// 2389 points (14 waves) 215 against 230, 2730 points 238 against 220; two
+// species 2560 points (10 waves) 129 against 132, 2816 points 135 against 133.
+// With linear-order kernels three species 2730 points (16 waves) 348 against
+// 374, 3072 points 386 against 376; two species 2816 points (11 waves) 200
+// against 208, 3072 points 217 against 213.  Small batches: static solve of 8
+// points 44 against 61, O(v) 119 against 173, with linear-order kernels 168
+// against 289.  The two kernels give the same bits, so results do not depend on
+// the batch; kernel_store = PAIRED keeps the two-point kernel.
+constexpr int split_waves(int ns) { return ns == 2 ? 16 : 20; }
+constexpr int split_waves_v(int ns, bool phi1) { return phi1 ? (ns == 2 ? 11 : 16) : (ns == 2 ? 10 : 14); }
 inline bool split_by_species(const nmc_launch& L, int64_t P, int ns, int num_cu, int waves) {
   return L.kernel_store == NMC_KERNELS_ON_CHIP && ns > 1 && (P + 1) / 2 * ns <= (int64_t)waves * num_cu;
 }

@@ -59,7 +59,7 @@ OPTIONS = [(SP3, {}), (SP2, {}), (SP3, {"fd_projection": 1}), (SP2, {"fd_project
 @pytest.mark.parametrize("P", [1, 2, 77, "line", "line + 1"])
 @pytest.mark.parametrize("sp,options", OPTIONS)
 def test_static(P, sp, options):
-    P = P if isinstance(P, int) else _line(len(sp), 16) + (P != "line")
+    P = P if isinstance(P, int) else _line(len(sp), {2: 16, 3: 20}[len(sp)]) + (P != "line")
     print(f"[case] static solve by batch size, P={P} species {sp} {options}", flush=True)
     m = S.Model(S.Grid(16), species=sp, **options)
     d = W.radial_profile(P=1 << 16, ns=len(sp), seed=11).take(np.linspace(3000, 60000, P).astype(np.int64))
@@ -109,7 +109,7 @@ def _solve_v(m, prm):
 @pytest.mark.parametrize("sp,options", [(SP3, {}), (SP2, {}), (SP3, PHI1), (SP2, PHI1),
                                         (SP3, {"flags": N.EMAB | N.NES}), ((N.NU_X, N.NU_E_BAR, N.NU_E), {})])
 def test_moving(P, sp, options):
-    P = P if isinstance(P, int) else _line(len(sp), 16 if options == PHI1 else 12) + (P != "line")
+    P = P if isinstance(P, int) else _line(len(sp), ({2: 11, 3: 16} if options == PHI1 else {2: 10, 3: 14})[len(sp)]) + (P != "line")
     print(f"[case] O(v) solve by batch size, P={P} species {sp} {options}", flush=True)
     m = S.Model(S.Grid(16), species=sp, **options)
     t = _moving(m, W.radial_profile_v(P=1 << 16, ns=len(sp)).take(np.linspace(4000, 55000, P).astype(np.int64)))
