@@ -24,9 +24,13 @@
 // forward solve's contraction on the symmetric core (24 n^2 multiply-adds for
 // both columns of C) where an elimination takes (2/3) (64^3 + 32^3).
 //
+// A long step or strong coupling makes N large: the changes then have to keep a
+// pace (kAdjPace bits per iteration, looked at after 2, 6 and 12), and a point
+// that falls behind is left to the elimination at once.
+//
 // Elimination (PointAdjoint): for points that the iteration does not settle
 // (slow convergence, a non-finite value) or whose grid spans too many powers
-// of two for it.  A is block diagonal over pair-coupled species: NES couples
+// of two for it, in a second kernel with a work-group per point.  A is block diagonal over pair-coupled species: NES couples
 // the nodes of one species, pair processes couple a species with its partner,
 // so with species in id order the blocks are (nu_e, anti-nu_e) of size 64 and
 // nu_x of size 32.  Each block is factorised in registers, one wavefront per
@@ -35,8 +39,14 @@
 // row exchanges, broadcasting the two pivot rows of each step through LDS.
 //
 // Every work-group adds its points' terms in order and writes one row of
-// partial sums; a second kernel adds the rows of each column in a fixed
-// order.  Where the caller asks for them, the per-point terms go to a
+// partial sums (one of the elimination only if it had a point); a last kernel
+// adds the rows of each column in a fixed order.
+//
+// us of a call, eliminating every point / without the pace and two points of a
+// pair eliminated one after the other / so: 8 points at 0.5 km, none settling,
+// 70 / 117 / 54; 65536 such points 1954 / 2831 / 2086; the whole profile at 0.5
+// km, 65536 points, 1946 / 959 / 829; 65536 points of 0.1-0.2 MeV 1946 / 2063 /
+// 1910; at 1e-3 km, all settling, 1951 / 305 / 303.  Where the caller asks for them, the per-point terms go to a
 // (P, nq + 2) array as well.
 #include "nmc_pair.h"
 
@@ -455,6 +465,11 @@ struct AdjPairLds {
 // would change it by a fraction of that)
 constexpr int kAdjMaxIt = 24;
 constexpr double kAdjSettled = 0x1p-48;
+// bits that the largest change has to lose per iteration.  48 / kAdjMaxIt = 2
+// would keep every point that can settle: 4-8% less for 65536 points of which a
+// part settles slowly, but 8 points of the dense centre at 0.5 km then take 82 us
+// instead of 54, a wavefront waiting for the slowest of them
+constexpr int kAdjPace = 3;
 
 // Two points per wavefront by iteration: lane 32 h + q holds node q of the
 // point of half h, for every species.
@@ -535,6 +550,7 @@ struct PairAdjoint {
     const int nlo = h ? lo1 : lo0, nhi = h ? hi1 : hi0;
     const int c = (nlo + nhi) >> 1;
     bool act = warm && nhi - nlo <= pairk::kDirectBits;
+    if (__builtin_amdgcn_ballot_w64(act) == 0) return false;
     const double gq = ldexp(xs.R, c - xs.n), rgq = ldexp(xs.P, xs.n - c);
     const double hq = ldexp(xs.R * xs.R, -2 * xs.n);  // exp(-e / T)
     double B[16], kx;
@@ -625,7 +641,11 @@ struct PairAdjoint {
     for (int it = 0; it < kAdjMaxIt && __builtin_amdgcn_ballot_w64(act) != 0; ++it) {
 #pragma unroll
       for (int j = 0; j < 16; ++j) asm volatile("" : "+v"(B[j]));
-      bool moved = false;
+      // after 2, 6 and 12 iterations the changes have to be down to pace
+      const int done = it + 1;
+      const bool look = done == 2 || done == 6 || done == 12;
+      const double pace = ldexp(1.0, 1 - kAdjPace * done);
+      bool moved = false, behind = false;
 #pragma unroll
       for (int k = 0; k < 2; ++k) {
         double xg[NS], yg[NS], xd[NS], hy[NS];
@@ -650,13 +670,15 @@ struct PairAdjoint {
           const double off = __builtin_fma(wn, nes, -wp * pr);
           const double cc = k ? c1[t] : c0[t];
           const double zn = __builtin_fma(off, rcp_nr(dg[t]), cc);
-          moved = moved || !(fabs(zn - z[k][t]) <= kAdjSettled * (fabs(zn) + fabs(cc)));
+          const double change = fabs(zn - z[k][t]), size = fabs(zn) + fabs(cc);
+          moved = moved || !(change <= kAdjSettled * size);
+          if (look) behind = behind || !(change <= pace * size);
           z[k][t] = act ? zn : z[k][t];
         }
       }
       const bool on = pairk::half_any(moved);
       solved = solved || (act && !on);
-      act = act && on;
+      act = act && on && !pairk::half_any(behind);
     }
 
     // ---- Schur complement on (Ye, e), multipliers and gradient ------------
@@ -696,12 +718,12 @@ struct PairAdjoint {
 // node and the two amplitudes
 struct AdjSums {
   double s = 0.0, nes = 0.0, pair = 0.0;
-  // the work-group's row of partial sums, set or added to
-  __device__ __forceinline__ void store(double* __restrict__ row, bool add) const {
+  // the work-group's row of partial sums
+  __device__ __forceinline__ void store(double* __restrict__ row) const {
     const int lane = threadIdx.x;
     const double a = sum_halves(s), b = sum_halves(nes), c = sum_halves(pair);
     const double v = lane < NQ ? a : (lane == NQ ? b : c);
-    if (lane < NQ + 2) row[lane] = add ? row[lane] + v : v;
+    if (lane < NQ + 2) row[lane] = v;
   }
 };
 
@@ -741,58 +763,63 @@ __global__ __launch_bounds__(kLanes, 2) void adj_kernel(AdjArgs a) {
     if (lane == 0) a.left[u] = (uint8_t)((left & 1) | ((left >> 32) & 1) << 1);
     __syncthreads();
   }
-  sum.store(a.partial + (int64_t)blockIdx.x * (NQ + 2), false);
+  sum.store(a.partial + (int64_t)blockIdx.x * (NQ + 2));
 }
 
 // The points that the iteration left over, by elimination: every work-group
-// looks through the flags of its own pairs (the same ones as in adj_kernel, 64
-// at a time) and adds to its own row, so the order of the sums is fixed.
+// looks through the flags of its own points, 64 at a time, and writes a row of
+// partial sums if it had any, so the order of the sums is fixed.
 template <int NS>
 __global__ __launch_bounds__(kLanes) void adj_left_kernel(AdjArgs a) {
   __shared__ AdjLds<NS> S;
   const int lane = threadIdx.x, h = lane >> 5;
   AdjSums sum;
   bool any = false;
-  const int64_t pairs = (a.P + 1) / 2;
-  for (int64_t u0 = blockIdx.x; u0 < pairs; u0 += (int64_t)kLanes * gridDim.x) {
-    const int64_t u = u0 + (int64_t)lane * gridDim.x;
-    const int f = u < pairs ? a.left[u] : 0;
-    for (uint64_t todo = __builtin_amdgcn_ballot_w64(f != 0); todo != 0; todo &= todo - 1) {
-      const int l = __builtin_ctzll(todo);
-      const int bits = __builtin_amdgcn_readlane(f, l);
+  for (int64_t p0 = blockIdx.x; p0 < a.P; p0 += (int64_t)kLanes * gridDim.x) {
+    const int64_t p = p0 + (int64_t)lane * gridDim.x;
+    const bool mine = p < a.P && ((a.left[p >> 1] >> (p & 1)) & 1) != 0;
+    for (uint64_t todo = __builtin_amdgcn_ballot_w64(mine); todo != 0; todo &= todo - 1) {
       if (!any) load_model(a.mdl, a.theta, S.m);
       any = true;
-      for (int k = 0; k < 2; ++k) {
-        if (((bits >> k) & 1) == 0) continue;
-        const int64_t pt = uniform64(2 * (u0 + (int64_t)l * gridDim.x) + k);
-        double g_s, g_nes, g_pair, own, other;
-        PointAdjoint<NS>::run(a, pt, S, g_s, g_nes, g_pair);
-        swap32(g_s, own, other);  // the s_q terms of lanes 0..31 in both halves
-        sum.s += h == 0 ? own : 0.0;
-        sum.nes += h == 0 ? g_nes : 0.0;
-        sum.pair += h == 0 ? g_pair : 0.0;
-        if (a.grad_pp && h == 0) store_terms(a.grad_pp, pt, own, g_nes, g_pair);
-      }
+      const int64_t pt = uniform64(p0 + (int64_t)__builtin_ctzll(todo) * gridDim.x);
+      double g_s, g_nes, g_pair, own, other;
+      PointAdjoint<NS>::run(a, pt, S, g_s, g_nes, g_pair);
+      swap32(g_s, own, other);  // the s_q terms of lanes 0..31 in both halves
+      sum.s += h == 0 ? own : 0.0;
+      sum.nes += h == 0 ? g_nes : 0.0;
+      sum.pair += h == 0 ? g_pair : 0.0;
+      if (a.grad_pp && h == 0) store_terms(a.grad_pp, pt, own, g_nes, g_pair);
     }
   }
-  if (any) sum.store(a.partial + (int64_t)blockIdx.x * (NQ + 2), true);
+  if (any) sum.store(a.partial_left + (int64_t)blockIdx.x * (NQ + 2));
+  if (lane == 0) a.had[blockIdx.x] = any ? 1 : 0;
 }
 
 template <int NS>
-void launch_adjoint_t(const AdjArgs& a, unsigned grid, hipStream_t s) {
+void launch_adjoint_t(const AdjArgs& a, unsigned grid, unsigned grid_left, hipStream_t s) {
   hipLaunchKernelGGL(adj_kernel<NS>, dim3(grid), dim3(kLanes), 0, s, a);
-  hipLaunchKernelGGL(adj_left_kernel<NS>, dim3(grid), dim3(kLanes), 0, s, a);
+  hipLaunchKernelGGL(adj_left_kernel<NS>, dim3(grid_left), dim3(kLanes), 0, s, a);
 }
 
 // Adds the work-groups' rows of partial sums to out, one work-group per
-// column: thread t adds rows t, t + 256, ... in order, then a fixed-shape tree
-// over the 256 threads.  (One work-group for all 34 columns took 55 us.)
-__global__ __launch_bounds__(256) void reduce_partials(const double* __restrict__ partial, int rows, int ncol,
+// column: thread t adds rows t, t + 256, ... of the iteration in order, then
+// rows 16 t .. 16 t + 15 of the elimination where they are marked, then a fixed-shape tree over the 256 threads.
+// (One work-group for all 34 columns took 55 us.)
+__global__ __launch_bounds__(256) void reduce_partials(AdjArgs a, int rows, int rows_left, int ncol,
                                                        double* __restrict__ out) {
   __shared__ double red[256];
   const int t = threadIdx.x, c = blockIdx.x;
   double s = 0.0;
-  for (int b = t; b < rows; b += 256) s += partial[(int64_t)b * ncol + c];
+  for (int b = t; b < rows; b += 256) s += a.partial[(int64_t)b * ncol + c];
+  static_assert(kAdjPartials == 256 * 16, "16 marks per thread");
+  const uint4 had = ((const uint4*)a.had)[t];
+  if ((had.x | had.y | had.z | had.w) != 0) {
+    const uint32_t word[4] = {had.x, had.y, had.z, had.w};
+    for (int i = 0; i < 16; ++i) {
+      const int b = 16 * t + i;
+      if (b < rows_left && (word[i >> 2] >> (8 * (i & 3)) & 0xff) != 0) s += a.partial_left[(int64_t)b * ncol + c];
+    }
+  }
   red[t] = s;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
@@ -808,17 +835,22 @@ hipError_t launch_adjoint(const AdjArgs& a, int nq, int ns, int num_cu, double* 
   if (nq != NQ || ns < 1 || ns > 3) return hipErrorInvalidValue;
   if (a.P == 0) return hipSuccess;
   const int64_t pairs = (a.P + 1) / 2;
-  int64_t grid = (int64_t)num_cu * 8;  // two work-groups per SIMD stay resident
+  // two work-groups per SIMD stay resident; the elimination's unevenly loaded
+  // ones are twice as many in long batches (65536 points, all eliminated, 2086
+  // against 2151 us; 4096 points, none, 39.6 against 37.4 us)
+  int64_t grid = (int64_t)num_cu * 8, left = a.P > 4 * grid ? 2 * grid : grid;
   if (grid > pairs) grid = pairs;
   if (grid > kAdjPartials) grid = kAdjPartials;
+  if (left > a.P) left = a.P;
+  if (left > kAdjPartials) left = kAdjPartials;
   switch (ns) {
-    case 1: launch_adjoint_t<1>(a, (unsigned)grid, s); break;
-    case 2: launch_adjoint_t<2>(a, (unsigned)grid, s); break;
-    default: launch_adjoint_t<3>(a, (unsigned)grid, s); break;
+    case 1: launch_adjoint_t<1>(a, (unsigned)grid, (unsigned)left, s); break;
+    case 2: launch_adjoint_t<2>(a, (unsigned)grid, (unsigned)left, s); break;
+    default: launch_adjoint_t<3>(a, (unsigned)grid, (unsigned)left, s); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(reduce_partials, dim3(NQ + 2), dim3(256), 0, s, a.partial, (int)grid, NQ + 2, grad_theta);
+  hipLaunchKernelGGL(reduce_partials, dim3(NQ + 2), dim3(256), 0, s, a, (int)grid, (int)left, NQ + 2, grad_theta);
   return hipGetLastError();
 }
 

@@ -350,17 +350,33 @@ int nmc_model_destroy(nmc_model* m) {
   return e == hipSuccess ? NMC_OK : hip_fail(e, "model_destroy");
 }
 
-static size_t adj_partial_bytes(const nmc_model* m, int64_t P) {
+namespace {
+size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// workspace of the adjoint behind the queue counters: a row of partial sums per
+// work-group of the iteration and of the elimination, the latter's marks and a
+// flag byte per pair of points
+struct AdjWs {
+  size_t partial, partial_left, had, left, total;
+};
+
+AdjWs adj_layout(const nmc_model* m, int64_t P) {
   const size_t pairs = ((size_t)P + 1) / 2, most = (size_t)nmc::kAdjPartials;
-  return ((pairs < most ? pairs : most) * ((size_t)m->host.nq + 2) * sizeof(double) + 255) & ~(size_t)255;
+  const size_t row = ((size_t)m->host.nq + 2) * sizeof(double);
+  const size_t rows = pairs < most ? pairs : most, rows_left = (size_t)P < most ? (size_t)P : most;
+  AdjWs w;
+  w.partial = kCounterBytes;
+  w.partial_left = w.partial + al256(rows * row);
+  w.had = w.partial_left + al256(rows_left * row);
+  w.left = w.had + most;
+  w.total = w.left + al256(pairs);
+  return w;
 }
+}  // namespace
 
 size_t nmc_workspace_bytes(const nmc_model* m, int64_t P) {
   if (!m || P < 0) return 0;
-  // queue counters + the adjoint's rows of partial sums, one per work-group,
-  // and its flags, one byte per pair of points
-  const size_t pairs = ((size_t)P + 1) / 2;
-  return kCounterBytes + adj_partial_bytes(m, P) + ((pairs + 255) & ~(size_t)255);
+  return adj_layout(m, P).total;
 }
 
 size_t nmc_kernel_store_bytes(const nmc_model* m, int64_t P) {
@@ -609,8 +625,6 @@ struct PdarsWs {
   size_t total;
 };
 
-size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 PdarsWs pdars_layout(const nmc_model* m, int64_t P, char* base) {
   PdarsWs w;
   const size_t nn = (size_t)m->host.ns * m->host.nq, pp = (size_t)P;
@@ -740,8 +754,11 @@ int nmc_solve_batch_adjoint(const nmc_model* m, const nmc_solver_params* prm, in
   a.n_outer = fwd->n_outer;
   a.gbar = gbar;
   a.grad_pp = grad_pp;
-  a.partial = (double*)((char*)ws + kCounterBytes);
-  a.left = (uint8_t*)ws + kCounterBytes + adj_partial_bytes(m, P);
+  const AdjWs w = adj_layout(m, P);
+  a.partial = (double*)((char*)ws + w.partial);
+  a.partial_left = (double*)((char*)ws + w.partial_left);
+  a.had = (uint8_t*)ws + w.had;
+  a.left = (uint8_t*)ws + w.left;
   hipError_t e = nmc::launch_adjoint(a, m->host.nq, m->host.ns, m->num_cu, grad_theta, (hipStream_t)stream);
   return e == hipSuccess ? NMC_OK : hip_fail(e, "adjoint: launch");
 }

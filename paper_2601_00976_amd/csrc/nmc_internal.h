@@ -10,7 +10,7 @@ namespace nmc {
 
 constexpr int kMaxNq = 64;
 constexpr int kMaxNs = 3;
-constexpr int kAdjPartials = 4096;  // most work-groups of the adjoint, a row of partial sums each
+constexpr int kAdjPartials = 4096;  // most work-groups of either adjoint kernel, a row of partial sums each
 
 // Model table resident in device memory.  The kernels copy the per-node
 // tables into LDS once per work-group and read the uniform scalars through
@@ -112,7 +112,9 @@ struct AdjArgs {
   const int32_t *status, *n_outer;
   const double* gbar;
   double* grad_pp;     // (P, nq + 2) per-point terms or nullptr
-  double* partial;     // (work-groups, nq + 2) partial sums
+  double* partial;       // (work-groups of the iteration, nq + 2) partial sums
+  double* partial_left;  // (work-groups of the elimination, nq + 2) likewise, written where `had` is set
+  uint8_t* had;          // per work-group of the elimination: whether it had a point (kAdjPartials bytes)
   uint8_t* left;       // per pair of points: bit h set where half h is left to the elimination
 };
 
