@@ -69,12 +69,6 @@ struct AdjLds {
   alignas(16) double prow[2 * (2 * NQ + 2)];  // pivot-row buffers of the block factorisation
 };
 
-__device__ __forceinline__ double readlane_f64(double v, int lane) {
-  const uint32_t lo = __builtin_amdgcn_readlane((int)lo32(v), lane);
-  const uint32_t hi = __builtin_amdgcn_readlane((int)hi32(v), lane);
-  return mk64(lo, hi);
-}
-
 // ds_write2_b64 of (a, b) to LDS bytes base + 8 J and base + 8 (J + 1)
 template <int J>
 __device__ __forceinline__ void lds_write2_f64(uint32_t base, double a, double b) {
@@ -156,8 +150,8 @@ __device__ __forceinline__ bool solve_block_transposed(double (&R)[N], double c0
     lds_f64* prow = (lds_f64*)prow_generic;
     lds_f64x2* prow2 = (lds_f64x2*)prow;
     // the pivot block B = [[a00, a01], [a10, a11]] (rows k, k+1, columns k, k+1)
-    const double a00 = readlane_f64(R[k], k), a01 = readlane_f64(R[k + 1], k);
-    const double a10 = readlane_f64(R[k], k + 1), a11 = readlane_f64(R[k + 1], k + 1);
+    const double a00 = readlane(R[k], k), a01 = readlane(R[k + 1], k);
+    const double a10 = readlane(R[k], k + 1), a11 = readlane(R[k + 1], k + 1);
     if (lane == k || lane == k + 1) {
       // rows k and k+1 (columns k..N-1) to their buffers: ds_write2_b64 from
       // one base register per lane with 8-byte-unit offsets
