@@ -214,7 +214,7 @@ struct PointSolver64 {
 
   // settle() is called once the point's inputs are loaded (work-queue hook)
   template <class Settle>
-  __device__ static void solve(int64_t p, Lds64<NS>& S, Settle&& settle) {
+  __device__ __forceinline__ static void solve(int64_t p, Lds64<NS>& S, Settle&& settle) {
     const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
     const_ptr<DevModel> md = scalar_ptr(a->mdl);
     const ModelLdsN<NQ>& mt = S.m;

@@ -70,7 +70,7 @@ struct PairSolver {
 
   // settle() is called once the pair's inputs are loaded (work-queue hook)
   template <class Settle>
-  __device__ static void solve(int64_t u, PairLds<NS>& S, Settle&& settle) {
+  __device__ __forceinline__ static void solve(int64_t u, PairLds<NS>& S, Settle&& settle) {
     const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
     const_ptr<DevModel> md = scalar_ptr(a->mdl);
     const ModelLds& mt = S.m;

@@ -64,7 +64,7 @@ struct SplitSolver {
     half_own_sums<1>(v, m);
   }
 
-  __device__ static void solve(int64_t u, SplitLds<NS>& S) {
+  __device__ __forceinline__ static void solve(int64_t u, SplitLds<NS>& S) {
     const_ptr<FwdArgs> a = kernel_args<FwdArgs>();
     const_ptr<DevModel> md = scalar_ptr(a->mdl);
     const ModelLds& mt = S.m;

@@ -160,7 +160,7 @@ struct VPairSolver {
   }
 
   template <class Settle>
-  __device__ static void solve(int64_t u, VPairLds<NS>& S, Settle&& settle) {
+  __device__ __forceinline__ static void solve(int64_t u, VPairLds<NS>& S, Settle&& settle) {
     const_ptr<FwdVArgs> a = kernel_args<FwdVArgs>();
     const DevModel* mdl = a->mdl;
     const_ptr<DevModel> md = scalar_ptr(mdl);

@@ -90,7 +90,7 @@ struct VSplitSolver {
     for (int j = 0; j < 3; ++j) yq[2 + j] = pt.yst[2 + j] - Kv * (X[2 + j] - pt.X0[2 + j]);
   }
 
-  __device__ static void solve(int64_t u, Lds& S) {
+  __device__ __forceinline__ static void solve(int64_t u, Lds& S) {
     const_ptr<FwdVArgs> a = kernel_args<FwdVArgs>();
     const DevModel* mdl = a->mdl;
     const_ptr<DevModel> md = scalar_ptr(mdl);

@@ -291,7 +291,9 @@ __device__ __forceinline__ const_ptr<T> scalar_ptr(const T* p) {
 // kernarg segment), laundered like opaque_ptr: its members are read by scalar
 // loads where they are used.  As ordinary parameters they would be loaded
 // once and held, some 60 scalar registers that the solve kernels do not have:
-// they were spilled to vector-register lanes and read back lane by lane.
+// they were spilled to vector-register lanes and read back lane by lane.  The
+// segment pointer exists in kernels alone (a function that is called gets a
+// null one), so every function that uses this is __forceinline__.
 template <class A>
 __device__ __forceinline__ const_ptr<A> kernel_args() {
   return scalar_ptr((const A*)__builtin_amdgcn_kernarg_segment_ptr());
