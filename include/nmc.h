@@ -172,7 +172,8 @@ typedef struct {
 
 typedef struct {
   int blocks_per_cu;   /* resident work-groups per compute unit for the persistent grid (0 = auto) */
-  int chunk;           /* most points taken per work-queue grab (>= 1); short batches take fewer */
+  int chunk;           /* most points (or pairs) taken per work-queue grab (>= 1): at most 1/64 of a work-group's
+                        * even share of the batch */
   int persistent;      /* 1: persistent grid with an atomic work queue (with blocks_per_cu 0, batches of a few
                         * rounds of the chip get one work-group per point or pair instead); 0: one work-group per
                         * chunk */

@@ -1,10 +1,10 @@
 """Launch-shape autotuner for the persistent solve kernel.
 
-The knobs are the points taken per work-queue grab (`chunk`), the resident
-work-groups per compute unit of the persistent grid (`blocks_per_cu`, 0 =
-occupancy limit), persistent versus one-work-group-per-chunk launches, and
-(32 nodes) the kernel-row mode: regenerated with cached pair factors (the
-default), fully regenerated, or register-resident.
+The knobs are the most points taken per work-queue grab (`chunk`), the resident
+work-groups per compute unit of the persistent grid (`blocks_per_cu`),
+persistent versus one-work-group-per-chunk launches, and (32 nodes) the
+kernel mode: two points per wavefront (the default), one, fully regenerated
+factors, or register-resident rows.
 `tune()` times candidate shapes on a real batch and stores the winner in a
 JSON cache next to this file, keyed by (energy nodes, species, device name);
 `best_launch()` reads the cache and falls back to the persistent default.
@@ -49,17 +49,24 @@ def best_launch(model, P: int) -> S.LaunchConfig:
     return S.LaunchConfig(blocks_per_cu=0, chunk=4, persistent=True)
 
 
-def candidates(model=None, persistent_only=True):
-    """Launch shapes to try.  The batched solve is specified as a persistent
-    work-queue kernel, so by default only persistent shapes are tuned (one
-    work-group per chunk, the hardware dispatcher acting as the queue, is
-    available through LaunchConfig(persistent=False))."""
+def candidates(model=None, persistent_only=True, P=1 << 16, num_cu=256):
+    """Launch shapes to try on a batch of P points.  The batched solve is
+    specified as a persistent work-queue kernel, so by default only shapes with
+    the queue are tuned: blocks_per_cu 0 leaves the choice to the library, which
+    gives batches of a few rounds one work-group per unit, as does
+    LaunchConfig(persistent=False).  The library takes at most 1/64 of a
+    work-group's share of the batch per grab, so larger chunks would be the same
+    launch again and are left out."""
     stores = (0, 5, 2, 3) if model is None or model.nq == 32 else (0,)
     for store in stores:
-        for persistent in ((True,) if persistent_only else (True, False)):
+        units = (P + 1) // 2 if store == 0 and (model is None or model.nq == 32) else P
+        for bpc in (8, 12, 16):
             for chunk in (1, 2, 4, 8):
-                for bpc in ((0, 8, 12) if persistent else (0,)):
-                    yield S.LaunchConfig(blocks_per_cu=bpc, chunk=chunk, persistent=persistent, kernel_store=store)
+                if chunk == 1 or 64 * chunk * bpc * num_cu <= units:
+                    yield S.LaunchConfig(blocks_per_cu=bpc, chunk=chunk, persistent=True, kernel_store=store)
+        if not persistent_only:
+            for chunk in (1, 2, 4, 8):
+                yield S.LaunchConfig(blocks_per_cu=0, chunk=chunk, persistent=False, kernel_store=store)
 
 
 def tune(model, params, dtau, D0, I0, rho11, ye0, e0, theta, repeats: int = 5, write: bool = True,
@@ -73,7 +80,7 @@ def tune(model, params, dtau, D0, I0, rho11, ye0, e0, theta, repeats: int = 5, w
     P = D0.shape[0]
     ws = S.Workspace(model, P, D0.device)
     out = S.alloc_outputs(model, P, D0.device)
-    cands = list(candidates(model, persistent_only))
+    cands = list(candidates(model, persistent_only, P, torch.cuda.get_device_properties(0).multi_processor_count))
 
     def run(L):
         S.solve(model, params, dtau, D0, I0, rho11, ye0, e0, theta, out=out, workspace=ws, launch=L)

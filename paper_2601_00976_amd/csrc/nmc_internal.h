@@ -141,8 +141,9 @@ struct LaunchPlan {
 // tables once: 4096 points (2 rounds) 226 against 233 us, 8192 points (4
 // rounds) 410 against 404, 16384 points 777 against 756; with linear-order
 // kernels 8192 points 662 against 675, 32768 points 2510 against 2467.
-// A grab takes at most 1/64 of a work-group's even share of the batch,
-// whatever chunk allows, so that no work-group is left with several units
+// A grab takes at most 1/64 of a work-group's even share of the batch (among
+// the caller's work-groups where blocks_per_cu sets them), whatever chunk
+// allows, so that no work-group is left with several units
 // when the others are done (4 pairs per grab: 4095 points 320 us, one: 95 us).
 constexpr int64_t kDirectRounds = 16, kDirectRoundsV = 4;
 inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, int num_cu,
@@ -151,7 +152,8 @@ inline LaunchPlan plan_launch(const nmc_launch& L, int64_t units, int per_cu, in
   if (L.persistent) {
     const int64_t slots = (int64_t)per_cu * num_cu;
     p.queue = L.blocks_per_cu > 0 || units > rounds * slots;
-    const int64_t share = p.queue ? units / (64 * slots) : 1;
+    const int64_t groups = L.blocks_per_cu > 0 ? (int64_t)L.blocks_per_cu * num_cu : slots;
+    const int64_t share = p.queue ? units / (64 * groups) : 1;
     if (p.chunk > share) p.chunk = share > 1 ? (int)share : 1;
   }
   p.grid = (units + p.chunk - 1) / p.chunk;
