@@ -690,8 +690,10 @@ struct VPairSolver {
   }
 };
 
+// one wave per SIMD where two or three species need more than 256 registers
+// (one species fits two: 16384 points 228 us so, 291 us with one register too many)
 template <int NS, bool COUPLED, bool PHI1, bool QUEUE>
-__global__ __launch_bounds__(kLanes, COUPLED ? 1 : 2) void fwd_vpair_kernel(FwdVArgs a) {
+__global__ __launch_bounds__(kLanes, COUPLED && NS > 1 ? 1 : 2) void fwd_vpair_kernel(FwdVArgs a) {
   __shared__ VPairLds<NS> S;
   load_model(a.mdl, a.theta, S.m);
   const int64_t pairs = (a.P + 1) / 2;
