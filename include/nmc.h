@@ -246,9 +246,8 @@ size_t nmc_kernel_store_bytes(const nmc_model* m, int64_t P);
  * matter right-hand side evaluated at the final moments, so lepton number and
  * energy balance hold to rounding.  `ws` is device workspace of at least
  * nmc_workspace_bytes(m, P) bytes, 256-byte aligned, not shared with a
- * concurrently running call.  `launch` may be NULL: persistent grid, one
- * point per grab, kernels on chip (the Python layer passes the autotuned
- * shape).  Returns NMC_E_UNSUPPORTED for grids other than 32 or 64 nodes. */
+ * concurrently running call.  `launch` may be NULL: persistent launch, one
+ * point or pair per grab, kernels on chip.  Returns NMC_E_UNSUPPORTED for grids other than 32 or 64 nodes. */
 int nmc_solve_batch(const nmc_model* m, const nmc_solver_params* prm, int64_t P, double dtau,
                     const nmc_batch_in* in, const nmc_batch_out* out, void* ws, size_t ws_bytes,
                     const nmc_launch* launch, void* stream);
@@ -257,8 +256,8 @@ int nmc_solve_batch(const nmc_model* m, const nmc_solver_params* prm, int64_t P,
  * allocate device memory: code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation.  It takes no workspace: the work-queue
  * counters live in a static device array of 4 MiB (one copy per device,
- * held until the process ends) that the call clears with a kernel before
- * its solve.  Inputs, outputs, launch and stream are as for
+ * held until the process ends); a call that takes its points from the queue
+ * clears them with a kernel before its solve.  Inputs, outputs, launch and stream are as for
  * nmc_solve_batch, with the same results; nothing is allocated or freed.
  * With launch->kernel_store = NMC_KERNELS_HBM the kernel store also lives
  * there, so P is limited to what fits (NMC_E_WORKSPACE beyond: 2 KiB of

@@ -21,8 +21,8 @@
 //     shares LDS with the Anderson history, which is dead between inner loops).
 // An inner iteration is ~690 instructions, 216 of them the multiply-adds of
 // the rates (with the whole rows of 32 columns and the vectors redistributed
-// ~890, 384 of them): 65536 points of the radial profile, two steps, 1180 us
-// (1459 us).  Half of the Anderson history stays in registers, as far as two
+// ~890, 384 of them): 65536 points of the radial profile, three steps, 1180
+// us (1459 us).  Half of the Anderson history stays in registers, as far as two
 // waves per SIMD leave room: 1149 us (4095 points 78 us, 82 us with all of it
 // in LDS).  Instruction issue at two waves per SIMD bounds large batches.
 // The row sums take their factors A e_q in the Q step.

@@ -8,7 +8,7 @@
 // of the point of half h.  A wave of the two-point kernel needs more than 256
 // registers for three species (one wave per SIMD, its dependent chains
 // exposed) and ~1120 instructions per inner iteration; a species' share fits
-// two waves per SIMD with its Anderson history in registers and takes ~470.
+// two waves per SIMD with its Anderson history in registers and takes ~430.
 // Through LDS go the lane's terms of the Gram sums of the Anderson step, the
 // moments of the pair partner and the convergence flags (two barriers per inner
 // iteration) and the lane's terms of the Eulerian integrals of the matter

@@ -138,9 +138,11 @@ struct LaunchPlan {
 // rounds) 434 against 450 us, 131072 points (64 rounds) 1726 against 1728 us.
 // The coupled O(v) kernel, alone on its SIMD, has no other wave to cover the
 // start of a work-group (model tables, inputs), and a queue's waves load the
-// tables once: 4096 points (2 rounds) 226 against 233 us, 8192 points (4
-// rounds) 410 against 404, 16384 points 777 against 756; with linear-order
-// kernels 8192 points 662 against 675, 32768 points 2510 against 2467.
+// tables once: 4096 points (2 rounds) 241 against 247 us, 8192 points (4
+// rounds) 415 against 414, 16384 points 774 against 775, 32768 points 1500
+// against 1488; with linear-order kernels 4096 points 401 against 406, 8192
+// points 683 against 677, 16384 points 1277 against 1266, 32768 points 2476
+// against 2441.
 // A grab takes at most 1/64 of a work-group's even share of the batch (among
 // the caller's work-groups where blocks_per_cu sets them), whatever chunk
 // allows, so that no work-group is left with several units

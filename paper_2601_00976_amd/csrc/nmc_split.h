@@ -40,8 +40,9 @@ __device__ __forceinline__ bool half_any(bool b, int h) {
 // b = exp(-|e_q - e_j| / (2T)).  CORE: b^2; otherwise signed as in
 // signed_contract (+b where j is the upper node); the values of
 // pair_tile_rows, the diagonal written as its callers do.  The work-group calls
-// it together, every wave with the same values.  2048 points of 0.13-0.2 MeV take
-// 128 us so, 435 us with every column regenerated in every inner iteration.
+// it together, every wave with the same values.  2048 points of 0.13-0.2 MeV took
+// 128 us so, 435 us with every column regenerated in every inner iteration, in
+// the signed form; the symmetric one, up to kSymBits, takes 4% less.
 template <bool CORE>
 __device__ __forceinline__ void cold_rows(SplitExp& E, int q, const ExpSplit& xs, double (&B)[16], double& k) {
   E.P2[q] = xs.P;
