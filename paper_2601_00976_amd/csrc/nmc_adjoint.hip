@@ -30,10 +30,11 @@
 //
 // Elimination (PointAdjoint): for points that the iteration does not settle
 // (slow convergence, a non-finite value) or whose grid spans too many powers
-// of two for it, in a second kernel with a work-group per point.  A is block diagonal over pair-coupled species: NES couples
-// the nodes of one species, pair processes couple a species with its partner,
-// so with species in id order the blocks are (nu_e, anti-nu_e) of size 64 and
-// nu_x of size 32.  Each block is factorised in registers, one wavefront per
+// of two for it, in a second kernel with a work-group per point.  A is block
+// diagonal over pair-coupled species: NES couples the nodes of one species,
+// pair processes couple a species with its partner, so with species in id
+// order the blocks are (nu_e, anti-nu_e) of size 64 and nu_x of size 32.  Each
+// block is factorised in registers, one wavefront per
 // point: lane r holds row r of A^T (column r of A) and the two right-hand
 // sides.  Block Gauss-Jordan elimination with 2 x 2 pivot blocks runs without
 // row exchanges, broadcasting the two pivot rows of each step through LDS.
@@ -46,8 +47,8 @@
 // pair eliminated one after the other / so: 8 points at 0.5 km, none settling,
 // 70 / 117 / 54; 65536 such points 1954 / 2831 / 2086; the whole profile at 0.5
 // km, 65536 points, 1946 / 959 / 829; 65536 points of 0.1-0.2 MeV 1946 / 2063 /
-// 1910; at 1e-3 km, all settling, 1951 / 305 / 303.  Where the caller asks for them, the per-point terms go to a
-// (P, nq + 2) array as well.
+// 1910; at 1e-3 km, all settling, 1951 / 305 / 303.  Where the caller asks for
+// them, the per-point terms go to a (P, nq + 2) array as well.
 #include "nmc_pair.h"
 
 namespace nmc {
@@ -797,8 +798,9 @@ void launch_adjoint_t(const AdjArgs& a, unsigned grid, unsigned grid_left, hipSt
 
 // Adds the work-groups' rows of partial sums to out, one work-group per
 // column: thread t adds rows t, t + 256, ... of the iteration in order, then
-// rows 16 t .. 16 t + 15 of the elimination where they are marked, then a fixed-shape tree over the 256 threads.
-// (One work-group for all 34 columns took 55 us.)
+// rows 16 t .. 16 t + 15 of the elimination where they are marked, then a
+// fixed-shape tree over the 256 threads.  (One work-group for all 34 columns
+// took 55 us.)
 __global__ __launch_bounds__(256) void reduce_partials(AdjArgs a, int rows, int rows_left, int ncol,
                                                        double* __restrict__ out) {
   __shared__ double red[256];
@@ -828,19 +830,12 @@ __global__ __launch_bounds__(256) void reduce_partials(AdjArgs a, int rows, int 
 hipError_t launch_adjoint(const AdjArgs& a, int nq, int ns, int num_cu, double* grad_theta, hipStream_t s) {
   if (nq != NQ || ns < 1 || ns > 3) return hipErrorInvalidValue;
   if (a.P == 0) return hipSuccess;
-  const int64_t pairs = (a.P + 1) / 2;
-  // two work-groups per SIMD stay resident; the elimination's unevenly loaded
-  // ones are twice as many in long batches (65536 points, all eliminated, 2086
-  // against 2151 us; 4096 points, none, 39.6 against 37.4 us)
-  int64_t grid = (int64_t)num_cu * 8, left = a.P > 4 * grid ? 2 * grid : grid;
-  if (grid > pairs) grid = pairs;
-  if (grid > kAdjPartials) grid = kAdjPartials;
-  if (left > a.P) left = a.P;
-  if (left > kAdjPartials) left = kAdjPartials;
+  const AdjGrid g = adj_grid(a.P, num_cu);
+  const unsigned grid = (unsigned)g.iterate, left = (unsigned)g.eliminate;
   switch (ns) {
-    case 1: launch_adjoint_t<1>(a, (unsigned)grid, (unsigned)left, s); break;
-    case 2: launch_adjoint_t<2>(a, (unsigned)grid, (unsigned)left, s); break;
-    default: launch_adjoint_t<3>(a, (unsigned)grid, (unsigned)left, s); break;
+    case 1: launch_adjoint_t<1>(a, grid, left, s); break;
+    case 2: launch_adjoint_t<2>(a, grid, left, s); break;
+    default: launch_adjoint_t<3>(a, grid, left, s); break;
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -361,14 +361,13 @@ struct AdjWs {
 };
 
 AdjWs adj_layout(const nmc_model* m, int64_t P) {
-  const size_t pairs = ((size_t)P + 1) / 2, most = (size_t)nmc::kAdjPartials;
-  const size_t row = ((size_t)m->host.nq + 2) * sizeof(double);
-  const size_t rows = pairs < most ? pairs : most, rows_left = (size_t)P < most ? (size_t)P : most;
+  const size_t pairs = ((size_t)P + 1) / 2, row = ((size_t)m->host.nq + 2) * sizeof(double);
+  const nmc::AdjGrid g = nmc::adj_grid(P, m->num_cu);
   AdjWs w;
   w.partial = kCounterBytes;
-  w.partial_left = w.partial + al256(rows * row);
-  w.had = w.partial_left + al256(rows_left * row);
-  w.left = w.had + most;
+  w.partial_left = w.partial + al256((size_t)g.iterate * row);
+  w.had = w.partial_left + al256((size_t)g.eliminate * row);
+  w.left = w.had + nmc::kAdjPartials;
   w.total = w.left + al256(pairs);
   return w;
 }

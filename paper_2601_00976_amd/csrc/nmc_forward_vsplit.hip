@@ -12,9 +12,8 @@
 // Through LDS go the lane's terms of the Gram sums of the Anderson step, the
 // moments of the pair partner and the convergence flags (two barriers per inner
 // iteration) and the lane's terms of the Eulerian integrals of the matter
-// update.  What
-// follows from them is computed by every wave from the same values, so the
-// waves take every branch together.  Sums over species add the lane's terms in
+// update.  What follows from them is computed by every wave from the same
+// values, so the waves take every branch together.  Sums over species add the lane's terms in
 // the two-point kernel's order and the sums of one species take its reduction
 // tree, so the two kernels give the same bits.
 #include "nmc_closure.h"

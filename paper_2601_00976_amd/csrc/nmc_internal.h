@@ -118,6 +118,23 @@ struct AdjArgs {
   uint8_t* left;       // per pair of points: bit h set where half h is left to the elimination
 };
 
+// Work-groups of the adjoint's two kernels.  Two per SIMD stay resident; the
+// elimination's unevenly loaded ones are twice as many in long batches (65536
+// points, all eliminated, 2086 against 2151 us; 4096 points, none, 39.6 against
+// 37.4 us).
+struct AdjGrid {
+  int64_t iterate, eliminate;
+};
+inline AdjGrid adj_grid(int64_t P, int num_cu) {
+  const int64_t pairs = (P + 1) / 2, resident = (int64_t)num_cu * 8;
+  AdjGrid g = {resident, P > 4 * resident ? 2 * resident : resident};
+  if (g.iterate > kAdjPartials) g.iterate = kAdjPartials;
+  if (g.eliminate > kAdjPartials) g.eliminate = kAdjPartials;
+  if (g.iterate > pairs) g.iterate = pairs;
+  if (g.eliminate > P) g.eliminate = P;
+  return g;
+}
+
 // How a solve over `units` (points, or pairs of points) is launched.
 struct LaunchPlan {
   int64_t grid;
